@@ -73,13 +73,17 @@ def parse():
     return ap.parse_args()
 
 
-GEMM_SRC = os.path.join(ROOT, "paper_2607_15810_amd", "csrc", "gemm.hip")
+GEMM_SRCS = [os.path.join(ROOT, "paper_2607_15810_amd", "csrc", f)
+             for f in ("gemm.hip", "gemm_panel.h", "gemm_args.h")]
 PROFILES = os.path.join(ROOT, "profiles")
 
 
 def gemm_source_hash():
-    with open(GEMM_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    d = hashlib.sha256()
+    for src in GEMM_SRCS:
+        with open(src, "rb") as f:
+            d.update(f.read())
+    return d.hexdigest()
 
 
 def measured_traffic(workload):

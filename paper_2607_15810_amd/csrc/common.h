@@ -280,11 +280,10 @@ bool gemm_wants_rq_sel(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks
 bool gemm_takes_bitmap(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
                        int32_t epilogue);
 // The number of amax partials the grouped GEMM's kernel on these sizes
-// writes (its grid; moe_w4a4_grouped_gemm_amax_count is an upper bound over
-// the kernels that could run); sfrag: the weights carry fragment-ordered
-// scales; bitmap: the residual comes in bitmap mode.
+// writes (its grid; moe_w4a4_grouped_gemm_amax_count is an upper bound);
+// bitmap: the residual comes in bitmap mode.
 int64_t gemm_amax_written(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
-                          int32_t epilogue, bool sfrag, bool bitmap);
+                          int32_t epilogue, bool bitmap);
 // moe_w4a4_grouped_gemm in bitmap mode: bitmap [K / 32] marks the selected
 // channels S in place of a list; the decode kernel writes S in ascending
 // order to sel_out.  QD_ERR_UNSUPPORTED where gemm_takes_bitmap is false.
@@ -293,19 +292,4 @@ qd_status grouped_gemm_bitmap(const qd_nvfp4 *a, const int32_t *row_token,
                               const qd_nvfp4 *w, const qd_nvfp4 *rq, const uint32_t *bitmap,
                               int32_t Ks, int32_t *sel_out, int32_t epilogue, void *out,
                               float *amax_partials, hipStream_t stream);
-// Bytes of the staged A operand the grouped GEMM reads on these sizes (the
-// tile kernel with the residual, gathered rows and the A-scale ring): codes
-// [K / 64][rows][32 B] then scales [K / 256][rows][16 B]; 0 where it reads the
-// gathered rows directly.  gemm_stage_reserve: an upper bound over K_s >= 1.
-int64_t gemm_stage_bytes(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
-                         int32_t epilogue);
-int64_t gemm_stage_reserve(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t epilogue);
-// moe_w4a4_grouped_gemm with the A operand also given staged (a_stg, as
-// gemm_stage_bytes describes; the kernel falls back to the gathered rows
-// where it does not use it).
-qd_status grouped_gemm_staged(const qd_nvfp4 *a, const int32_t *row_token,
-                              const int32_t *expert_offsets, int32_t E, int64_t rows,
-                              const qd_nvfp4 *w, const qd_nvfp4 *rq, const int32_t *sel_idx,
-                              int32_t Ks, const void *rq_sel, int32_t epilogue, void *out,
-                              float *amax_partials, const uint8_t *a_stg, hipStream_t stream);
 }  // namespace qdi

@@ -17,7 +17,8 @@
 // loads 16 contiguous code bytes (32 elements) of its row per 128-element K
 // chunk; k-step s of the chunk uses its elements 8s..8s+7.  A and B use the
 // same assignment, so each MFMA reduces over a permuted but common K subset.
-#include "common.h"
+#include "gemm_args.h"
+#include "gemm_panel.h"
 #include "lds_dma.h"
 #include "tile_sched.h"
 
@@ -25,66 +26,13 @@ namespace {
 
 using namespace qd;
 using namespace qdl;
-
-struct GemmArgs {
-  const uint8_t *a_codes;
-  const uint8_t *a_scales;
-  const float *a_gs;
-  const int32_t *row_token;
-  const int32_t *offsets;
-  int E;
-  int64_t rows;
-  const uint8_t *w_codes;
-  const uint8_t *w_scales;
-  const uint8_t *w_sfrag;  // optional: the weight scales in fragment order
-  const float *w_gs;
-  int N;
-  int K;
-  const uint8_t *r_codes;
-  const uint8_t *r_scales;
-  const float *r_gs;
-  const int32_t *sel;
-  int Ks;
-  const uint16_t *r_sel;   // f16 [a rows][ksa]: the residual at the selected channels
-  int ksa;                 // row length of r_sel (Ks rounded up to 16)
-  // bitmap mode (decode kernel only): r_bitmap [K / 32] marks S in place of
-  // sel, and the kernel lists S into sel_out
-  const uint32_t *r_bitmap;
-  int32_t *sel_out;
-  uint16_t *out;
-  float *amax_part;
-  int64_t amax_n;          // entries of amax_part (>= the grid; the rest are zeroed)
-  // per-expert channel sets (tile kernel only): S of expert e at
-  // sel + e * sel_stride, and r_sel indexed by grouped row instead of token
-  int sel_stride;
-  int rsel_rows;
-  // optional (tile kernel, gathered rows, A-scale ring on): the A operand
-  // staged by grouped row, stage-major -- codes [K / 64][rows][32 B], then
-  // the scales of four stages at a time [K / 256][rows][16 B] -- so that a
-  // tile's loads of one stage are contiguous
-  const uint8_t *a_stg;
-};
-
-// one maximum of |out| per workgroup into amax_part; workgroups also zero
-// the entries past the grid, so every one of the amax_n entries is written
-__device__ __forceinline__ void put_amax(const GemmArgs &p, float m) {
-  if (p.amax_part && threadIdx.x == 0) {
-    const int64_t g = (int64_t)gridDim.x * gridDim.y;
-    const int64_t b = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    p.amax_part[b] = m;
-    for (int64_t j = b + g; j < p.amax_n; j += g) p.amax_part[j] = 0.0f;
-  }
-}
+using namespace qdg;
 
 constexpr int BM = 64;
 constexpr int BN = 64;     // weight rows per workgroup (32 gate/up pairs for SwiGLU)
 
 __device__ __forceinline__ f32x4 mfma16(f16x8 a, f16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ uint32_t word_of(uint4 v, int s) {
-  return s == 0 ? v.x : (s == 1 ? v.y : (s == 2 ? v.z : v.w));
 }
 
 // find the (expert, first row) of m-tile mt; false if mt is past the last tile
@@ -852,53 +800,47 @@ __global__ __launch_bounds__(SK_THREADS) void gemm_skinny_kernel(GemmArgs p, int
 }
 
 // ---------------------------------------------------------------------------
-// Prefill-shaped grouped GEMM (hundreds of rows per expert): MFMA-bound.
+// Grouped GEMM with per-expert channel sets whose compact table (256 weight
+// rows x K_s) leaves the panel kernel (gemm_panel.h) no room for its ring:
+// 128 weight rows per tile here hold tables of up to about 440 channels.
 //
 //  * Workgroup tile 256 rows x 128 weight rows (SwiGLU: 64 gate rows and
 //    the matching 64 up rows); four waves in a 2 x 2 grid, each 128 x 64 on
-//    v_mfma_f32_32x32x16_f16 (4 x 2 fragments, 128 accumulators), two
-//    workgroups per CU.  Two waves share each SIMD, so one wave's decode
-//    VALU work runs under the other's MFMAs, and one workgroup's prologue
-//    and epilogue under the other's main loop.  A tile of at most 128 rows
-//    (an expert's remainder) splits its rows 64 / 64 between the wave rows
-//    instead, and fragments wholly past the expert's last row are skipped.
-//  * Operand codes are decoded to f16 in registers right before use.
+//    v_mfma_f32_32x32x16_f16 (4 x 2 fragments, 128 accumulators).  A tile of
+//    at most 128 rows (an expert's remainder) splits its rows 64 / 64 between
+//    the wave rows instead, and fragments wholly past the expert's last row
+//    are skipped.  Operand codes are decoded to f16 in registers right before
+//    use.
 //  * M-tiles never straddle experts.  The grid is an upper bound on the
 //    tile count; every workgroup derives the real tiles from the expert
 //    offsets, and tile indices run contiguously within an XCD (workgroups
 //    are dealt to the eight XCDs in turn), so the tiles in flight on an
 //    XCD share an expert's weights or a block of activation rows in its L2.
 //  * K goes through a ring of TL_NS LDS slots of 64-element stages filled
-//    by direct global->LDS loads (five per wave and stage) TL_NS - 1 stages
-//    ahead.  A wave reads a stage's raw codes and scales into registers one
-//    stage before it multiplies them: halfway through stage s it waits for
-//    stage s + 1, meets the other waves at a barrier, issues the loads of
-//    stage s + TL_NS - 1 into the slot of stage s - 1 (read during stage
-//    s - 2) and reads stage s + 1 while the MFMAs of stage s drain.
-//
-//  * RAC: the residual contraction runs over the selected channels alone,
-//    compacted.  While a stage is in LDS the workgroup copies the selected
-//    channels of its weight rows out of it, decoded to f16, into a compact
-//    [128 rows][K_s] LDS table; after the K loop the accumulators are
-//    rescaled by -s_dec_x / s_dec_r and the residual (compacted per token,
-//    f16, from the caller) is multiplied onto them against that table, so
-//    the epilogue's single scale -s_dec_r * s_dec_w yields
+//    by direct global->LDS loads TL_NS - 1 stages ahead.  A wave reads a
+//    stage's raw codes and scales into registers one stage before it
+//    multiplies them: halfway through stage s it waits for stage s + 1, meets
+//    the other waves at a barrier, issues the loads of stage s + TL_NS - 1
+//    into the slot of stage s - 1 (read during stage s - 2) and reads stage
+//    s + 1 while the MFMAs of stage s drain.
+//  * The residual: while a stage is in LDS the workgroup copies the selected
+//    channels of its weight rows out of it, decoded to f16, into the compact
+//    table; after the K loop the accumulators are rescaled by
+//    -s_dec_x / s_dec_r and the residual (compacted per row, f16, from the
+//    caller) is multiplied onto them against that table, so the epilogue's
+//    single scale -s_dec_r * s_dec_w yields
 //    s_dec_x s_dec_w acc - s_dec_r s_dec_w accr with one extra f32 rounding
-//    of the main sum.  A ring of three slots leaves LDS room for the table.
+//    of the main sum.
 //
 // Stage slot: A codes [8 fragments][64 lanes][16 B], B codes [4 fragments]
 // likewise, then A scale dwords [256 rows] and B scale dwords [128 rows].
 // Scale loads are the costly part of a stage (4 bytes per row, each in a
 // different scale line): the B scales come from the weights'
 // fragment-ordered copy when present (64 contiguous bytes per 16 rows), and
-// when LDS allows, the A scales of four stages at a time (16 contiguous
+// where LDS allows (grp), the A scales of four stages at a time (16 contiguous
 // bytes per row, one load per 16-byte piece) go into a two-slot ring of their
-// own.  With the four-slot ring the three stages between those loads issue a
-// one-line placeholder load instead, so every stage issues the same number of
-// loads; with the three-slot ring (RAC) the wait before each stage covers
-// every outstanding load, so those stages issue none, and the stage slot
-// drops its A-scale area (B scales right after the codes), which leaves the
-// A-scale ring room beside the compact table.
+// own; the stages between those loads issue none, the wait before each stage
+// covering every outstanding load, and the stage slot drops its A-scale area.
 // Lane l of a fragment holds row l % 32, elements 32 (l / 32) .. +31 of the
 // stage; MFMA k-step s (0..3) takes elements 8s .. 8s+7 of each half, for A
 // and B alike.
@@ -911,37 +853,23 @@ constexpr int TL_BCODE = 8192;
 constexpr int TL_ASCL = 12288;
 constexpr int TL_BSCL = 13312;
 constexpr int TL_STAGE = 13824;
-constexpr int TL_BSCL_G = 12288;         // three-slot ring with the A-scale ring
+constexpr int TL_BSCL_G = 12288;         // with the A-scale ring
 constexpr int TL_STAGE_G = 12800;
 constexpr int TL_PAD = 4;                // f16 columns past each compact table row
 constexpr int TL_EMAX = 1024;            // experts handled by the tile scan (4 per thread)
 constexpr int TL_LDS_MAX = 160 * 1024 - 1024;   // dynamic LDS beside the static arrays
 
-// ring depth: four slots, or three with RAC, which leaves LDS room for the
-// compact table (three slots measured 1-3% slower without RAC)
-__host__ __device__ constexpr int tl_ns(bool rac) { return rac ? 3 : 4; }
+constexpr int TL_NS = 3;                 // ring depth
 // stage slot size and the B-scale offset inside it (grp: the A-scale ring is on)
-__host__ __device__ constexpr int tl_stage(bool rac, bool grp) {
-  return tl_ns(rac) == 3 && grp ? TL_STAGE_G : TL_STAGE;
-}
-__host__ __device__ constexpr int tl_bscl(bool rac, bool grp) {
-  return tl_ns(rac) == 3 && grp ? TL_BSCL_G : TL_BSCL;
-}
-// LDS: ring, then (RAC) the compact weight table [128][ksa + TL_PAD] f16 and
-// the selected channels [ksa], then (grp) the A-scale ring
-__host__ __device__ inline int tl_lds_bytes(bool rac, int ksa, bool grp) {
-  return tl_ns(rac) * tl_stage(rac, grp) + (rac ? TL_N * (ksa + TL_PAD) * 2 + ksa * 4 : 0);
+__host__ __device__ constexpr int tl_stage(bool grp) { return grp ? TL_STAGE_G : TL_STAGE; }
+__host__ __device__ constexpr int tl_bscl(bool grp) { return grp ? TL_BSCL_G : TL_BSCL; }
+// LDS: ring, then the compact weight table [128][ksa + TL_PAD] f16 and the
+// selected channels [ksa], then (grp) the A-scale ring
+__host__ __device__ inline int tl_lds_bytes(int ksa, bool grp) {
+  return TL_NS * tl_stage(grp) + TL_N * (ksa + TL_PAD) * 2 + ksa * 4;
 }
 constexpr int TL_AGRP = 2 * TL_M * 16;   // the A-scale ring: 2 slots x 256 rows x 16 B
 constexpr int TL_LDS_2WG = TL_LDS_MAX / 2;   // two workgroups per CU
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ f32x16 mfma32(f16x8 a, f16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-}
 
 // the tile's weight row tb (0..127): for SwiGLU, fragments (32 rows) 0, 1
 // are gate rows and 2, 3 the matching up rows
@@ -1013,20 +941,9 @@ __device__ __forceinline__ void tl_stage(const TlRaw &R, f32x16 (&acc)[4][2], in
   }
 }
 
-// silu(g) * u from f32 g and u: exp on the transcendental unit and one
-// reciprocal (a few f32 ulp, far inside the bf16 rounding that follows)
-__device__ __forceinline__ float swiglu_fast(float g, float u) {
-  const float e = __builtin_amdgcn_exp2f(-g * 1.4426950408889634f);
-  return g * __builtin_amdgcn_rcpf(1.0f + e) * u;
-}
-
-// DENSE (with RAC): the residual as a second pass over K on the masked
-// residual codes (for K_s too large for the compact table)
-template <bool GATHER, bool RAC, int EPI, bool DENSE = false>
+template <bool GATHER, int EPI>
 __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, int ntn, int grp) {
-  static_assert(RAC || !DENSE, "the dense residual mode needs RAC");
-  constexpr bool CMP = RAC && !DENSE;      // compact residual table
-  constexpr int NS = tl_ns(CMP);
+  constexpr int NS = TL_NS;
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int sh_w[4];
   __shared__ int sh_t[4];
@@ -1064,54 +981,25 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
     const int bsstep = sfrag ? 64 : 4;
     const int nst = K / TL_K;
     // stage slots, and the A-scale ring (grp) after them and the compact table
-    const int tls = tl_stage(CMP, grp != 0), bsc = tl_bscl(CMP, grp != 0);
-    const uint32_t agrp = lds0 + (uint32_t)tl_lds_bytes(CMP, CMP ? p.ksa : 0, grp != 0);
+    const int tls = tl_stage(grp != 0), bsc = tl_bscl(grp != 0);
+    const uint32_t agrp = lds0 + (uint32_t)tl_lds_bytes(p.ksa, grp != 0);
     const uint32_t oag = arow(64 * w + lane) * (uint32_t)kb16;
-    // the staged A operand (first pass only): row offsets within a stage's
-    // [rows][32 B] and a group's [rows][16 B] record
-    bool stg = GATHER && grp && p.a_stg != nullptr;
-    auto srow = [&](int r) __attribute__((always_inline)) -> uint32_t {
-      return (uint32_t)(row0 + (r < nrows ? r : 0));
-    };
-    const uint32_t os0 = srow(64 * w + (lane & 31)) * 32u + hb;
-    const uint32_t os1 = srow(64 * w + 32 + (lane & 31)) * 32u + hb;
-    const uint32_t osg = srow(64 * w + lane) * 16u;
-    // five loads per wave and stage, four between A-scale groups with the
-    // three-slot ring (waves 0 / 2 and 1 / 3 load the same B scale half:
-    // equal bytes to equal places)
-    // the A operand of the pass: the activations, then (DENSE) the masked
-    // residual, same layout
-    const uint8_t *a_cod = p.a_codes, *a_scl = p.a_scales;
+    // five loads per wave and stage, four between A-scale groups (waves 0 / 2
+    // and 1 / 3 load the same B scale half: equal bytes to equal places)
     auto issue = [&](int s, int q) __attribute__((always_inline)) {
       s = min(s, nst - 1);
       const uint32_t sb = uni(lds0 + q * tls);
-      const uint8_t *ac = uni_ptr(a_cod + s * 32), *as_ = uni_ptr(a_scl + s * 4);
+      const uint8_t *ac = uni_ptr(p.a_codes + s * 32), *as_ = uni_ptr(p.a_scales + s * 4);
       const uint8_t *bc = uni_ptr(wc + s * 32), *bs_ = uni_ptr(ws + s * bsstep);
-      if (stg) {
-        const uint8_t *sc = uni_ptr(p.a_stg + (int64_t)s * p.rows * 32);
-        dma16s(sc, os0, sb + TL_ACODE + (2 * w) * 1024);
-        dma16s(sc, os1, sb + TL_ACODE + (2 * w + 1) * 1024);
-      } else {
-        dma16s(ac, oa0, sb + TL_ACODE + (2 * w) * 1024);
-        dma16s(ac, oa1, sb + TL_ACODE + (2 * w + 1) * 1024);
-      }
+      dma16s(ac, oa0, sb + TL_ACODE + (2 * w) * 1024);
+      dma16s(ac, oa1, sb + TL_ACODE + (2 * w + 1) * 1024);
       dma16s(bc, ob, sb + TL_BCODE + w * 1024);
       if (grp) {
         // stage 4G brings group G's A scales (rows 64 w .. 64 w + 63, 16 B
-        // each) into ring slot G % 2; with four slots other stages load one
-        // line (the group scales of the wave's first row: a different line
-        // per workgroup, never one line for the whole chip) into the unused
-        // A-scale area of their stage slot
-        if ((s & 3) == 0) {
-          if (stg)
-            dma16s(uni_ptr(p.a_stg + (int64_t)p.rows * kb2 + (int64_t)(s >> 2) * p.rows * 16), osg,
-                   uni(agrp + ((s >> 2) & 1) * (TL_AGRP / 2) + w * 1024));
-          else
-            dma16s(uni_ptr(a_scl + (s >> 2) * 16), oag,
-                   uni(agrp + ((s >> 2) & 1) * (TL_AGRP / 2) + w * 1024));
-        }
-        else if constexpr (NS != 3)
-          dma16s(uni_ptr(a_scl + (s >> 2) * 16), uni(oag), sb + TL_ASCL);
+        // each) into ring slot G % 2
+        if ((s & 3) == 0)
+          dma16s(uni_ptr(p.a_scales + (s >> 2) * 16), oag,
+                 uni(agrp + ((s >> 2) & 1) * (TL_AGRP / 2) + w * 1024));
       } else {
         dma4s(as_, oas, sb + TL_ASCL + w * 256);
       }
@@ -1125,29 +1013,23 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
     const int astr = grp ? 16 : 4;
     const float a_dec = p.a_gs[1], sw = p.w_gs[2 * e + 1];
     float alpha = a_dec * sw;
-    // RAC: acc -> acc * inv_c + accr, then alpha = -s_dec_r * s_dec_w.  A
-    // residual whose tensor scale is below 2^-60 of the activation's is
-    // left out (its share of any output is far below f32 resolution).
-    float inv_c = 0.0f;
-    bool res_on = false;
-    const int ksa = CMP ? p.ksa : 0, ksp = ksa + TL_PAD;
+    // acc -> acc * inv_c + accr, then alpha = -s_dec_r * s_dec_w.  A residual
+    // whose tensor scale is below 2^-60 of the activation's is left out (its
+    // share of any output is far below f32 resolution).
+    const int ksa = p.ksa, ksp = ksa + TL_PAD;
     unsigned char *bres = lds + NS * tls;
     int32_t *sel_l = reinterpret_cast<int32_t *>(bres + TL_N * ksp * 2);
-    if (RAC) {
-      const float r_dec = p.r_gs[1];
-      inv_c = -(a_dec / r_dec);
-      res_on = r_dec > 0.0f && fabsf(inv_c) <= 0x1p60f;
-      if (res_on) alpha = -r_dec * sw;
-      if constexpr (CMP) {
-        for (int i = tid; i < ksa; i += TL_THREADS)
-          sel_l[i] = i < p.Ks ? p.sel[(int64_t)e * p.sel_stride + i] : 0;
-        // pad columns of the compact table are zero (the residual's are too)
-        const int pad = ksa - p.Ks;
-        for (int i = tid; i < TL_N * pad; i += TL_THREADS)
-          *reinterpret_cast<_Float16 *>(bres + ((i / pad) * ksp + p.Ks + i % pad) * 2) =
-              (_Float16)0.0f;
-      }
-    }
+    const float r_dec = p.r_gs[1];
+    const float inv_c = -(a_dec / r_dec);
+    const bool res_on = r_dec > 0.0f && fabsf(inv_c) <= 0x1p60f;
+    if (res_on) alpha = -r_dec * sw;
+    for (int i = tid; i < ksa; i += TL_THREADS)
+      sel_l[i] = i < p.Ks ? p.sel[(int64_t)e * p.sel_stride + i] : 0;
+    // pad columns of the compact table are zero (the residual's are too)
+    const int pad = ksa - p.Ks;
+    for (int i = tid; i < TL_N * pad; i += TL_THREADS)
+      *reinterpret_cast<_Float16 *>(bres + ((i / pad) * ksp + p.Ks + i % pad) * 2) =
+          (_Float16)0.0f;
     const int wm = w & 1, wn = w >> 1;
     const bool wide = nrows > 128;
     const int fa0 = wide ? 4 * wm : 2 * wm;
@@ -1170,7 +1052,7 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
       // RAC: the tokens of this lane's residual rows, loaded before the K
       // loop so the residual steps after it wait for one load, not two
       int32_t tkr[MTV > 0 ? MTV : 1];
-      if constexpr (CMP && MTV > 0) {
+      if constexpr (MTV > 0) {
 #pragma unroll
         for (int i = 0; i < MTV; ++i) {
           const int rr = 32 * (fa0 + i) + (lane & 31);
@@ -1192,7 +1074,7 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
           if constexpr (MTV > 0)
             tl_read<MTV>(Rn, lds + ((s + 1) % NS) * tls, a_src(s + 1), astr, bsc, fa0, fb0, fbs,
                          lane);
-          if constexpr (CMP) {
+          {
             // selected channels of stage s (slot s % NS holds it until the
             // next barrier): decoded weight values into the compact table
             // (the hardware FP4 conversion with a power-of-two scale and one
@@ -1222,11 +1104,11 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
 #pragma unroll
         for (int t = 0; t < NS - 1; ++t) issue(t, t);
         // stage 0 has landed once at most stage NS - 2's loads are in flight
-        // (three slots with the A-scale ring: stage 1 issues four)
-        if (NS == 3 && grp) wait_vm<4>();
+        // (with the A-scale ring: stage 1 issues four)
+        if (grp) wait_vm<4>();
         else wait_vm<(NS - 2) * 5>();
         __syncthreads();
-        if constexpr (CMP) nsel = nk < p.Ks ? (int)uni((uint32_t)sel_l[nk]) : 0x7fffffff;
+        nsel = nk < p.Ks ? (int)uni((uint32_t)sel_l[nk]) : 0x7fffffff;
         if constexpr (MTV > 0) tl_read<MTV>(R0, lds, a_src(0), astr, bsc, fa0, fb0, fbs, lane);
         for (int s = 0; s < nst; s += 2) {     // nst is even
           body(R0, R1, s);
@@ -1235,26 +1117,7 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
         wait_vm<0>();
       };
       kpass();
-      if constexpr (DENSE) {
-        // the residual: acc -> acc * inv_c, then a second pass over K with
-        // the masked residual codes as the A operand (zero outside S), so the
-        // epilogue's scale -s_dec_r * s_dec_w yields
-        // s_dec_x s_dec_w acc - s_dec_r s_dec_w accr
-        if (res_on) {
-          __syncthreads();                     // every wave is done with the ring
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-              for (int q = 0; q < 16; ++q) acc[i][j][q] *= inv_c;
-          a_cod = p.r_codes;
-          a_scl = p.r_scales;
-          stg = false;
-          kpass();
-        }
-      }
-      if constexpr (CMP) {
+      {
         if (res_on) {
           __syncthreads();                     // the compact table is complete
           if constexpr (MTV > 0) {
@@ -1350,444 +1213,6 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
   put_amax(p, m);
 }
 
-// ---------------------------------------------------------------------------
-// Prefill-shaped grouped GEMM with wide tiles (hundreds of rows per expert).
-//
-// What bounds the exact-NVFP4 prefill GEMM on gfx950 is VALU work per MFMA,
-// not bytes: every operand fragment is decoded in registers (8 VALU ops per
-// 32x16 fragment), so the decode cost per MFMA falls with the wave tile.
-//
-//  * Workgroup tile 256 rows x 256 weight rows (SwiGLU: 128 gate rows and
-//    the matching 128 up rows), four waves in a 2 x 2 grid, each 128 x 128
-//    on v_mfma_f32_32x32x16_f16 (4 x 4 fragments, 256 accumulators): one
-//    wave per SIMD, 8 fragment decodes per 16 MFMAs.  M-tiles never straddle
-//    experts; a tile of at most 128 rows splits them 64 / 64 between the
-//    wave rows, and fragments wholly past the expert's last row are skipped.
-//  * K in stages of 128 elements through a two-slot LDS ring filled by direct
-//    global->LDS loads: every load brings 16 rows x 64 contiguous bytes, the
-//    16-byte pieces of a row placed by a row-dependent XOR so the fragment
-//    reads are free of bank conflicts.  A wave reads a stage's raw codes and
-//    scales into registers one stage before it multiplies them: halfway
-//    through stage s it waits for stage s + 1, meets the other waves at the
-//    one barrier of the stage, issues the loads of stage s + 2 into the slot
-//    stage s occupied and reads stage s + 1 while the MFMAs of stage s drain.
-//  * Inside a stage lane (row r, half h) owns elements 64 h .. 64 h + 63;
-//    MFMA k-step s (0..7) takes elements 8 s .. 8 s + 7 of each half, for A
-//    and B alike (a common permutation of K).
-//  * Scales: the weights' from their fragment-ordered copy (128 contiguous
-//    bytes per 16 rows and stage), the activations' 16 bytes per row every
-//    second stage into a ring of their own; odd stages issue a one-line
-//    placeholder load instead, so every stage issues ten loads per wave.
-//  * Persistent: one workgroup per CU walks a static list of tiles; halfway
-//    through the last two stages of a tile it issues the first two stages
-//    of its next tile, so the next tile's loads overlap the epilogue.
-//  * Plain W4A4 only (no fused residual): with the RAC residual fused, the
-//    compact weight table and the residual operand do not fit beside the
-//    256 accumulators of this tile shape, and the 256 x 128 tile kernel
-//    below takes those problems.
-constexpr int TW_THREADS = 256;
-constexpr int TW_M = 256;
-constexpr int TW_N = 256;
-constexpr int TW_K = 128;
-constexpr int TW_ACODE = 0;               // [8 fragments][2 halves][64 lanes][16 B]
-constexpr int TW_BCODE = 16384;          // the same for the 256 weight rows
-constexpr int TW_BSCL = 32768;           // [16 row groups][128 B]
-constexpr int TW_STAGE = 34816;
-constexpr int TW_ASCL = 2 * TW_STAGE;    // A-scale ring [2 slots][256 rows][16 B]
-constexpr int TW_DUMMY = TW_ASCL + 8192; // target of the odd stages' placeholder load
-constexpr int TW_TOK = TW_DUMMY + 1024;  // gathered rows: tokens of the current and next tile [2][256]
-constexpr int TW_SCHED = TW_TOK + 2 * TW_M * 4;   // the tile schedule: two int arrays [E + 1]
-constexpr int TW_LOADS = 10;             // loads per wave and stage
-__host__ __device__ inline int tw_lds_bytes(int E) { return TW_SCHED + 2 * (E + 1) * 4; }
-
-// 16-byte piece p of tile row ri (0..15 within a 16-row load) sits at piece
-// p ^ tw_swz(ri) of the row's 64-byte LDS record
-__device__ __forceinline__ int tw_swz(int ri) { return ((ri >> 1) ^ (ri >> 2)) & 3; }
-
-// the tile's weight row tb (0..255): for SwiGLU wave column wn = tb / 128
-// holds gate rows (fragments 0, 1) and the matching up rows (2, 3)
-template <int EPI>
-__device__ __forceinline__ int wide_wrow(int tb, int nt, int N) {
-  if (EPI == QD_EPI_SWIGLU) {
-    const int wn = tb >> 7, f = (tb >> 5) & 3, r = tb & 31;
-    return (f < 2 ? 0 : (N >> 1)) + nt * 128 + wn * 64 + (f & 1) * 32 + r;
-  }
-  return nt * TW_N + tb;
-}
-
-// a wave's raw operands of one stage, A fragments fa0 .. fa0 + 3 and B
-// fragments fb0 .. fb0 + 3: the codes of k-steps 0..3 with the scale dwords
-// (read halfway through the previous stage) and the codes of k-steps 4..7
-// (read at the start of the stage), so that only half a stage of codes is
-// held twice
-struct TwLo {
-  uint4 a[4], b[4];
-  uint32_t as[4], bs[4];
-};
-struct TwHi {
-  uint4 a[4], b[4];
-};
-
-// LDS byte offset of lane (r, h)'s piece c (0, 1) of fragment f in a code area
-__device__ __forceinline__ int tw_frag_off(int f, int lane, int c) {
-  const int r = lane & 31, h = lane >> 5, ri = r & 15;
-  return ((2 * f + (r >> 4)) * 64 + 4 * ri + ((2 * h + c) ^ tw_swz(ri))) * 16;
-}
-
-template <int MTV>
-__device__ __forceinline__ void tw_read_lo(TwLo &R, const unsigned char *sl, const unsigned char *ascl,
-                                           int s, int fa0, int fb0, int lane) {
-  const int r = lane & 31, h = lane >> 5;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int fb = fb0 + j;
-    R.b[j] = *reinterpret_cast<const uint4 *>(sl + TW_BCODE + tw_frag_off(fb, lane, 0));
-    R.bs[j] = *reinterpret_cast<const uint32_t *>(sl + TW_BSCL + (2 * fb + (r >> 4)) * 128 +
-                                                  (16 * h + (r & 15)) * 4);
-  }
-#pragma unroll
-  for (int i = 0; i < MTV; ++i) {
-    const int fa = fa0 + i;
-    R.a[i] = *reinterpret_cast<const uint4 *>(sl + TW_ACODE + tw_frag_off(fa, lane, 0));
-    R.as[i] = *reinterpret_cast<const uint32_t *>(ascl + (32 * fa + r) * 16 + (s & 1) * 8 + 4 * h);
-  }
-}
-
-template <int MTV>
-__device__ __forceinline__ void tw_read_hi(TwHi &R, const unsigned char *sl, int fa0, int fb0,
-                                           int lane) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    R.b[j] = *reinterpret_cast<const uint4 *>(sl + TW_BCODE + tw_frag_off(fb0 + j, lane, 1));
-#pragma unroll
-  for (int i = 0; i < MTV; ++i)
-    R.a[i] = *reinterpret_cast<const uint4 *>(sl + TW_ACODE + tw_frag_off(fa0 + i, lane, 1));
-}
-
-// k-steps 4c .. 4c + 3 of a stage from codes ca / cb and the scale dwords
-template <int MTV>
-__device__ __forceinline__ void tw_half(const uint4 (&ca)[4], const uint4 (&cb)[4],
-                                        const uint32_t (&as)[4], const uint32_t (&bs)[4],
-                                        f32x16 (&acc)[4][4], int c) {
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const bool hi = (q >> 1) != 0;
-    f16x8 bf[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) bf[j] = decode8_sel(word_of(cb[j], q), scale_pair_of(bs[j], c), hi);
-#pragma unroll
-    for (int i = 0; i < MTV; ++i) {
-      const f16x8 af = decode8_sel(word_of(ca[i], q), scale_pair_of(as[i], c), hi);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = mfma32(af, bf[j], acc[i][j]);
-    }
-  }
-}
-
-// Tiles of the persistent wide kernel: m-tile mt of the experts' TW_M-row
-// tiles (M-tiles never straddle experts), weight-row tile nt.
-struct TwTile {
-  int e, row0, nrows, nt;
-};
-
-// The tile schedule in LDS: offs [E + 1] row offsets, mpre [E + 1] the
-// m-tiles of the experts before e.  Tiles t = mt * ntn + nt; XCD x = b % 8
-// owns the contiguous range [x * per, x * per + per) and its workgroups
-// (b / 8) take every (G / 8)-th tile of it, so the tiles in flight on an XCD
-// share an expert's weights or a block of activation rows in its L2.
-// Tiles are visited in increasing order, so an expert cursor advances by a
-// wave ballot over the next 64 experts.
-__device__ __forceinline__ TwTile tw_locate(const int32_t *offs, const int32_t *mpre, int E,
-                                            int ntn, int t, int &ecur, int lane) {
-  const int mt = t / ntn;
-  for (;;) {
-    const int c = (int)uni((uint32_t)ecur) + 1 + lane;
-    const bool le = c <= E && mpre[c] <= mt;
-    const uint64_t bal = __ballot(le);
-    const int adv = __popcll(bal);
-    ecur += adv;
-    if (adv < 64) break;
-  }
-  TwTile tl;
-  tl.e = (int)uni((uint32_t)ecur);
-  tl.row0 = (int)uni((uint32_t)(offs[tl.e] + (mt - mpre[tl.e]) * TW_M));
-  tl.nrows = (int)uni((uint32_t)min(TW_M, offs[tl.e + 1] - tl.row0));
-  tl.nt = (int)uni((uint32_t)(t - mt * ntn));
-  return tl;
-}
-
-template <bool GATHER, int EPI>
-__global__ __launch_bounds__(TW_THREADS, 1) void gemm_wide_kernel(GemmArgs p, int ntn) {
-  extern __shared__ __align__(16) unsigned char lds[];
-  __shared__ int sh_w[4];
-  __shared__ float red[16];
-  const int tid = threadIdx.x, lane = tid & 63, w = (int)uni((uint32_t)tid >> 6);
-  const int K = p.K, N = p.N, E = p.E;
-  const int64_t kb2 = K >> 1, kb16 = K >> 4;
-  const int nst = K / TW_K;
-  int32_t *offs = reinterpret_cast<int32_t *>(lds + TW_SCHED);
-  int32_t *mpre = offs + (E + 1);
-  int32_t *tokb = reinterpret_cast<int32_t *>(lds + TW_TOK);
-  const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
-  const uint32_t tok0 = lds0 + (uint32_t)TW_TOK;
-
-  // ---- the schedule: row offsets and m-tile prefix counts (four experts
-  // per thread, E <= 1024)
-  {
-    int cnt[4], tsum = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = 4 * tid + q;
-      int o0 = 0, o1 = 0;
-      if (e <= E) {
-        o0 = p.offsets ? p.offsets[e] : (e == 0 ? 0 : (int)p.rows);
-        offs[e] = o0;
-      }
-      if (e < E) o1 = p.offsets ? p.offsets[e + 1] : (int)p.rows;
-      cnt[q] = e < E ? (max(o1 - o0, 0) + TW_M - 1) / TW_M : 0;
-      tsum += cnt[q];
-    }
-    int xs = tsum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(xs, o, 64);
-      if (lane >= o) xs += y;
-    }
-    if (lane == 63) sh_w[w] = xs;
-    __syncthreads();
-    int base = xs - tsum;
-    for (int ww = 0; ww < w; ++ww) base += sh_w[ww];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = 4 * tid + q;
-      if (e <= E) mpre[e] = base;
-      base += cnt[q];
-    }
-  }
-  const float a_dec = p.a_gs[1];
-  __syncthreads();
-  const int T = (int)uni((uint32_t)mpre[E]) * ntn;
-  const int G = gridDim.x, nsl = G >> 3, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int per = (T + 7) >> 3;
-  const int t_end = min(T, (xcd + 1) * per);
-  int t = xcd * per + slot;
-  int ecur = 0;
-  float vmax = 0.0f;
-
-  const int wm = w & 1, wn = w >> 1, fb0 = 4 * wn;
-  const int ri = lane >> 2;
-  const uint32_t pc = 16u * (uint32_t)((lane & 3) ^ tw_swz(ri));
-  // per-lane load offsets of a tile: wave w loads A and B fragments 2w,
-  // 2w + 1 (two 16-row halves each), lane l row l / 4 of the half, piece
-  // (l % 4) ^ swz; B rows of one load are consecutive weight rows (one
-  // per-lane offset, a uniform row per load); B scales (fragment-ordered):
-  // load w & 1 covers tile row groups 8 (w & 1) .. + 7, lane l group
-  // 8 (w & 1) + l / 8, piece l % 8 (waves 2, 3 repeat waves 0, 1: equal
-  // bytes to equal places); A scales: rows 64 w + l, 16 bytes every second
-  // stage
-  struct Offs {
-    uint32_t oa[4], obs, oag;
-  };
-  const uint32_t ob = (uint32_t)ri * (uint32_t)kb2 + pc;
-  const int bg = 8 * (w & 1) + (lane >> 3);
-  auto b_off = [&](const TwTile &tl) __attribute__((always_inline)) -> Offs {
-    Offs o;
-    o.obs = (uint32_t)((wide_wrow<EPI>(16 * bg, tl.nt, N) >> 4) * (K >> 8)) * 256u +
-            16u * (uint32_t)(lane & 7);
-    if (!GATHER) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int r = 32 * (2 * w + (j >> 1)) + 16 * (j & 1) + ri;
-        o.oa[j] = (uint32_t)(tl.row0 + (r < tl.nrows ? r : 0)) * (uint32_t)kb2 + pc;
-      }
-      const int r = 64 * w + lane;
-      o.oag = (uint32_t)(tl.row0 + (r < tl.nrows ? r : 0)) * (uint32_t)kb16;
-    }
-    return o;
-  };
-  // gathered rows: the tile's 256 row tokens go to LDS by direct loads
-  // (wave w: rows 64 w + l; rows past the tile repeat its first row), so
-  // neither the next tile's load offsets nor the residual rows wait on a
-  // load the compiler tracks
-  auto tok_dma = [&](const TwTile &tl, int buf) __attribute__((always_inline)) {
-    const int r = 64 * w + lane;
-    dma4s(uni_ptr(p.row_token), (uint32_t)(tl.row0 + (r < tl.nrows ? r : 0)) * 4u,
-          uni(tok0 + buf * (TW_M * 4) + w * 256));
-  };
-  // the per-lane A offsets from the tokens in LDS buffer buf
-  auto a_off_tok = [&](Offs &o, int buf) __attribute__((always_inline)) {
-    const int32_t *tb = tokb + buf * TW_M;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      o.oa[j] = (uint32_t)tb[32 * (2 * w + (j >> 1)) + 16 * (j & 1) + ri] * (uint32_t)kb2 + pc;
-    o.oag = (uint32_t)tb[64 * w + lane] * (uint32_t)kb16;
-  };
-  auto issue = [&](const TwTile &tl, const Offs &o, int s, int q, int apar)
-                   __attribute__((always_inline)) {
-    const uint32_t sb = uni(lds0 + q * TW_STAGE);
-    const uint8_t *ac = uni_ptr(p.a_codes + s * 64);
-    const uint8_t *bc = uni_ptr(p.w_codes + (int64_t)tl.e * N * kb2 + s * 64);
-    const uint8_t *wsf = uni_ptr(p.w_sfrag + (int64_t)tl.e * N * kb16);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dma16s(ac, o.oa[j], sb + TW_ACODE + (4 * w + j) * 1024);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      dma16s(uni_ptr(bc + (int64_t)wide_wrow<EPI>(32 * (2 * w + (j >> 1)) + 16 * (j & 1), tl.nt, N) * kb2),
-             ob, sb + TW_BCODE + (4 * w + j) * 1024);
-    dma16s(uni_ptr(wsf + (s >> 1) * 256 + (s & 1) * 128), o.obs, sb + TW_BSCL + (w & 1) * 1024);
-    if ((s & 1) == 0)
-      dma16s(uni_ptr(p.a_scales + (s >> 1) * 16), o.oag,
-             uni(lds0 + TW_ASCL + ((apar + (s >> 1)) & 1) * 4096 + w * 1024));
-    else
-      dma16s(uni_ptr(p.a_scales + (s >> 1) * 16), uni(o.oag), uni(lds0 + TW_DUMMY));
-  };
-
-  TwTile cur{};
-  bool have = t < t_end;
-  Offs oc{};
-  int apar = 0;          // A-scale ring slot of the tile's first stage pair
-  int tbuf = 0;          // token buffer of the current tile
-  if (have) {
-    cur = tw_locate(offs, mpre, E, ntn, t, ecur, lane);
-    oc = b_off(cur);
-    if (GATHER) {
-      tok_dma(cur, 0);
-      wait_vm<0>();
-      __syncthreads();
-      a_off_tok(oc, 0);
-    }
-    issue(cur, oc, 0, 0, apar);
-    issue(cur, oc, 1, 1, apar);
-  }
-  while (have) {
-    const int e = cur.e, nt = cur.nt, row0 = cur.row0, nrows = cur.nrows;
-    const int tn = t + nsl;
-    const bool hn = tn < t_end;
-    TwTile nx{};
-    if (hn) nx = tw_locate(offs, mpre, E, ntn, tn, ecur, lane);
-    Offs on{};           // the next tile's load offsets (set in the last stages)
-    const int apar_n = (apar + (nst >> 1)) & 1;
-    const float sw = p.w_gs[2 * e + 1];
-    const bool wide = nrows > 128;
-    const int fa0 = wide ? 4 * wm : 2 * wm;
-    const int mtv = wide ? min(max((nrows - 128 * wm + 31) >> 5, 0), 4)
-                         : min(max((nrows - 64 * wm + 31) >> 5, 0), 2);
-    auto a_src = [&](int s) __attribute__((always_inline)) -> const unsigned char * {
-      return lds + TW_ASCL + ((apar + (s >> 1)) & 1) * 4096;
-    };
-
-    auto run = [&](auto mtv_c) __attribute__((always_inline)) {
-      constexpr int MTV = decltype(mtv_c)::value;
-      f32x16 acc[4][4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;
-      TwLo L0, L1;
-      // stage 0 of this tile: issued during the previous tile (or above)
-      wait_vm<TW_LOADS>();
-      __syncthreads();
-      // the next tile's tokens into the buffer the previous tile used (every
-      // wave is past it now); landed by the first mid-stage wait
-      if (GATHER && hn) tok_dma(nx, tbuf ^ 1);
-      if constexpr (MTV > 0) tw_read_lo<MTV>(L0, lds, a_src(0), 0, fa0, fb0, lane);
-      // one stage; TAIL: one of the last two, whose mid issues the next
-      // tile's first stages instead of this tile's
-      auto body = [&](const TwLo &Lc, TwLo &Ln, int s, auto tail_c) __attribute__((always_inline)) {
-        constexpr bool TAIL = decltype(tail_c)::value;
-        TwHi Hc;
-        if constexpr (MTV > 0) {
-          tw_read_hi<MTV>(Hc, lds + (s & 1) * TW_STAGE, fa0, fb0, lane);
-          tw_half<MTV>(Lc.a, Lc.b, Lc.as, Lc.bs, acc, 0);
-        }
-        wait_vm<0>();
-        __syncthreads();
-        if constexpr (!TAIL) {
-          issue(cur, oc, s + 2, s & 1, apar);
-        } else if (hn) {
-          if (s + 2 == nst) {
-            on = b_off(nx);
-            if (GATHER) a_off_tok(on, tbuf ^ 1);
-          }
-          issue(nx, on, s + 2 - nst, s & 1, apar_n);
-        }
-        if (!TAIL || s + 1 < nst) {
-          if constexpr (MTV > 0)
-            tw_read_lo<MTV>(Ln, lds + ((s + 1) & 1) * TW_STAGE, a_src(s + 1), s + 1, fa0, fb0, lane);
-        }
-        if constexpr (MTV > 0) tw_half<MTV>(Hc.a, Hc.b, Lc.as, Lc.bs, acc, 1);
-      };
-      for (int s = 0; s < nst - 2; s += 2) {     // nst is even
-        body(L0, L1, s, std::false_type{});
-        body(L1, L0, s + 1, std::false_type{});
-      }
-      body(L0, L1, nst - 2, std::true_type{});
-      body(L1, L0, nst - 1, std::true_type{});
-      // ---- epilogue: tensor scales, SwiGLU (gate fragments 0, 1 with up
-      // fragments 2, 3) or plain, bf16 pairs of adjacent columns swapped
-      // between neighbouring lanes so that every store writes 4 bytes
-      const int h = lane >> 5;
-      const bool odd = (lane & 1) != 0;
-      const int cpair = (lane & 31) & ~1;
-      constexpr int NO = EPI == QD_EPI_SWIGLU ? 2 : 4;
-      const int ldo = EPI == QD_EPI_SWIGLU ? (N >> 1) : N;
-      const bool full = nrows == TW_M;
-      unsigned char *obase = reinterpret_cast<unsigned char *>(p.out);
-      const float alpha = a_dec * sw;
-#pragma unroll
-      for (int i = 0; i < MTV; ++i) {
-        const int rl = 32 * (fa0 + i) + 4 * h + (odd ? 1 : 0);
-#pragma unroll
-        for (int jj = 0; jj < NO; ++jj) {
-          const int cb = EPI == QD_EPI_SWIGLU ? nt * 128 + wn * 64 + 32 * jj
-                                              : nt * TW_N + 32 * (fb0 + jj);
-          const uint32_t voff = (uint32_t)((row0 + rl) * ldo + cb + cpair) * 2u;
-          float v[16];
-#pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            if (EPI == QD_EPI_SWIGLU)
-              v[q] = swiglu_fast(alpha * acc[i][jj][q], alpha * acc[i][jj + 2][q]);
-            else
-              v[q] = alpha * acc[i][jj][q];
-          }
-#pragma unroll
-          for (int q = 0; q < 16; q += 2) {
-            const float send = odd ? v[q] : v[q + 1];
-            const float x = __int_as_float(
-                __builtin_amdgcn_mov_dpp(__float_as_int(send), 0xB1, 0xF, 0xF, false));
-            const f32x2_t pr = odd ? f32x2_t{x, v[q + 1]} : f32x2_t{v[q], x};
-            const uint32_t pk = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2_t));
-            const int qr = 8 * (q >> 2) + (q & 3);
-            if (full || rl + qr < nrows) {
-              *reinterpret_cast<uint32_t *>(obase + (size_t)(qr * ldo * 2) + voff) = pk;
-              vmax = fmaxf(vmax, fmaxf(fabsf(__uint_as_float(pk << 16)),
-                                       fabsf(__uint_as_float(pk & 0xFFFF0000u))));
-            }
-          }
-        }
-      }
-    };
-    switch (mtv) {
-      case 4: run(std::integral_constant<int, 4>{}); break;
-      case 3: run(std::integral_constant<int, 3>{}); break;
-      case 2: run(std::integral_constant<int, 2>{}); break;
-      case 1: run(std::integral_constant<int, 1>{}); break;
-      default: run(std::integral_constant<int, 0>{}); break;
-    }
-    t = tn;
-    have = hn;
-    cur = nx;
-    oc = on;
-    apar = apar_n;
-    tbuf ^= 1;
-  }
-  wait_vm<0>();
-  const float m = block_max(vmax, red);
-  put_amax(p, m);
-}
-
 // host-side plan of the decode kernel
 struct SkPlan {
   bool ok;
@@ -1835,37 +1260,25 @@ void launch_skinny(const GemmArgs &p, const SkPlan &pl, hipStream_t s) {
   hipLaunchKernelGGL(kern, dim3((unsigned)pl.grid), dim3(SK_THREADS), pl.lds, s, p, pl.nblk);
 }
 
-// host-side plan of the prefill kernel
+// host-side plan of the tile kernel
 struct TlPlan {
   bool ok;
-  bool dense;   // RAC as a second pass over K on the masked residual
   int ntn, grid, lds, grp;
 };
 
-// rac: the residual is fused, in its compact form (rq_sel) while the compact
-// weight table leaves LDS for two workgroups per CU, else as the dense second
-// pass over the masked residual (faster than the table at one workgroup per
-// CU); compact_only: the table wherever it fits at all
-inline TlPlan tile_plan(int64_t rows, int E, int64_t N, int64_t K, bool rac, int Ks,
-                        bool compact_only = false) {
+inline TlPlan tile_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks) {
   TlPlan pl{};
-  if (K < 4 * TL_K || K % (2 * TL_K) != 0 || N % TL_N != 0 || E > TL_EMAX) return pl;
+  if (Ks <= 0 || K < 4 * TL_K || K % (2 * TL_K) != 0 || N % TL_N != 0 || E > TL_EMAX) return pl;
   // byte offsets inside one activation matrix or one expert's weights, and
   // output offsets, fit 32 bits
   if (N * K / 2 >= (1LL << 32) || (rows + 1) * K / 2 >= (1LL << 32)) return pl;
   if ((rows + TL_M) * N * 2 >= (1LL << 32)) return pl;
-  bool cmp = rac;
-  int ksa = rac ? (Ks + 15) / 16 * 16 : 0;
-  if (rac && !compact_only && tl_lds_bytes(true, ksa, false) > TL_LDS_2WG) {
-    pl.dense = true;
-    cmp = false;
-    ksa = 0;
-  }
-  pl.lds = tl_lds_bytes(cmp, ksa, false);
+  const int ksa = (Ks + 15) / 16 * 16;
+  pl.lds = tl_lds_bytes(ksa, false);
   if (pl.lds > TL_LDS_MAX) return pl;
   // the A-scale ring where it keeps the workgroups per CU (groups of four
   // stages: K a multiple of 256, so no group reads past a row's scales)
-  const int lg = tl_lds_bytes(cmp, ksa, true) + TL_AGRP;
+  const int lg = tl_lds_bytes(ksa, true) + TL_AGRP;
   if (K % 256 == 0 && ((pl.lds <= TL_LDS_2WG && lg <= TL_LDS_2WG) ||
                        (pl.lds > TL_LDS_2WG && lg <= TL_LDS_MAX))) {
     pl.lds = lg;
@@ -1879,9 +1292,74 @@ inline TlPlan tile_plan(int64_t rows, int E, int64_t N, int64_t K, bool rac, int
   return pl;
 }
 
-template <bool GATHER, bool RAC, int EPI, bool DENSE = false>
+// The form of the residual outside the decode kernel: compact (rq_sel) while
+// two workgroups of the tile kernel's table and ring would fit a CU (K_s <=
+// 144), else the masked residual rq (the dense second pass).  The table costs
+// about 7% of the GEMM at K_s = 128, the second pass 100%, but a larger table
+// leaves the panel kernel's ring no room.
+inline bool compact_form(int Ks) {
+  return Ks > 0 && tl_lds_bytes((Ks + 15) / 16 * 16, false) <= TL_LDS_2WG;
+}
+
+// host-side plan of the panel kernel
+struct PnPlan {
+  bool ok;
+  bool dense;
+  int mf, ns, ntn, grid, lds;
+};
+
+inline PnPlan panel_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, bool per_expert) {
+  PnPlan pl{};
+  if (K < 2 * qdp::PN_K || K % qdp::PN_K != 0 || N % 128 != 0 || E > qdp::PN_EMAX) return pl;
+  int ksa = (Ks + 15) / 16 * 16;
+  // the compact residual up to the K_s whose table leaves room for the ring,
+  // the dense second pass above (per-expert sets have the compact form only)
+  if (Ks > 0 && !per_expert && !compact_form(Ks)) {
+    pl.dense = true;
+    ksa = 0;
+  }
+  // 32-bit byte offsets into one operand and into the output
+  if ((rows + 1) * K / 2 >= (1LL << 32) || (rows + 1) * ksa * 2 >= (1LL << 32) ||
+      (rows + 320) * N * 2 >= (1LL << 32))
+    return pl;
+  // tiles of the height that takes most experts' rows at once, with uniform
+  // routing (a row count above it costs a second tile of that expert); lower
+  // tiles leave LDS for a deeper ring, which is what a few rows need
+  const double mean = (double)rows / E, want = mean + 2.5 * sqrt(mean);
+  static const int kMf[4] = {5, 3, 2, 1};
+  int c = 0;
+  while (c < 3 && want <= 64.0 * kMf[c + 1]) ++c;
+  const int nst = (int)(K / qdp::PN_K);
+  for (; c < 4; ++c) {
+    int ns = std::min(qdp::PN_NSMAX, nst);
+    while (ns >= 2 && qdp::pn_layout(kMf[c], ns, ksa, E).total > qdp::PN_LDS_MAX) --ns;
+    if (ns >= 2) {
+      pl.mf = kMf[c];
+      pl.ns = ns;
+      pl.lds = qdp::pn_layout(pl.mf, ns, ksa, E).total;
+      break;
+    }
+  }
+  if (c == 4) return pl;
+  pl.ntn = (int)((N + qdp::PN_N - 1) / qdp::PN_N);
+  // persistent: one workgroup per CU (256), a multiple of 8 (the XCDs)
+  pl.grid = (int)std::min<int64_t>(256, qdt::tile_grid(rows, E, 64 * pl.mf, pl.ntn));
+  pl.ok = true;
+  return pl;
+}
+
+void launch_pn(const GemmArgs &p, int epi, const PnPlan &pl, hipStream_t s) {
+  switch (pl.mf) {
+    case 5: qdp::launch_panel<5>(p, epi, pl.ntn, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
+    case 3: qdp::launch_panel<3>(p, epi, pl.ntn, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
+    case 2: qdp::launch_panel<2>(p, epi, pl.ntn, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
+    default: qdp::launch_panel<1>(p, epi, pl.ntn, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
+  }
+}
+
+template <bool GATHER, int EPI>
 void launch_tile(const GemmArgs &p, const TlPlan &pl, hipStream_t s) {
-  auto kern = gemm_tile_kernel<GATHER, RAC, EPI, DENSE>;
+  auto kern = gemm_tile_kernel<GATHER, EPI>;
   static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                                TL_LDS_MAX) == hipSuccess;
@@ -1890,72 +1368,62 @@ void launch_tile(const GemmArgs &p, const TlPlan &pl, hipStream_t s) {
                      pl.grp);
 }
 
-// host-side plan of the wide prefill kernel (needs the weights'
-// fragment-ordered scales)
-struct WdPlan {
-  bool ok;
-  int ntn, grid, lds;
+// The kernel of a grouped GEMM: the decode kernel for few rows per expert,
+// the panel kernel above, the tile kernel for per-expert sets whose table the
+// panel kernel cannot hold, and the generic kernel for sizes none takes.
+enum class Kern { skinny, panel, tile, generic };
+
+struct Choice {
+  Kern k;
+  SkPlan sk;
+  PnPlan pn;
+  TlPlan tl;
 };
 
-inline WdPlan wide_plan(int64_t rows, int E, int64_t N, int64_t K, bool rac, int Ks, bool sfrag) {
-  WdPlan pl{};
-  (void)Ks;
-  if (rac || !sfrag || K < 2 * TW_K || K % (2 * TW_K) != 0 || N % TW_N != 0 || E > TL_EMAX)
-    return pl;
-  if (N * K / 2 >= (1LL << 32) || (rows + 1) * K / 2 >= (1LL << 32)) return pl;
-  if ((rows + TW_M) * N * 2 >= (1LL << 32)) return pl;
-  pl.lds = tw_lds_bytes(E);
-  if (pl.lds > TL_LDS_MAX) return pl;
-  pl.ntn = (int)(N / TW_N);
-  // persistent: one workgroup per CU (256 on MI355X), a multiple of 8 (the
-  // XCDs), at most the tile count's upper bound
-  const int64_t g = qdt::tile_grid(rows, E, TW_M, pl.ntn);
-  pl.grid = (int)std::min<int64_t>(256, g);
-  pl.ok = true;
-  return pl;
-}
-
-template <bool GATHER, int EPI>
-void launch_wide(const GemmArgs &p, const WdPlan &pl, hipStream_t s) {
-  auto kern = gemm_wide_kernel<GATHER, EPI>;
-  static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               TL_LDS_MAX) == hipSuccess;
-  (void)attr;
-  hipLaunchKernelGGL(kern, dim3((unsigned)pl.grid), dim3(TW_THREADS), (size_t)pl.lds, s, p, pl.ntn);
+inline Choice choose(int64_t rows, int E, int64_t N, int64_t K, int Ks, int epilogue, bool bitmap,
+                     bool per_expert) {
+  Choice c{};
+  c.k = Kern::generic;
+  if (!per_expert) c.sk = skinny_plan(rows, E, N, K, Ks, epilogue, bitmap);
+  if (c.sk.ok) {
+    c.k = Kern::skinny;
+    return c;
+  }
+  c.pn = panel_plan(rows, E, N, K, Ks, per_expert);
+  if (c.pn.ok) {
+    c.k = Kern::panel;
+    return c;
+  }
+  if (per_expert) {
+    c.tl = tile_plan(rows, E, N, K, Ks);
+    if (c.tl.ok) c.k = Kern::tile;
+  }
+  return c;
 }
 
 template <bool GATHER, bool RAC>
-void launch_epi(const GemmArgs &p, int epi, dim3 grid, hipStream_t s, const SkPlan &pl,
-                const TlPlan &tp, const WdPlan &wp) {
-  if (pl.ok) {
-    if (epi == QD_EPI_SWIGLU) launch_skinny<GATHER, RAC, QD_EPI_SWIGLU>(p, pl, s);
-    else launch_skinny<GATHER, RAC, QD_EPI_NONE>(p, pl, s);
-    return;
-  }
-  if constexpr (!RAC) {
-    if (wp.ok) {
-      if (epi == QD_EPI_SWIGLU) launch_wide<GATHER, QD_EPI_SWIGLU>(p, wp, s);
-      else launch_wide<GATHER, QD_EPI_NONE>(p, wp, s);
+void launch_epi(const GemmArgs &p, int epi, dim3 grid, hipStream_t s, const Choice &c) {
+  const bool sw = epi == QD_EPI_SWIGLU;
+  switch (c.k) {
+    case Kern::skinny:
+      if (sw) launch_skinny<GATHER, RAC, QD_EPI_SWIGLU>(p, c.sk, s);
+      else launch_skinny<GATHER, RAC, QD_EPI_NONE>(p, c.sk, s);
       return;
-    }
-  }
-  if (tp.ok) {
-    if constexpr (RAC) {
-      if (tp.dense) {
-        if (epi == QD_EPI_SWIGLU) launch_tile<GATHER, true, QD_EPI_SWIGLU, true>(p, tp, s);
-        else launch_tile<GATHER, true, QD_EPI_NONE, true>(p, tp, s);
-        return;
+    case Kern::panel:
+      launch_pn(p, epi, c.pn, s);
+      return;
+    case Kern::tile:
+      if constexpr (RAC) {
+        if (sw) launch_tile<GATHER, QD_EPI_SWIGLU>(p, c.tl, s);
+        else launch_tile<GATHER, QD_EPI_NONE>(p, c.tl, s);
       }
-    }
-    if (epi == QD_EPI_SWIGLU) launch_tile<GATHER, RAC, QD_EPI_SWIGLU>(p, tp, s);
-    else launch_tile<GATHER, RAC, QD_EPI_NONE>(p, tp, s);
-    return;
+      return;
+    default:
+      if (sw)
+        hipLaunchKernelGGL((gemm_w4a4_kernel<GATHER, RAC, QD_EPI_SWIGLU>), grid, dim3(256), 0, s, p);
+      else
+        hipLaunchKernelGGL((gemm_w4a4_kernel<GATHER, RAC, QD_EPI_NONE>), grid, dim3(256), 0, s, p);
   }
-  if (epi == QD_EPI_SWIGLU)
-    hipLaunchKernelGGL((gemm_w4a4_kernel<GATHER, RAC, QD_EPI_SWIGLU>), grid, dim3(256), 0, s, p);
-  else
-    hipLaunchKernelGGL((gemm_w4a4_kernel<GATHER, RAC, QD_EPI_NONE>), grid, dim3(256), 0, s, p);
 }
 
 }  // namespace
@@ -1963,24 +1431,17 @@ void launch_epi(const GemmArgs &p, int epi, dim3 grid, hipStream_t s, const SkPl
 bool qdi::gemm_wants_rq_sel(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
                             int32_t epilogue) {
   if (Ks <= 0 || rows <= 0 || E < 1 || N <= 0 || K <= 0) return false;
-  if (skinny_plan(rows, E, N, K, Ks, epilogue).ok) return false;
-  const TlPlan tp = tile_plan(rows, E, N, K, true, Ks);
-  return tp.ok && !tp.dense;
+  const Choice c = choose(rows, E, N, K, Ks, epilogue, false, false);
+  return c.k == Kern::panel && !c.pn.dense;
 }
 
 int64_t qdi::gemm_amax_written(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
-                               int32_t epilogue, bool sfrag, bool bitmap) {
+                               int32_t epilogue, bool bitmap) {
   if (rows <= 0 || E < 1 || N <= 0 || K <= 0 || Ks < 0) return 0;
-  // the kernel choice of the grouped GEMM (launch_epi) and its grid
-  const bool rac = Ks > 0;
-  const SkPlan pl = skinny_plan(rows, E, N, K, Ks, epilogue, bitmap);
-  if (pl.ok) return pl.grid;
-  if (!rac) {
-    const WdPlan wp = wide_plan(rows, E, N, K, false, Ks, sfrag);
-    if (wp.ok) return wp.grid;
-  }
-  const TlPlan tp = tile_plan(rows, E, N, K, rac, Ks);
-  if (tp.ok) return tp.grid;
+  // the grid of the kernel the grouped GEMM takes
+  const Choice c = choose(rows, E, N, K, Ks, epilogue, bitmap, false);
+  if (c.k == Kern::skinny) return c.sk.grid;
+  if (c.k == Kern::panel) return c.pn.grid;
   return grid_x(rows, E, true) * grid_y(N, epilogue);
 }
 
@@ -1999,23 +1460,19 @@ extern "C" int32_t moe_w4a4_grouped_gemm_residual_form(int64_t rows, int64_t N, 
 extern "C" int64_t moe_w4a4_grouped_gemm_amax_count(int64_t rows, int64_t N, int64_t K,
                                                     int32_t E, int32_t Ks, int32_t epilogue) {
   if (rows < 0 || N <= 0 || K <= 0 || E < 1 || Ks < 0) return 0;
-  const SkPlan pl = skinny_plan(rows, E, N, K, Ks, epilogue);
-  if (pl.ok) return pl.grid;
-  // whichever of the other kernels runs (the wide one needs the weights'
-  // fragment-ordered scales) writes every entry of the largest grid
-  const WdPlan wp = wide_plan(rows, E, N, K, Ks > 0, Ks, true);
-  const TlPlan tp = tile_plan(rows, E, N, K, Ks > 0, Ks);
-  return std::max<int64_t>(std::max<int64_t>(wp.ok ? wp.grid : 0, tp.ok ? tp.grid : 0),
+  const Choice c = choose(rows, E, N, K, Ks, epilogue, false, false);
+  if (c.k == Kern::skinny) return c.sk.grid;
+  // every kernel writes (or zeroes) every entry, up to the largest grid
+  return std::max<int64_t>(c.k == Kern::panel ? c.pn.grid : 0,
                            grid_x(rows, E, true) * grid_y(N, epilogue));
 }
 
 extern "C" int64_t moe_w4a4_grouped_gemm_per_expert_amax_count(int64_t rows, int64_t N,
                                                                int64_t K, int32_t E, int32_t Ks,
                                                                int32_t epilogue) {
-  (void)epilogue;
   if (rows < 0 || N <= 0 || K <= 0 || E < 1 || Ks < 1) return 0;
-  const TlPlan tp = tile_plan(rows, E, N, K, true, Ks, true);
-  return tp.ok ? tp.grid : 0;
+  const Choice c = choose(rows, E, N, K, Ks, epilogue, false, true);
+  return c.k == Kern::panel ? c.pn.grid : c.k == Kern::tile ? c.tl.grid : 0;
 }
 
 // Fragment-ordered weight scales: one thread per output dword, i.e. per
@@ -2066,7 +1523,7 @@ qd_status grouped_gemm_impl(const qd_nvfp4 *a, const int32_t *row_token,
                             const qd_nvfp4 *w, const qd_nvfp4 *rq, const int32_t *sel_idx,
                             int32_t Ks, const void *rq_sel, const uint32_t *bitmap,
                             int32_t epilogue, void *out, float *amax_partials, void *stream,
-                            bool per_expert = false, const uint8_t *a_stg = nullptr) {
+                            bool per_expert = false) {
   if (!a || !w || !out) return QD_ERR_NULL;
   if (epilogue != QD_EPI_NONE && epilogue != QD_EPI_SWIGLU) return QD_ERR_DTYPE;
   if (E < 1 || rows < 0) return QD_ERR_SHAPE;
@@ -2097,14 +1554,12 @@ qd_status grouped_gemm_impl(const qd_nvfp4 *a, const int32_t *row_token,
   if (N > 0x7fffffff || K > 0x7fffffff) return QD_ERR_UNSUPPORTED;
   const int64_t gx = grid_x(rows, E, true), gy = grid_y(N, epilogue);
   if (gx > 0x7fffffffLL || gy > 65535) return QD_ERR_UNSUPPORTED;
-  // per-expert channel sets run on the tile kernel alone
-  const SkPlan pl = per_expert ? SkPlan{} : skinny_plan(rows, E, N, K, rac ? Ks : 0, epilogue, bitmap != nullptr);
-  if (bitmap && !pl.ok) return QD_ERR_UNSUPPORTED;
+  const Choice c = choose(rows, E, N, K, rac ? Ks : 0, epilogue, bitmap != nullptr, per_expert);
+  if (bitmap && c.k != Kern::skinny) return QD_ERR_UNSUPPORTED;
   if (per_expert) {
     // per-expert sets take the compact residual (one per grouped row)
-    const TlPlan pp = tile_plan(rows, E, N, K, true, Ks, true);
-    if (!rac || !rq_sel || !pp.ok)
-      return rac && rq_sel ? QD_ERR_UNSUPPORTED : QD_ERR_NULL;
+    if (!rac || !rq_sel) return QD_ERR_NULL;
+    if (c.k != Kern::panel && c.k != Kern::tile) return QD_ERR_UNSUPPORTED;
   }
   if (qdh::fault_injected()) return QD_ERR_HIP;
   if (rows == 0) return QD_OK;
@@ -2139,25 +1594,23 @@ qd_status grouped_gemm_impl(const qd_nvfp4 *a, const int32_t *row_token,
     }
   }
   p.out = static_cast<uint16_t *>(out);
-  p.a_stg = row_token && !per_expert ? a_stg : nullptr;
   p.amax_part = amax_partials;
   p.amax_n = !amax_partials ? 0
              : per_expert ? moe_w4a4_grouped_gemm_per_expert_amax_count(rows, N, K, E, Ks, epilogue)
                           : moe_w4a4_grouped_gemm_amax_count(rows, N, K, E, rac ? Ks : 0, epilogue);
-  const TlPlan tp = tile_plan(rows, E, N, K, rac, Ks, per_expert);
-  const WdPlan wp = wide_plan(rows, E, N, K, rac, Ks, w->scales_frag != nullptr);
-  // the tile kernel takes the residual in its compact form unless its plan
+  // the panel kernel takes the residual in its compact form unless its plan
   // is the dense second pass (which reads the masked residual rq)
-  if (rac && !pl.ok && tp.ok && !tp.dense && (!rq_sel || !qdh::aligned16(rq_sel)))
+  if (rac && ((c.k == Kern::panel && !c.pn.dense) || c.k == Kern::tile) &&
+      (!rq_sel || !qdh::aligned16(rq_sel)))
     return rq_sel ? QD_ERR_ALIGN : QD_ERR_NULL;
   dim3 grid((unsigned)gx, (unsigned)gy);
   hipStream_t s = qdh::S(stream);
   if (row_token) {
-    if (rac) launch_epi<true, true>(p, epilogue, grid, s, pl, tp, wp);
-    else launch_epi<true, false>(p, epilogue, grid, s, pl, tp, wp);
+    if (rac) launch_epi<true, true>(p, epilogue, grid, s, c);
+    else launch_epi<true, false>(p, epilogue, grid, s, c);
   } else {
-    if (rac) launch_epi<false, true>(p, epilogue, grid, s, pl, tp, wp);
-    else launch_epi<false, false>(p, epilogue, grid, s, pl, tp, wp);
+    if (rac) launch_epi<false, true>(p, epilogue, grid, s, c);
+    else launch_epi<false, false>(p, epilogue, grid, s, c);
   }
   return qdh::check_launch();
 }
@@ -2182,38 +1635,6 @@ extern "C" qd_status moe_w4a4_grouped_gemm(const qd_nvfp4 *a, const int32_t *row
                                            void *stream) {
   return grouped_gemm_impl(a, row_token, expert_offsets, E, rows, w, rq, sel_idx, Ks, rq_sel,
                            nullptr, epilogue, out, amax_partials, stream);
-}
-
-// Staging costs rows x K x 9/16 bytes written and read once, and saves time in
-// proportion to N (the n-tiles that re-read each stage): measured at N = 3072,
-// K = 4096 the tile GEMM gains 2.5x the copy's time, at N = 1536, K = 2048
-// 0.8x, so it is taken from N = 2048 on.
-constexpr int64_t kStageMinN = 2048;
-
-int64_t qdi::gemm_stage_bytes(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
-                              int32_t epilogue) {
-  if (Ks <= 0 || rows <= 0 || E < 1 || N < kStageMinN || K <= 0) return 0;
-  if (skinny_plan(rows, E, N, K, Ks, epilogue).ok) return 0;
-  const TlPlan tp = tile_plan(rows, E, N, K, true, Ks);
-  if (!tp.ok || !tp.grp) return 0;
-  return rows * (K / 2 + K / 16);
-}
-
-int64_t qdi::gemm_stage_reserve(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t epilogue) {
-  if (rows <= 0 || E < 1 || N < kStageMinN || K <= 0 || K % 256 != 0) return 0;
-  if (skinny_plan(rows, E, N, K, 1, epilogue).ok) return 0;
-  return tile_plan(rows, E, N, K, true, 1).ok ? rows * (K / 2 + K / 16) : 0;
-}
-
-qd_status qdi::grouped_gemm_staged(const qd_nvfp4 *a, const int32_t *row_token,
-                                   const int32_t *expert_offsets, int32_t E, int64_t rows,
-                                   const qd_nvfp4 *w, const qd_nvfp4 *rq, const int32_t *sel_idx,
-                                   int32_t Ks, const void *rq_sel, int32_t epilogue, void *out,
-                                   float *amax_partials, const uint8_t *a_stg, hipStream_t stream) {
-  if (!a_stg || !row_token) return QD_ERR_NULL;
-  if (!qdh::aligned16(a_stg)) return QD_ERR_ALIGN;
-  return grouped_gemm_impl(a, row_token, expert_offsets, E, rows, w, rq, sel_idx, Ks, rq_sel,
-                           nullptr, epilogue, out, amax_partials, stream, false, a_stg);
 }
 
 qd_status qdi::grouped_gemm_bitmap(const qd_nvfp4 *a, const int32_t *row_token,

@@ -341,9 +341,8 @@ __global__ __launch_bounds__(256) void layer_resq_kernel(
 // prefill W13 kernel consumes), with the residual's tensor scale
 // (bitmap not NULL: S comes as the selection bitmap; every workgroup lists
 // it into LDS, and workgroup 0 also into sel for the GEMM)
-// (workgroup bid of nblk)
-__device__ __forceinline__ void compact_part(
-    int bid, int nblk, const uint16_t *__restrict__ x, const uint8_t *__restrict__ xcodes,
+__global__ __launch_bounds__(256) void layer_compact_kernel(
+    const uint16_t *__restrict__ x, const uint8_t *__restrict__ xcodes,
     const uint8_t *__restrict__ xscales, const float *__restrict__ xgs, int64_t T, int64_t K,
     const float *__restrict__ ramax, int32_t *__restrict__ sel, int Ks, int width,
     uint16_t *__restrict__ out, float *__restrict__ rgs, const uint32_t *__restrict__ bitmap) {
@@ -353,20 +352,12 @@ __device__ __forceinline__ void compact_part(
   if (bitmap) {
     qdc::rac_list_selected(bitmap, (int)K, lsel, sh);
     __syncthreads();
-    if (bid == 0)
+    if (blockIdx.x == 0)
       for (int i = threadIdx.x; i < Ks; i += blockDim.x) sel[i] = lsel[i];
     sp = lsel;
   }
-  qdc::rac_compact_body(bid, nblk, x, xcodes, xscales, xgs, T, K, ramax, sp, Ks, width, out, rgs);
-}
-
-__global__ __launch_bounds__(256) void layer_compact_kernel(
-    const uint16_t *__restrict__ x, const uint8_t *__restrict__ xcodes,
-    const uint8_t *__restrict__ xscales, const float *__restrict__ xgs, int64_t T, int64_t K,
-    const float *__restrict__ ramax, int32_t *__restrict__ sel, int Ks, int width,
-    uint16_t *__restrict__ out, float *__restrict__ rgs, const uint32_t *__restrict__ bitmap) {
-  compact_part(blockIdx.x, gridDim.x, x, xcodes, xscales, xgs, T, K, ramax, sel, Ks, width, out,
-               rgs, bitmap);
+  qdc::rac_compact_body(blockIdx.x, gridDim.x, x, xcodes, xscales, xgs, T, K, ramax, sp, Ks,
+                        width, out, rgs);
 }
 
 // routing scatter (nr workgroups) | RAC channel selection by rank and the
@@ -389,65 +380,9 @@ __global__ __launch_bounds__(qdc::kRankSelThreads) void layer_pre3r_kernel(
                               rcodes, rscales, rgs);
 }
 
-// The quantised activations of every grouped row copied stage-major for the
-// W13 tile GEMM (its A loads of one stage then read one contiguous 8 KB
-// piece per tile instead of 32 bytes from each of 256 gathered rows): codes
-// [K / 64][R][32 B], then the scales of four stages at a time [K / 256][R][16 B].
-// Grid (ceil(2R / 256), K / 64 + K / 256): row y < K / 64 is code stage y,
-// thread x its 16-byte piece x % 2 of grouped row x / 2; the rows after are
-// scale group y - K / 64, thread x grouped row x.  Consecutive threads write
-// consecutive 16-byte pieces.
-__device__ __forceinline__ void stage_part(int64_t bx, int64_t y,
-                                           const int32_t *__restrict__ row_token,
-                                           const uint8_t *__restrict__ codes,
-                                           const uint8_t *__restrict__ scales, int64_t R,
-                                           int64_t K, uint8_t *__restrict__ out) {
-  const int64_t x = bx * 256 + threadIdx.x;
-  const int64_t nst = K / 64;
-  uint4 *o = reinterpret_cast<uint4 *>(out);
-  if (y < nst) {
-    if (x >= 2 * R) return;
-    const int64_t r = x >> 1, half = x & 1;
-    const int64_t t = row_token[r];
-    o[y * 2 * R + x] = *reinterpret_cast<const uint4 *>(codes + t * (K / 2) + 32 * y + 16 * half);
-  } else {
-    if (x >= R) return;
-    const int64_t g = y - nst;
-    const int64_t t = row_token[x];
-    o[R * (K / 32) + g * R + x] = *reinterpret_cast<const uint4 *>(scales + t * (K / 16) + 16 * g);
-  }
-}
-
-__global__ __launch_bounds__(256) void layer_stage_kernel(const int32_t *__restrict__ row_token,
-                                                          const uint8_t *__restrict__ codes,
-                                                          const uint8_t *__restrict__ scales,
-                                                          int64_t R, int64_t K,
-                                                          uint8_t *__restrict__ out) {
-  stage_part(blockIdx.x, blockIdx.y, row_token, codes, scales, R, K, out);
-}
-
-// the compact residual (gc workgroups) | the staged W13 operand (gxs x gys
-// workgroups of layer_stage_kernel's grid, x fastest) in one launch: the two
-// are independent and run side by side
-__global__ __launch_bounds__(256) void layer_compact_stage_kernel(
-    const uint16_t *__restrict__ x, const uint8_t *__restrict__ xcodes,
-    const uint8_t *__restrict__ xscales, const float *__restrict__ xgs, int64_t T, int64_t K,
-    const float *__restrict__ ramax, int32_t *__restrict__ sel, int Ks, int width,
-    uint16_t *__restrict__ out, float *__restrict__ rgs, const uint32_t *__restrict__ bitmap,
-    int gc, const int32_t *__restrict__ row_token, int64_t R, int64_t gxs,
-    uint8_t *__restrict__ stg) {
-  const int b = blockIdx.x;
-  if (b < gc) {
-    compact_part(b, gc, x, xcodes, xscales, xgs, T, K, ramax, sel, Ks, width, out, rgs, bitmap);
-  } else {
-    const int64_t q = b - gc;
-    stage_part(q % gxs, q / gxs, row_token, xcodes, xscales, R, K, stg);
-  }
-}
-
 struct Layout {
   int64_t off[QD_VIEW_COUNT];
-  int64_t route_ws, q1_ws, sel_ws, q2_ws, sel2_ws, stg, stg_bytes, total;
+  int64_t route_ws, q1_ws, sel_ws, q2_ws, sel2_ws, total;
   // the block entry point's extra views after the layer's workspace: the
   // normalised state x and the router logits
   int64_t xn, lg, block_total;
@@ -506,9 +441,6 @@ Layout make_layout(int64_t T, int64_t H, int32_t E, int32_t k, int64_t I) {
   put(QD_VIEW_HR_SCALES, R * I / 16);
   put(QD_VIEW_HR_GSCALE, 8);
   put(QD_VIEW_HR_SEL, R * (int64_t)rac_selected_width((int32_t)I) * 2);
-  // the staged W13 operand, where the tile GEMM may take it
-  L.stg_bytes = qdi::gemm_stage_reserve(R, E, 2 * I, H, QD_EPI_SWIGLU);
-  L.stg = blob(L.stg_bytes);
   L.total = o;
   L.xn = blob(T * H * 2);
   L.lg = blob(T * (int64_t)E * 4);
@@ -633,16 +565,6 @@ qd_status layer_impl(const void *x, const float *logits, int64_t T, int64_t H, i
   int gx, gy;
   qdq::quant_grid(T, H, rac, gx, gy);
 
-  // the staged W13 operand (timed with the steps before the GEMM, so that
-  // the W13 stage is the GEMM launch alone); with the compact residual it is
-  // written by the same launch
-  const int64_t stg_bytes = rank_sel ? 0 : qdi::gemm_stage_bytes(R, E, 2 * I, H, Ks, QD_EPI_SWIGLU);
-  const bool staged = stg_bytes > 0 && stg_bytes <= L.stg_bytes;
-  uint8_t *stg = reinterpret_cast<uint8_t *>(b + L.stg);
-  const int64_t gxs = (2 * R + 255) / 256, gys = H / 64 + H / 256;
-  if (staged && (gxs > 0x7fffffffLL || gys > 65535 || gxs * gys > 0x7fff0000LL))
-    return QD_ERR_UNSUPPORTED;
-  bool stg_done = false;
   mark(QD_STAGE_ROUTE);
   int np = ga;      // amax partials of X
   if (blk) {
@@ -703,19 +625,10 @@ qd_status layer_impl(const void *x, const float *logits, int64_t T, int64_t H, i
       int64_t g = (total + 255) / 256;
       if (g > 8192) g = 8192;
       if (g < 1) g = 1;
-      if (staged) {
-        hipLaunchKernelGGL(layer_compact_stage_kernel, dim3((unsigned)(g + gxs * gys)), dim3(256),
-                           0, s, static_cast<const uint16_t *>(x), xq.codes, xq.scales, xq.gscale,
-                           T, H, ramax, sel, Ks, width, static_cast<uint16_t *>(rq_sel),
-                           rq.gscale, rank_only ? bitmap : nullptr, (int)g, row_token, R, gxs,
-                           stg);
-        stg_done = true;
-      } else {
-        hipLaunchKernelGGL(layer_compact_kernel, dim3((unsigned)g), dim3(256), 0, s,
-                           static_cast<const uint16_t *>(x), xq.codes, xq.scales, xq.gscale, T,
-                           H, ramax, sel, Ks, width, static_cast<uint16_t *>(rq_sel), rq.gscale,
-                           rank_only ? bitmap : nullptr);
-      }
+      hipLaunchKernelGGL(layer_compact_kernel, dim3((unsigned)g), dim3(256), 0, s,
+                         static_cast<const uint16_t *>(x), xq.codes, xq.scales, xq.gscale, T, H,
+                         ramax, sel, Ks, width, static_cast<uint16_t *>(rq_sel), rq.gscale,
+                         rank_only ? bitmap : nullptr);
     } else if (!rank_sel) {
       const int64_t total = T * (H / 16);
       int64_t g = (total + 255) / 256;
@@ -734,17 +647,10 @@ qd_status layer_impl(const void *x, const float *logits, int64_t T, int64_t H, i
   if (st) return st;
   uint16_t *h = (uint16_t *)P(QD_VIEW_H);
   float *hamax = (float *)P(QD_VIEW_H_AMAX);
-  if (staged && !stg_done) {
-    hipLaunchKernelGGL(layer_stage_kernel, dim3((unsigned)gxs, (unsigned)gys), dim3(256), 0, s,
-                       row_token, xq.codes, xq.scales, R, H, stg);
-  }
   mark(QD_STAGE_W13);
   if (rank_sel) {
     st = qdi::grouped_gemm_bitmap(&xq, row_token, offs, E, R, w13, &rq, bitmap, Ks, sel,
                                   QD_EPI_SWIGLU, h, hamax, s);
-  } else if (staged) {
-    st = qdi::grouped_gemm_staged(&xq, row_token, offs, E, R, w13, &rq, sel, Ks, rq_sel,
-                                  QD_EPI_SWIGLU, h, hamax, stg, s);
   } else {
     st = moe_w4a4_grouped_gemm(&xq, row_token, offs, E, R, w13, rac ? &rq : nullptr,
                                rac ? sel : nullptr, Ks, rq_sel, QD_EPI_SWIGLU, h, hamax, stream);
@@ -762,8 +668,7 @@ qd_status layer_impl(const void *x, const float *logits, int64_t T, int64_t H, i
   bool bm2 = false;                 // the W2 GEMM takes S as a bitmap
   if (!rac2) {
     st = nvfp4_quantize_act(h, QD_DTYPE_BF16, R, I, hamax,
-                            qdi::gemm_amax_written(R, E, 2 * I, H, Ks, QD_EPI_SWIGLU,
-                                                   w13->scales_frag != nullptr, rank_sel),
+                            qdi::gemm_amax_written(R, E, 2 * I, H, Ks, QD_EPI_SWIGLU, rank_sel),
                             &hq, nullptr, nullptr, b + L.q2_ws,
                             nvfp4_quantize_act_workspace(R, I), stream);
     if (st) return st;

@@ -1,0 +1,133 @@
+"""GPU parity of the grouped GEMM's panel kernel at the edges of its tiles:
+row counts around its 32-row fragments and around each tile height (64, 128,
+192, 320 rows), widths that are no multiple of its 256 weight rows, K of two
+and three stages (three: no fragment-ordered scales), every form of the
+residual, and the largest expert count of its schedule.
+
+Against the oracle's float64 contraction of its own quantised operands, with
+the tolerance every GEMM stage has."""
+
+import zlib
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import layer as OL, rac as OR
+from paper_2607_15810_amd import ops
+from paper_2607_15810_amd import quads as Q
+
+from helpers import assert_nvfp4_equal, check_close_bf16, np_bf16, oracle_bank
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    Q.lib()
+    yield
+
+
+CASES = [
+    # name, rows per expert, K, N, Ks, gathered rows
+    ("few_rows_k384", [1, 31, 32, 33, 0, 5], 384, 256, 16, True),
+    ("k384_half_tile", [63, 64, 65, 0], 384, 128, 0, False),
+    ("k256_two_stages", [70, 64, 65, 96], 256, 384, 24, True),
+    ("around_128", [127, 128, 129, 97], 512, 256, 40, True),
+    ("around_192", [191, 192, 193, 129], 512, 384, 8, True),
+    ("around_320", [319, 320, 321, 289], 512, 256, 16, True),
+    ("two_tiles", [640, 641, 1, 330], 256, 128, 32, False),
+    ("one_expert", [333], 768, 256, 48, False),
+    ("dense_residual", [150, 60, 100], 384, 256, 200, True),
+    ("dense_residual_320", [300, 321], 512, 128, 160, False),
+    ("largest_table", [90, 70], 256, 256, 144, True),
+]
+
+
+@pytest.mark.parametrize("epi", [Q.QD_EPI_NONE, Q.QD_EPI_SWIGLU], ids=["plain", "swiglu"])
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_panel_gemm(case, epi):
+    name, counts, K, N, Ks, gather = case
+    E, R = len(counts), sum(counts)
+    T = (R + 1) // 2 if gather else R
+    rng = np.random.default_rng(zlib.crc32(name.encode()))
+    g = torch.Generator().manual_seed(zlib.crc32(name.encode()))
+    x = torch.randn((T, K), generator=g)
+    x[:, ::29] *= 20.0
+    x = x.to(torch.bfloat16)
+    wb = (torch.randn((E, N, K), generator=g) * 0.02).to(torch.bfloat16)
+    tok = rng.integers(0, T, R).astype(np.int32) if gather else np.arange(R, dtype=np.int32)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    w, W = ops.quantize_weight(wb.to(DEV)), oracle_bank(wb)
+    xg = x.to(DEV)
+    xq, scores, ramax = ops.quantize_act(xg, rac=True)
+    act = OR.rac_activation(np_bf16(x), Ks)
+    assert_nvfp4_equal(xq, act["xq"], "xq")
+    sel = rq = None
+    if Ks:
+        sel, rq, _, _ = ops.select_channels(xg, xq, Ks, scores, ramax)
+        assert np.array_equal(sel.cpu().numpy(), act["sel"])
+    out, amax = ops.grouped_gemm(xq, w, R, torch.from_numpy(tok).to(DEV) if gather else None,
+                                 torch.from_numpy(offsets).to(DEV) if E > 1 else None, rq, sel,
+                                 epi, want_amax=True)
+    gu, mag = OL.w13_stage(act["xq"], act["rq"] if Ks else None, tok, offsets, W)
+    if epi == Q.QD_EPI_SWIGLU:
+        I = N // 2
+        ref = OL.silu(gu[:, :I]) * gu[:, I:]
+        mag = (np.abs(OL.silu(gu[:, :I])) * mag[:, I:] + 1.1 * np.abs(gu[:, I:]) * mag[:, :I])
+    else:
+        ref = gu
+    check_close_bf16(np_bf16(out), ref, mag, name)
+    assert amax.max().item() == np.max(np.abs(np_bf16(out)))
+
+
+def test_panel_gemm_most_experts():
+    """E = 1024, the last entry of the tile schedule: rows on the first, a
+    middle and the last expert only."""
+    E, K, N = 1024, 384, 128
+    counts = np.zeros(E, np.int64)
+    counts[[0, 517, 1023]] = (33, 70, 64)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    R = int(offsets[-1])
+    g = torch.Generator().manual_seed(7)
+    x = torch.randn((R, K), generator=g).to(torch.bfloat16)
+    wb = torch.zeros((E, N, K), dtype=torch.bfloat16)
+    live = np.nonzero(counts)[0]
+    for e in live:
+        wb[e] = (torch.randn((N, K), generator=g) * 0.02).to(torch.bfloat16)
+    w, W = ops.quantize_weight(wb.to(DEV)), oracle_bank(wb, live)
+    xq, _, _ = ops.quantize_act(x.to(DEV))
+    act = OR.rac_activation(np_bf16(x), 0)
+    out, _ = ops.grouped_gemm(xq, w, R, None, torch.from_numpy(offsets).to(DEV))
+    ref, mag = OL.w13_stage(act["xq"], None, np.arange(R), offsets, W)
+    check_close_bf16(np_bf16(out), ref, mag, "E = 1024")
+
+
+@pytest.mark.parametrize("Ks", [24, 250], ids=["panel", "tile"])
+def test_panel_gemm_per_expert_sets(Ks):
+    """One channel set per expert: the panel kernel, and above its largest
+    table the tile kernel."""
+    counts, K, N = [130, 0, 65, 33], 512, 256
+    E, R = len(counts), sum(counts)
+    T = R // 2
+    rng = np.random.default_rng(5)
+    g = torch.Generator().manual_seed(5)
+    x = torch.randn((T, K), generator=g)
+    x[:, ::17] *= 20.0
+    x = x.to(torch.bfloat16)
+    wb = (torch.randn((E, N, K), generator=g) * 0.02).to(torch.bfloat16)
+    tok = np.concatenate([np.sort(rng.integers(0, T, c)) for c in counts]).astype(np.int32)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    w, W = ops.quantize_weight(wb.to(DEV)), oracle_bank(wb)
+    xg, tg, og = x.to(DEV), torch.from_numpy(tok).to(DEV), torch.from_numpy(offsets).to(DEV)
+    xq, _, _ = ops.quantize_act(xg)
+    sel, rq, rows, _, _ = ops.select_channels_per_expert(xg, xq, Ks, tg, og)
+    act = OR.rac_activation_per_expert(np_bf16(x), Ks, tok, offsets)
+    assert np.array_equal(sel.cpu().numpy(), act["sel_pe"])
+    out, _ = ops.grouped_gemm_per_expert(xq, w, R, tg, og, rq, sel, rows)
+    ref, mag = OL.w13_stage_per_expert(act["xq"], act["rq"], act["sel_pe"], tok, offsets, W)
+    check_close_bf16(np_bf16(out), ref, mag, f"per-expert sets, K_s = {Ks}")
