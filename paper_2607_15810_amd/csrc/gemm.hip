@@ -18,6 +18,7 @@
 // chunk; k-step s of the chunk uses its elements 8s..8s+7.  A and B use the
 // same assignment, so each MFMA reduces over a permuted but common K subset.
 #include "gemm_args.h"
+#include "gemm_few.h"
 #include "gemm_panel.h"
 #include "lds_dma.h"
 #include "tile_sched.h"
@@ -1368,13 +1369,14 @@ void launch_tile(const GemmArgs &p, const TlPlan &pl, hipStream_t s) {
                      pl.grp);
 }
 
-// The kernel of a grouped GEMM: the decode kernel for few rows per expert,
-// the panel kernel above, the tile kernel for per-expert sets whose table the
+// The kernel of a grouped GEMM: the few-row kernel for a handful of rows, the
+// decode kernel for few rows per expert, the panel kernel above, the tile kernel for per-expert sets whose table the
 // panel kernel cannot hold, and the generic kernel for sizes none takes.
-enum class Kern { skinny, panel, tile, generic };
+enum class Kern { few, skinny, panel, tile, generic };
 
 struct Choice {
   Kern k;
+  qdf::FwPlan fw;
   SkPlan sk;
   PnPlan pn;
   TlPlan tl;
@@ -1384,7 +1386,14 @@ inline Choice choose(int64_t rows, int E, int64_t N, int64_t K, int Ks, int epil
                      bool per_expert) {
   Choice c{};
   c.k = Kern::generic;
-  if (!per_expert) c.sk = skinny_plan(rows, E, N, K, Ks, epilogue, bitmap);
+  if (!per_expert) {
+    c.fw = qdf::few_plan(rows, E, N, K, Ks, epilogue, bitmap);
+    if (c.fw.ok) {
+      c.k = Kern::few;
+      return c;
+    }
+    c.sk = skinny_plan(rows, E, N, K, Ks, epilogue, bitmap);
+  }
   if (c.sk.ok) {
     c.k = Kern::skinny;
     return c;
@@ -1405,6 +1414,9 @@ template <bool GATHER, bool RAC>
 void launch_epi(const GemmArgs &p, int epi, dim3 grid, hipStream_t s, const Choice &c) {
   const bool sw = epi == QD_EPI_SWIGLU;
   switch (c.k) {
+    case Kern::few:
+      qdf::launch_few(p, epi, c.fw, s);
+      return;
     case Kern::skinny:
       if (sw) launch_skinny<GATHER, RAC, QD_EPI_SWIGLU>(p, c.sk, s);
       else launch_skinny<GATHER, RAC, QD_EPI_NONE>(p, c.sk, s);
@@ -1440,6 +1452,7 @@ int64_t qdi::gemm_amax_written(int64_t rows, int32_t E, int64_t N, int64_t K, in
   if (rows <= 0 || E < 1 || N <= 0 || K <= 0 || Ks < 0) return 0;
   // the grid of the kernel the grouped GEMM takes
   const Choice c = choose(rows, E, N, K, Ks, epilogue, bitmap, false);
+  if (c.k == Kern::few) return c.fw.grid;
   if (c.k == Kern::skinny) return c.sk.grid;
   if (c.k == Kern::panel) return c.pn.grid;
   return grid_x(rows, E, true) * grid_y(N, epilogue);
@@ -1448,7 +1461,8 @@ int64_t qdi::gemm_amax_written(int64_t rows, int32_t E, int64_t N, int64_t K, in
 bool qdi::gemm_takes_bitmap(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
                             int32_t epilogue) {
   if (Ks <= 0 || rows <= 0 || E < 1 || N <= 0 || K <= 0) return false;
-  return skinny_plan(rows, E, N, K, Ks, epilogue, true).ok;
+  const Kern k = choose(rows, E, N, K, Ks, epilogue, true, false).k;
+  return k == Kern::few || k == Kern::skinny;
 }
 
 extern "C" int32_t moe_w4a4_grouped_gemm_residual_form(int64_t rows, int64_t N, int64_t K,
@@ -1461,6 +1475,7 @@ extern "C" int64_t moe_w4a4_grouped_gemm_amax_count(int64_t rows, int64_t N, int
                                                     int32_t E, int32_t Ks, int32_t epilogue) {
   if (rows < 0 || N <= 0 || K <= 0 || E < 1 || Ks < 0) return 0;
   const Choice c = choose(rows, E, N, K, Ks, epilogue, false, false);
+  if (c.k == Kern::few) return c.fw.grid;
   if (c.k == Kern::skinny) return c.sk.grid;
   // every kernel writes (or zeroes) every entry, up to the largest grid
   return std::max<int64_t>(c.k == Kern::panel ? c.pn.grid : 0,
@@ -1555,7 +1570,7 @@ qd_status grouped_gemm_impl(const qd_nvfp4 *a, const int32_t *row_token,
   const int64_t gx = grid_x(rows, E, true), gy = grid_y(N, epilogue);
   if (gx > 0x7fffffffLL || gy > 65535) return QD_ERR_UNSUPPORTED;
   const Choice c = choose(rows, E, N, K, rac ? Ks : 0, epilogue, bitmap != nullptr, per_expert);
-  if (bitmap && c.k != Kern::skinny) return QD_ERR_UNSUPPORTED;
+  if (bitmap && c.k != Kern::few && c.k != Kern::skinny) return QD_ERR_UNSUPPORTED;
   if (per_expert) {
     // per-expert sets take the compact residual (one per grouped row)
     if (!rac || !rq_sel) return QD_ERR_NULL;
