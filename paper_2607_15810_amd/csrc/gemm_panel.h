@@ -13,10 +13,11 @@
 //    into ceil(f / 2 MF) tiles of equal height (to one fragment): a remainder
 //    of a few rows costs the fragments it has, not a second pass over the
 //    weights with nearly empty tiles.
-//  * Persistent: one workgroup per CU walks a static list of tiles
-//    (expert-major, a contiguous range per XCD, so the tiles in flight on an
-//    XCD share an expert's weights or a block of activation rows in its L2).
-//    The stages of all its tiles form one stream through an LDS ring of NS
+//  * Persistent: one workgroup per CU walks a static list of tiles, experts of
+//    tall tiles first, so that the last, partial round of the chip holds the
+//    smallest ones.  An M-tile's weight-row tiles (and the M-tiles of an expert
+//    that has several) go to one XCD, where they share activation rows (and
+//    weights) in its L2.  The stages of all its tiles form one stream through an LDS ring of NS
 //    slots, so the loads of the next tile run under the end of this one.
 //  * A stage is 128 K-elements of the tile's rows, codes and scales of both
 //    operands, filled by direct global->LDS loads (16 rows x 64 contiguous
@@ -45,7 +46,9 @@
 // of up to 320 rows in steps of 32 are what it was built for: a kernel of
 // 256 x 128 tiles with the residual took 1.08 ms there, one of 256 x 256
 // tiles without the residual 0.92 ms against 0.82 ms here, as every expert
-// with 257 rows or more paid a second, nearly empty tile.
+// with 257 rows or more paid a second, nearly empty tile.  With skewed routing
+// (popularity rank^-1.2) the sorted walk is what counts: K = 2048, 4000 tokens,
+// W13 319 -> 291 us, 1000 tokens 152 -> 137 us against one in expert order.
 #pragma once
 #include "gemm_args.h"
 #include "lds_dma.h"
@@ -69,6 +72,7 @@ constexpr int PN_K = 128;
 constexpr int PN_PAD = 4;                // f16 columns past each compact table row
 constexpr int PN_EMAX = 1024;
 constexpr int PN_NSMAX = 6;
+constexpr int PN_TILE = 2;               // a tile's fixed time, in that of a 32-row fragment
 constexpr int PN_LDS_MAX = 160 * 1024 - 512;   // dynamic LDS beside the static arrays
 
 template <int MF>
@@ -86,7 +90,7 @@ struct PnCfg {
 };
 
 struct PnLayout {
-  int tab, sel, tok, dummy, offs, mpre, total;
+  int tab, sel, tok, dummy, offs, mpre, perm, total;
 };
 
 // after the ring: the compact table and S (RAC, compact form), the tokens of
@@ -101,6 +105,7 @@ __host__ __device__ inline PnLayout pn_layout(int mf, int ns, int ksa, int E) {
   L.dummy = take(1024);
   L.offs = take((E + 1) * 4);
   L.mpre = take((E + 1) * 4);
+  L.perm = take(E * 2);
   L.total = o;
   return L;
 }
@@ -150,32 +155,43 @@ struct PnTile {
   int e, row0, nrows, nt;
 };
 
-// Tiles t = mt * ntn + nt; XCD x = b % 8 owns the contiguous range
-// [x * per, x * per + per) and its workgroups (b / 8) take every (G / 8)-th
-// tile of it.  Tiles are visited in increasing order, so an expert cursor
-// advances by a wave ballot over the next 64 experts.
+// The M-tiles run over the experts in the order of perm (mpre: M-tiles before
+// each place of it) and are dealt to the XCDs in groups of cg; XCD x = b % 8
+// walks its groups x, x + 8, .., the weight-row tiles of an M-tile innermost,
+// and its workgroups (b / 8) take every (G / 8)-th tile of that walk.  Place l
+// of the walk: visited in increasing order, so the cursor into perm advances
+// by a wave ballot over the next 64 places.
+// (Integer divisions run on the vector unit: their results are made scalar.)
+struct PnSched {
+  const int32_t *offs, *mpre;
+  const uint16_t *perm;
+  int E, ntn, cg, xcd;
+};
+
 template <int MF>
-__device__ __forceinline__ PnTile pn_locate(const int32_t *offs, const int32_t *mpre, int E,
-                                            int ntn, int t, int &ecur, int lane) {
-  // (integer divisions run on the vector unit: their results are made scalar)
-  const int mt = (int)uni((uint32_t)(t / ntn));
+__device__ __forceinline__ PnTile pn_locate(const PnSched &S, int l, int &cur, int lane) {
+  const int gt = S.cg * S.ntn;
+  const int q = (int)uni((uint32_t)l / (uint32_t)gt), rem = l - q * gt;
+  const int j = (int)uni((uint32_t)rem / (uint32_t)S.ntn);
+  const int mt = (S.xcd + 8 * q) * S.cg + j;
   for (;;) {
-    const int c = ecur + 1 + lane;
-    const bool le = c <= E && mpre[c] <= mt;
+    const int c = cur + 1 + lane;
+    const bool le = c <= S.E && S.mpre[c] <= mt;
     const int adv = __popcll(__ballot(le));
-    ecur = (int)uni((uint32_t)(ecur + adv));
+    cur = (int)uni((uint32_t)(cur + adv));
     if (adv < 64) break;
   }
   PnTile tl;
-  tl.e = ecur;
-  const int o0 = (int)uni((uint32_t)offs[tl.e]), rows = (int)uni((uint32_t)offs[tl.e + 1]) - o0;
-  const int i = mt - (int)uni((uint32_t)mpre[tl.e]);
+  tl.e = (int)uni((uint32_t)S.perm[cur]);
+  const int o0 = (int)uni((uint32_t)S.offs[tl.e]);
+  const int rows = (int)uni((uint32_t)S.offs[tl.e + 1]) - o0;
+  const int i = mt - (int)uni((uint32_t)S.mpre[cur]);
   const int nf = (rows + 31) >> 5, n = (nf + 2 * MF - 1) / (2 * MF);
   const int f0 = (int)uni((uint32_t)(i * nf) / (uint32_t)n);
   const int f1 = (int)uni((uint32_t)((i + 1) * nf) / (uint32_t)n);
   tl.row0 = o0 + 32 * f0;
   tl.nrows = min(32 * f1, rows) - 32 * f0;
-  tl.nt = t - mt * ntn;
+  tl.nt = rem - j * S.ntn;
   return tl;
 }
 
@@ -193,11 +209,12 @@ __device__ __forceinline__ int pn_wrow(int f, int nt, int N) {
 }
 
 template <int MF, int EPI>
-__global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, int ntn, int ns,
-                                                                   int dense) {
+__global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, int ntn, int cg,
+                                                                   int ns, int dense) {
   using C = PnCfg<MF>;
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int sh_w[8];
+  __shared__ int sh_c[8][2 * MF + 1];
   __shared__ float red[16];
   const int tid = threadIdx.x, lane = tid & 63, w = (int)uni((uint32_t)tid >> 6);
   const int K = p.K, N = p.N, E = p.E;
@@ -212,10 +229,12 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, i
   int32_t *sel_l = reinterpret_cast<int32_t *>(lds + L.sel);
   const int32_t *tokb = reinterpret_cast<const int32_t *>(lds + L.tok);
 
-  // ---- the schedule: row offsets and M-tile prefix counts (two experts
-  // per thread, E <= 1024)
+  // ---- the schedule (two experts per thread, E <= 1024): row offsets, the
+  // experts sorted by the height of their tiles, tallest first (then by
+  // index), and the M-tiles before each
+  uint16_t *perm = reinterpret_cast<uint16_t *>(lds + L.perm);
   {
-    int cnt[2], tsum = 0;
+    int cnt[2], cls[2];
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const int e = 2 * tid + q;
@@ -225,7 +244,39 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, i
         offs[e] = o0;
       }
       if (e < E) o1 = p.offsets ? p.offsets[e + 1] : (int)p.rows;
-      cnt[q] = e < E ? ((max(o1 - o0, 0) + 31) / 32 + 2 * MF - 1) / (2 * MF) : 0;
+      const int nf = e < E ? (max(o1 - o0, 0) + 31) / 32 : 0;
+      cnt[q] = (nf + 2 * MF - 1) / (2 * MF);
+      // sorting class: 2 MF - height of the expert's tallest tile (2 MF: none)
+      cls[q] = e >= E ? -1 : nf == 0 ? 2 * MF : 2 * MF - (nf + cnt[q] - 1) / cnt[q];
+    }
+    if (E == PN_EMAX && tid == 0) offs[E] = p.offsets ? p.offsets[E] : (int)p.rows;
+    int pos[2] = {0, 0};
+    const uint64_t lt = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int c = 0; c <= 2 * MF; ++c) {
+      const uint64_t b0 = __ballot(cls[0] == c), b1 = __ballot(cls[1] == c);
+      const int below = __popcll(b0 & lt) + __popcll(b1 & lt);
+      if (cls[0] == c) pos[0] = below;
+      if (cls[1] == c) pos[1] = below + (cls[0] == c ? 1 : 0);
+      if (lane == 0) sh_c[w][c] = __popcll(b0) + __popcll(b1);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (cls[q] < 0) continue;
+      int at = pos[q];
+      for (int c = 0; c < cls[q]; ++c)
+        for (int ww = 0; ww < 8; ++ww) at += sh_c[ww][c];
+      for (int ww = 0; ww < w; ++ww) at += sh_c[ww][cls[q]];
+      perm[at] = (uint16_t)(2 * tid + q);
+      mpre[at] = cnt[q];
+    }
+    __syncthreads();
+    // M-tile counts to prefix sums, in place
+    int tsum = 0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      cnt[q] = 2 * tid + q < E ? mpre[2 * tid + q] : 0;
       tsum += cnt[q];
     }
     int xs = tsum;
@@ -235,7 +286,6 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, i
       if (lane >= o) xs += y;
     }
     if (lane == 63) sh_w[w] = xs;
-    if (E == PN_EMAX && tid == 0) offs[E] = p.offsets ? p.offsets[E] : (int)p.rows;
     __syncthreads();
     int base = xs - tsum;
     for (int ww = 0; ww < w; ++ww) base += sh_w[ww];
@@ -273,11 +323,17 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, i
   const int nmain = res_on && dense ? 2 * nst : nst;
   const int nres = res_on && cmp ? (ksa + 31) >> 5 : 0;
   __syncthreads();
-  const int T = (int)uni((uint32_t)mpre[E]) * ntn;
-  const int G = gridDim.x, nsl = G >> 3, xcd = blockIdx.x & 7, slot0 = blockIdx.x >> 3;
-  const int per = (T + 7) >> 3;
-  const int t_end = min(T, (xcd + 1) * per);
-  int ct = xcd * per + slot0;              // the tile being multiplied
+  const PnSched S{offs, mpre, perm, E, ntn, cg, (int)(blockIdx.x & 7)};
+  const int nsl = gridDim.x >> 3;
+  int t_end;                               // tiles of this XCD's walk
+  {
+    const int mts = (int)uni((uint32_t)mpre[E]);
+    const int ng = (int)uni((uint32_t)(mts + cg - 1) / (uint32_t)cg);
+    const int nq = ng > S.xcd ? (ng - S.xcd + 7) >> 3 : 0;
+    const bool last = ng > 0 && ((ng - 1) & 7) == S.xcd;     // the group that may be short
+    t_end = (nq * cg - (last ? ng * cg - mts : 0)) * ntn;
+  }
+  int ct = blockIdx.x >> 3;                // the tile being multiplied
   float vmax = 0.0f;
 
   // two waves of a SIMD (w, w + 4) take different row halves
@@ -346,7 +402,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, i
     phase = 0;
     left = nst;
     if (it + nsl < t_end) {
-      nx = pn_locate<MF>(offs, mpre, E, ntn, it + nsl, ecur, lane);
+      nx = pn_locate<MF>(S, it + nsl, ecur, lane);
       tok_dma(nx, ibuf ^ 1);
     }
   };
@@ -448,7 +504,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, i
   };
 
   if (it < t_end) {
-    itl = pn_locate<MF>(offs, mpre, E, ntn, it, ecur, lane);
+    itl = pn_locate<MF>(S, it, ecur, lane);
     tok_dma(itl, 0);
     wait_vm<0>();
     pn_barrier();
@@ -751,20 +807,20 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, i
 }
 
 template <int MF, int EPI>
-void launch_panel_epi(const GemmArgs &p, int ntn, int grid, int ns, int dense, int lds,
+void launch_panel_epi(const GemmArgs &p, int ntn, int cg, int grid, int ns, int dense, int lds,
                       hipStream_t s) {
   auto kern = gemm_panel_kernel<MF, EPI>;
   static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                                PN_LDS_MAX) == hipSuccess;
   (void)attr;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(PN_THREADS), (size_t)lds, s, p, ntn, ns,
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(PN_THREADS), (size_t)lds, s, p, ntn, cg, ns,
                      dense);
 }
 
 // one compiled tile height each (gemm_panel_<MF>.hip)
 template <int MF>
-void launch_panel(const GemmArgs &p, int epi, int ntn, int grid, int ns, int dense, int lds,
+void launch_panel(const GemmArgs &p, int epi, int ntn, int cg, int grid, int ns, int dense, int lds,
                   hipStream_t s);
 
 }  // namespace qdp
