@@ -34,49 +34,113 @@ __global__ __launch_bounds__(256) void quantize_act_kernel(
                                  n_part, codes, scales, gscale, scores, ramax);
 }
 
-// Weight amax per group: grid (P, G); part[g * P + p].
+// The weight quantiser reads the bank twice, since a group's first code needs
+// its amax, and both passes run at what HBM gives: 4.6 bytes per element, 337
+// us for 128 x 1536 x 2048 (5.5 TB/s).  (Interleaving the two over parts of the
+// bank that fit the 256 MB Infinity Cache, so that the second read of a part
+// hits there, gained nothing: 358 us at best, the launches' ends included.)
+//
+// Weight amax per group: grid (P, G); part[g * P + b].  Four loads in flight per
+// thread.
 __global__ __launch_bounds__(256) void amax_group_kernel(const uint16_t *__restrict__ w,
                                                          int64_t n16_per_group,
                                                          float *__restrict__ part) {
   __shared__ float red[16];
   const int64_t g = blockIdx.y;
+  const int P = gridDim.x, s = blockIdx.x;
   const void *base = w + g * n16_per_group * 16;
   float m = 0.0f;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n16_per_group; b += stride) {
-    float v[16];
-    Loader<uint16_t>::load16(base, b * 16, v);
+  const int64_t stride = (int64_t)P * 256;
+  int64_t i = (int64_t)s * 256 + threadIdx.x;
+  for (; i + 3 * stride < n16_per_group; i += 4 * stride) {
+    Loader<uint16_t>::Raw r[4];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) m = fmaxf(m, fabsf(v[i]));
+    for (int q = 0; q < 4; ++q) Loader<uint16_t>::load_raw(base, (i + q * stride) * 16, r[q]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float v[16];
+      Loader<uint16_t>::unpack(r[q], v);
+#pragma unroll
+      for (int j = 0; j < 16; ++j) m = fmaxf(m, fabsf(v[j]));
+    }
+  }
+  for (; i < n16_per_group; i += stride) {
+    float v[16];
+    Loader<uint16_t>::load16(base, i * 16, v);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) m = fmaxf(m, fabsf(v[j]));
   }
   m = block_max(m, red);
-  if (threadIdx.x == 0) part[g * gridDim.x + blockIdx.x] = m;
+  if (threadIdx.x == 0) part[g * P + s] = m;
 }
 
-// Q_W: grid (tiles, G); each thread quantises one 16-element block of group g.
-__global__ __launch_bounds__(256) void quantize_weight_kernel(
-    const uint16_t *__restrict__ w, int64_t n16_per_group, const float *__restrict__ part,
-    int n_part, uint8_t *__restrict__ codes, uint8_t *__restrict__ scales,
-    float *__restrict__ gscale) {
+// Q_W: grid (Q, G); each thread quantises one 16-element block at a time.  With
+// FRAG (rows a multiple of 16, columns of 256) a workgroup's 256 blocks are 16
+// rows x 256 columns, whose scales are one contiguous record of the
+// fragment-ordered copy (nvfp4_pack_frag_scales), written in the same pass (a
+// pass of its own took 24 of 355 us at 128 x 1536 x 2048); else they are 256
+// blocks in storage order.
+template <bool FRAG>
+__global__ __launch_bounds__(256) void quantize_group_kernel(
+    const uint16_t *__restrict__ w, int64_t n16_per_group, int nbc,
+    const float *__restrict__ part, int P, uint8_t *__restrict__ codes,
+    uint8_t *__restrict__ scales, float *__restrict__ gscale, uint8_t *__restrict__ frag) {
   __shared__ float red[16];
   const int64_t g = blockIdx.y;
-  const float amax = block_max(partials_max(part + g * n_part, n_part), red);
+  const int Q = gridDim.x, s = blockIdx.x;
+  const int row = threadIdx.x >> 4, col = threadIdx.x & 15;
+  const int nchunk = FRAG ? nbc >> 4 : 1;
+  const int ntile = (int)((n16_per_group + 255) >> 8);
+  const auto block_of = [&](int t) -> int64_t {
+    if (!FRAG) return (int64_t)t * 256 + threadIdx.x;
+    const int f = t / nchunk, c = t - f * nchunk;
+    return (int64_t)(16 * f + row) * nbc + 16 * c + col;
+  };
+  // two tiles in flight: each is loaded two before its turn, the first ones
+  // before the partials are looked at
+  Loader<uint16_t>::Raw r[2];
+  const uint16_t *wg = w + g * n16_per_group * 16;
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    if (s + q * Q < ntile && block_of(s + q * Q) < n16_per_group)
+      Loader<uint16_t>::load_raw(wg, block_of(s + q * Q) * 16, r[q]);
+  const float amax = block_max(partials_max(part + g * P, P), red);
   float s_enc, s_dec;
   tensor_scale(amax, s_enc, s_dec);
   const bool zero_tensor = !(amax >= kZeroAmax);
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (s == 0 && threadIdx.x == 0) {
     gscale[2 * g] = s_enc;
     gscale[2 * g + 1] = s_dec;
   }
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < n16_per_group; b += stride) {
-    const int64_t gb = g * n16_per_group + b;
-    float v[16];
-    Loader<uint16_t>::load16(w, gb * 16, v);
-    uint32_t lo, hi;
-    uint32_t sb = quantize_block(v, s_enc, zero_tensor, lo, hi);
-    reinterpret_cast<uint2 *>(codes)[gb] = make_uint2(lo, hi);
-    scales[gb] = (uint8_t)sb;
+  for (int t0 = s; t0 < ntile; t0 += 2 * Q) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int t = t0 + q * Q;
+      if (t >= ntile) break;
+      const int64_t i = block_of(t);
+      uint32_t sb = 0;
+      if (i < n16_per_group) {
+        const int64_t gb = g * n16_per_group + i;
+        float v[16];
+        Loader<uint16_t>::unpack(r[q], v);
+        if (t + 2 * Q < ntile) {
+          const int64_t in = block_of(t + 2 * Q);
+          if (in < n16_per_group) Loader<uint16_t>::load_raw(wg, in * 16, r[q]);
+        }
+        uint32_t lo, hi;
+        sb = quantize_block(v, s_enc, zero_tensor, lo, hi);
+        reinterpret_cast<uint2 *>(codes)[gb] = make_uint2(lo, hi);
+        scales[gb] = (uint8_t)sb;
+      }
+      if (FRAG) {
+        // the scales of four neighbouring blocks are one dword of the record
+        uint32_t d = sb << (8 * (col & 3));
+        d |= __shfl_xor(d, 1, 64);
+        d |= __shfl_xor(d, 2, 64);
+        if ((col & 3) == 0)
+          reinterpret_cast<uint32_t *>(frag + (g * ntile + t) * 256)[16 * (col >> 2) + row] = d;
+      }
+    }
   }
 }
 
@@ -211,14 +275,21 @@ extern "C" qd_status nvfp4_quantize_weight(const void *w, int64_t groups, int64_
   hipStream_t s = qdh::S(stream);
   const int64_t n16 = rows * cols / 16;
   float *part = static_cast<float *>(ws);
-  const int P = 64;
-  hipLaunchKernelGGL(amax_group_kernel, dim3(P, (unsigned)groups), dim3(256), 0, s,
-                     static_cast<const uint16_t *>(w), n16, part);
-  int64_t tiles = (n16 + 255) / 256;
-  if (tiles > 1024) tiles = 1024;
-  hipLaunchKernelGGL(quantize_weight_kernel, dim3((unsigned)tiles, (unsigned)groups), dim3(256), 0,
-                     s, static_cast<const uint16_t *>(w), n16, part, P, out->codes, out->scales,
-                     out->gscale);
+  constexpr int P = 64;
+  // the fragment-ordered copy of the scales, where the caller gave it room
+  // and the sizes have one
+  const bool frag = out->scales_frag != nullptr && qdh::aligned16(out->scales_frag) &&
+                    rows % 16 == 0 && cols % 256 == 0;
+  const dim3 grid((unsigned)std::min<int64_t>((n16 + 255) / 256, 256), (unsigned)groups);
+  const uint16_t *wb = static_cast<const uint16_t *>(w);
+  hipLaunchKernelGGL(amax_group_kernel, dim3(P, (unsigned)groups), dim3(256), 0, s, wb, n16, part);
+  if (frag)
+    hipLaunchKernelGGL(quantize_group_kernel<true>, grid, dim3(256), 0, s, wb, n16,
+                       (int)(cols / 16), part, P, out->codes, out->scales, out->gscale,
+                       out->scales_frag);
+  else
+    hipLaunchKernelGGL(quantize_group_kernel<false>, grid, dim3(256), 0, s, wb, n16,
+                       (int)(cols / 16), part, P, out->codes, out->scales, out->gscale, nullptr);
   return qdh::check_launch();
 }
 

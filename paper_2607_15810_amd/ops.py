@@ -105,10 +105,11 @@ def quantize_weight(w, frag_scales=True):
     G, R, C = w.shape
     out = NVFP4Tensor.empty(G, R, C, w.device)
     ws = _ws(Q.lib().nvfp4_quantize_weight_workspace(G, R, C), w.device)
+    if frag_scales and R > 0 and Q.lib().nvfp4_frag_scales_bytes(G, R, C) > 0:
+        out.scales_frag = torch.empty((G, R // 16, C // 256, 256), dtype=torch.uint8,
+                                      device=w.device)      # written by the same call
     Q.call("nvfp4_quantize_weight", w.data_ptr(), G, R, C, _nv(out), ws.data_ptr(), ws.numel(),
            _stream())
-    if frag_scales and Q.lib().nvfp4_frag_scales_bytes(G, R, C) > 0:
-        out.scales_frag = pack_frag_scales(out)
     return out
 
 
