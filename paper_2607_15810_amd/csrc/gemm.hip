@@ -1324,34 +1324,17 @@ inline PnPlan panel_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, bool
       (rows + 320) * N * 2 >= (1LL << 32))
     return pl;
   pl.ntn = (int)((N + qdp::PN_N - 1) / qdp::PN_N);
-  // The tile height with the least estimated time: whole rounds of the 256
-  // CUs, each the time of a tile of average height.  The expected number of
-  // tiles is that of uniform routing (normal counts per expert).  (160 +- 13
-  // rows on each of 64 experts, 2048 weight rows: 192-row tiles make 520 tiles
-  // of them, a third round for eight, and 159 us; 320-row tiles 512 and 117 us.)
-  const double mean = (double)rows / E, sd = std::max(0.5, sqrt(mean));
   const int nst = (int)(K / qdp::PN_K);
-  double best = 0.0;
-  for (const int mf : {1, 2, 3, 5}) {
+  const qdp::PnHeight h = qdp::pn_height(rows, E, pl.ntn, [&](int mf) {
     int ns = std::min(qdp::PN_NSMAX, nst);
     while (ns >= 2 && qdp::pn_layout(mf, ns, ksa, E).total > qdp::PN_LDS_MAX) --ns;
-    if (ns < 2) continue;
-    double n = E > 1 ? 0.0 : std::ceil(mean / (64.0 * mf));
-    for (int j = 0; E > 1 && j <= mean / (64.0 * mf) + 4.0; ++j)
-      n += 0.5 * erfc((64.0 * mf * j - mean) / (sd * 1.4142135623730951));
-    n = std::max(n, 1.0 / E);
-    const double rounds = std::max(1.0, std::ceil((n * E - 0.2) * pl.ntn / 256.0));
-    const double t = rounds * (qdp::PN_TILE + (mean / 32.0 + 0.5) / n);
-    if (pl.mf == 0 || t < 0.999 * best) {     // even: the lower, its ring is deeper
-      best = t;
-      pl.mf = mf;
-      pl.ns = ns;
-      pl.lds = qdp::pn_layout(mf, ns, ksa, E).total;
-      // M-tiles dealt to the XCDs in the number an average expert has
-      pl.cg = std::max(1, std::min(8, (int)(n + 0.5)));
-    }
-  }
-  if (pl.mf == 0) return pl;
+    return ns;
+  });
+  if (h.mf == 0) return pl;
+  pl.mf = h.mf;
+  pl.ns = h.ns;
+  pl.cg = h.cg;
+  pl.lds = qdp::pn_layout(h.mf, h.ns, ksa, E).total;
   // persistent: one workgroup per CU (256), a multiple of 8 (the XCDs)
   pl.grid = (int)std::min<int64_t>(256, qdt::tile_grid(rows, E, 64 * pl.mf, pl.ntn));
   pl.ok = true;

@@ -52,7 +52,7 @@
 #pragma once
 #include "gemm_args.h"
 #include "lds_dma.h"
-#include "tile_sched.h"
+#include "panel_sched.h"
 
 namespace qdp {
 
@@ -66,14 +66,8 @@ using qdg::mfma32;
 using qdg::swiglu_fast;
 using qdg::word_of;
 
-constexpr int PN_THREADS = 512;
-constexpr int PN_N = 256;
 constexpr int PN_K = 128;
 constexpr int PN_PAD = 4;                // f16 columns past each compact table row
-constexpr int PN_EMAX = 1024;
-constexpr int PN_NSMAX = 6;
-constexpr int PN_TILE = 2;               // a tile's fixed time, in that of a 32-row fragment
-constexpr int PN_LDS_MAX = 160 * 1024 - 512;   // dynamic LDS beside the static arrays
 
 template <int MF>
 struct PnCfg {
@@ -114,33 +108,6 @@ __host__ __device__ inline PnLayout pn_layout(int mf, int ns, int ksa, int E) {
 // p ^ pn_swz(ri) of the row's 64-byte LDS record
 __device__ __forceinline__ int pn_swz(int ri) { return ((ri >> 1) ^ (ri >> 2)) & 3; }
 
-template <int LPS>
-__device__ __forceinline__ void pn_wait(int stages) {
-  switch (stages) {      // uniform
-    case 0: wait_vm<0>(); break;
-    case 1: wait_vm<LPS>(); break;
-    case 2: wait_vm<2 * LPS>(); break;
-    case 3: wait_vm<3 * LPS>(); break;
-    default: wait_vm<4 * LPS>(); break;
-  }
-}
-// this wave's LDS reads and writes are done, then the workgroup's barrier
-__device__ __forceinline__ void pn_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// the same value, computed anew from here on: keeps the address arithmetic of
-// the parts outside the K loop from being hoisted above it, where it would
-// hold registers the accumulators need
-__device__ __forceinline__ int pn_fresh(int v) {
-  asm volatile("" : "+v"(v));
-  return v;
-}
-__device__ __forceinline__ int pn_fresh_s(int v) {
-  asm volatile("" : "+s"(v));
-  return v;
-}
-
 // the kernel's arguments read anew from the kernarg segment (GemmArgs is the
 // kernel's first parameter): those the K loop seldom needs hold no scalar
 // registers across it
@@ -149,50 +116,6 @@ __device__ __forceinline__ PnArgPtr pn_args() {
   PnArgPtr q = (PnArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(q));
   return q;
-}
-
-struct PnTile {
-  int e, row0, nrows, nt;
-};
-
-// The M-tiles run over the experts in the order of perm (mpre: M-tiles before
-// each place of it) and are dealt to the XCDs in groups of cg; XCD x = b % 8
-// walks its groups x, x + 8, .., the weight-row tiles of an M-tile innermost,
-// and its workgroups (b / 8) take every (G / 8)-th tile of that walk.  Place l
-// of the walk: visited in increasing order, so the cursor into perm advances
-// by a wave ballot over the next 64 places.
-// (Integer divisions run on the vector unit: their results are made scalar.)
-struct PnSched {
-  const int32_t *offs, *mpre;
-  const uint16_t *perm;
-  int E, ntn, cg, xcd;
-};
-
-template <int MF>
-__device__ __forceinline__ PnTile pn_locate(const PnSched &S, int l, int &cur, int lane) {
-  const int gt = S.cg * S.ntn;
-  const int q = (int)uni((uint32_t)l / (uint32_t)gt), rem = l - q * gt;
-  const int j = (int)uni((uint32_t)rem / (uint32_t)S.ntn);
-  const int mt = (S.xcd + 8 * q) * S.cg + j;
-  for (;;) {
-    const int c = cur + 1 + lane;
-    const bool le = c <= S.E && S.mpre[c] <= mt;
-    const int adv = __popcll(__ballot(le));
-    cur = (int)uni((uint32_t)(cur + adv));
-    if (adv < 64) break;
-  }
-  PnTile tl;
-  tl.e = (int)uni((uint32_t)S.perm[cur]);
-  const int o0 = (int)uni((uint32_t)S.offs[tl.e]);
-  const int rows = (int)uni((uint32_t)S.offs[tl.e + 1]) - o0;
-  const int i = mt - (int)uni((uint32_t)S.mpre[cur]);
-  const int nf = (rows + 31) >> 5, n = (nf + 2 * MF - 1) / (2 * MF);
-  const int f0 = (int)uni((uint32_t)(i * nf) / (uint32_t)n);
-  const int f1 = (int)uni((uint32_t)((i + 1) * nf) / (uint32_t)n);
-  tl.row0 = o0 + 32 * f0;
-  tl.nrows = min(32 * f1, rows) - 32 * f0;
-  tl.nt = rem - j * S.ntn;
-  return tl;
 }
 
 // the tile's 32-row weight fragment f (0..7) starts at this weight row (0 for
@@ -229,74 +152,8 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, i
   int32_t *sel_l = reinterpret_cast<int32_t *>(lds + L.sel);
   const int32_t *tokb = reinterpret_cast<const int32_t *>(lds + L.tok);
 
-  // ---- the schedule (two experts per thread, E <= 1024): row offsets, the
-  // experts sorted by the height of their tiles, tallest first (then by
-  // index), and the M-tiles before each
   uint16_t *perm = reinterpret_cast<uint16_t *>(lds + L.perm);
-  {
-    int cnt[2], cls[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int e = 2 * tid + q;
-      int o0 = 0, o1 = 0;
-      if (e <= E) {
-        o0 = p.offsets ? p.offsets[e] : (e == 0 ? 0 : (int)p.rows);
-        offs[e] = o0;
-      }
-      if (e < E) o1 = p.offsets ? p.offsets[e + 1] : (int)p.rows;
-      const int nf = e < E ? (max(o1 - o0, 0) + 31) / 32 : 0;
-      cnt[q] = (nf + 2 * MF - 1) / (2 * MF);
-      // sorting class: 2 MF - height of the expert's tallest tile (2 MF: none)
-      cls[q] = e >= E ? -1 : nf == 0 ? 2 * MF : 2 * MF - (nf + cnt[q] - 1) / cnt[q];
-    }
-    if (E == PN_EMAX && tid == 0) offs[E] = p.offsets ? p.offsets[E] : (int)p.rows;
-    int pos[2] = {0, 0};
-    const uint64_t lt = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int c = 0; c <= 2 * MF; ++c) {
-      const uint64_t b0 = __ballot(cls[0] == c), b1 = __ballot(cls[1] == c);
-      const int below = __popcll(b0 & lt) + __popcll(b1 & lt);
-      if (cls[0] == c) pos[0] = below;
-      if (cls[1] == c) pos[1] = below + (cls[0] == c ? 1 : 0);
-      if (lane == 0) sh_c[w][c] = __popcll(b0) + __popcll(b1);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (cls[q] < 0) continue;
-      int at = pos[q];
-      for (int c = 0; c < cls[q]; ++c)
-        for (int ww = 0; ww < 8; ++ww) at += sh_c[ww][c];
-      for (int ww = 0; ww < w; ++ww) at += sh_c[ww][cls[q]];
-      perm[at] = (uint16_t)(2 * tid + q);
-      mpre[at] = cnt[q];
-    }
-    __syncthreads();
-    // M-tile counts to prefix sums, in place
-    int tsum = 0;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      cnt[q] = 2 * tid + q < E ? mpre[2 * tid + q] : 0;
-      tsum += cnt[q];
-    }
-    int xs = tsum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(xs, o, 64);
-      if (lane >= o) xs += y;
-    }
-    if (lane == 63) sh_w[w] = xs;
-    __syncthreads();
-    int base = xs - tsum;
-    for (int ww = 0; ww < w; ++ww) base += sh_w[ww];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int e = 2 * tid + q;
-      if (e <= E) mpre[e] = base;
-      base += cnt[q];
-    }
-    if (E == PN_EMAX && tid == PN_THREADS - 1) mpre[E] = base;
-  }
+  pn_schedule<MF>(p.offsets, p.rows, E, offs, mpre, perm, sh_w, sh_c);
   const bool per_expert = p.sel_stride != 0;
   if (cmp) {
     if (!per_expert)
@@ -325,14 +182,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, i
   __syncthreads();
   const PnSched S{offs, mpre, perm, E, ntn, cg, (int)(blockIdx.x & 7)};
   const int nsl = gridDim.x >> 3;
-  int t_end;                               // tiles of this XCD's walk
-  {
-    const int mts = (int)uni((uint32_t)mpre[E]);
-    const int ng = (int)uni((uint32_t)(mts + cg - 1) / (uint32_t)cg);
-    const int nq = ng > S.xcd ? (ng - S.xcd + 7) >> 3 : 0;
-    const bool last = ng > 0 && ((ng - 1) & 7) == S.xcd;     // the group that may be short
-    t_end = (nq * cg - (last ? ng * cg - mts : 0)) * ntn;
-  }
+  const int t_end = pn_walk(S);            // tiles of this XCD's walk
   int ct = blockIdx.x >> 3;                // the tile being multiplied
   float vmax = 0.0f;
 

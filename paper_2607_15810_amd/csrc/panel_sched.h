@@ -1,0 +1,208 @@
+// The tile schedule of the persistent prefill GEMMs (tiles of up to 64 MF rows
+// of one expert x 256 weight rows, one workgroup of eight waves per CU), and
+// the waits of their LDS rings.
+#pragma once
+#include <algorithm>
+#include <cmath>
+
+#include "common.h"
+#include "lds_dma.h"
+#include "tile_sched.h"
+
+namespace qdp {
+
+using namespace qd;
+using namespace qdl;
+
+constexpr int PN_THREADS = 512;
+constexpr int PN_N = 256;
+constexpr int PN_EMAX = 1024;
+constexpr int PN_NSMAX = 6;
+constexpr int PN_TILE = 2;               // a tile's fixed time, in that of a 32-row fragment
+constexpr int PN_LDS_MAX = 160 * 1024 - 512;   // dynamic LDS beside the static arrays
+
+template <int LPS>
+__device__ __forceinline__ void pn_wait(int stages) {
+  switch (stages) {      // uniform
+    case 0: wait_vm<0>(); break;
+    case 1: wait_vm<LPS>(); break;
+    case 2: wait_vm<2 * LPS>(); break;
+    case 3: wait_vm<3 * LPS>(); break;
+    default: wait_vm<4 * LPS>(); break;
+  }
+}
+// this wave's LDS reads and writes are done, then the workgroup's barrier
+__device__ __forceinline__ void pn_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// the same value, computed anew from here on: keeps the address arithmetic of
+// the parts outside the K loop from being hoisted above it, where it would
+// hold registers the accumulators need
+__device__ __forceinline__ int pn_fresh(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+__device__ __forceinline__ int pn_fresh_s(int v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
+struct PnTile {
+  int e, row0, nrows, nt;
+};
+
+// The M-tiles run over the experts in the order of perm (mpre: M-tiles before
+// each place of it) and are dealt to the XCDs in groups of cg; XCD x = b % 8
+// walks its groups x, x + 8, .., the weight-row tiles of an M-tile innermost,
+// and its workgroups (b / 8) take every (G / 8)-th tile of that walk.  Place l
+// of the walk: visited in increasing order, so the cursor into perm advances
+// by a wave ballot over the next 64 places.
+// (Integer divisions run on the vector unit: their results are made scalar.)
+struct PnSched {
+  const int32_t *offs, *mpre;
+  const uint16_t *perm;
+  int E, ntn, cg, xcd;
+};
+
+template <int MF>
+__device__ __forceinline__ PnTile pn_locate(const PnSched &S, int l, int &cur, int lane) {
+  const int gt = S.cg * S.ntn;
+  const int q = (int)uni((uint32_t)l / (uint32_t)gt), rem = l - q * gt;
+  const int j = (int)uni((uint32_t)rem / (uint32_t)S.ntn);
+  const int mt = (S.xcd + 8 * q) * S.cg + j;
+  for (;;) {
+    const int c = cur + 1 + lane;
+    const bool le = c <= S.E && S.mpre[c] <= mt;
+    const int adv = __popcll(__ballot(le));
+    cur = (int)uni((uint32_t)(cur + adv));
+    if (adv < 64) break;
+  }
+  PnTile tl;
+  tl.e = (int)uni((uint32_t)S.perm[cur]);
+  const int o0 = (int)uni((uint32_t)S.offs[tl.e]);
+  const int rows = (int)uni((uint32_t)S.offs[tl.e + 1]) - o0;
+  const int i = mt - (int)uni((uint32_t)S.mpre[cur]);
+  const int nf = (rows + 31) >> 5, n = (nf + 2 * MF - 1) / (2 * MF);
+  const int f0 = (int)uni((uint32_t)(i * nf) / (uint32_t)n);
+  const int f1 = (int)uni((uint32_t)((i + 1) * nf) / (uint32_t)n);
+  tl.row0 = o0 + 32 * f0;
+  tl.nrows = min(32 * f1, rows) - 32 * f0;
+  tl.nt = rem - j * S.ntn;
+  return tl;
+}
+
+// tiles of the walk of S's XCD
+__device__ __forceinline__ int pn_walk(const PnSched &S) {
+  const int mts = (int)uni((uint32_t)S.mpre[S.E]);
+  const int ng = (int)uni((uint32_t)(mts + S.cg - 1) / (uint32_t)S.cg);
+  const int nq = ng > S.xcd ? (ng - S.xcd + 7) >> 3 : 0;
+  const bool last = ng > 0 && ((ng - 1) & 7) == S.xcd;     // the group that may be short
+  return (nq * S.cg - (last ? ng * S.cg - mts : 0)) * S.ntn;
+}
+
+// The schedule (two experts per thread, E <= 1024): row offsets, the experts
+// sorted by the height of their tiles, tallest first (then by index), and the
+// M-tiles before each.  The caller's barrier makes mpre visible.
+template <int MF>
+__device__ __forceinline__ void pn_schedule(const int32_t *offsets, int64_t rows, int E,
+                                            int32_t *offs, int32_t *mpre, uint16_t *perm,
+                                            int *sh_w, int (*sh_c)[2 * MF + 1]) {
+  const int tid = threadIdx.x, lane = tid & 63, w = (int)uni((uint32_t)tid >> 6);
+  int cnt[2], cls[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int e = 2 * tid + q;
+    int o0 = 0, o1 = 0;
+    if (e <= E) {
+      o0 = offsets ? offsets[e] : (e == 0 ? 0 : (int)rows);
+      offs[e] = o0;
+    }
+    if (e < E) o1 = offsets ? offsets[e + 1] : (int)rows;
+    const int nf = e < E ? (max(o1 - o0, 0) + 31) / 32 : 0;
+    cnt[q] = (nf + 2 * MF - 1) / (2 * MF);
+    // sorting class: 2 MF - height of the expert's tallest tile (2 MF: none)
+    cls[q] = e >= E ? -1 : nf == 0 ? 2 * MF : 2 * MF - (nf + cnt[q] - 1) / cnt[q];
+  }
+  if (E == PN_EMAX && tid == 0) offs[E] = offsets ? offsets[E] : (int)rows;
+  int pos[2] = {0, 0};
+  const uint64_t lt = (1ull << lane) - 1ull;
+#pragma unroll
+  for (int c = 0; c <= 2 * MF; ++c) {
+    const uint64_t b0 = __ballot(cls[0] == c), b1 = __ballot(cls[1] == c);
+    const int below = __popcll(b0 & lt) + __popcll(b1 & lt);
+    if (cls[0] == c) pos[0] = below;
+    if (cls[1] == c) pos[1] = below + (cls[0] == c ? 1 : 0);
+    if (lane == 0) sh_c[w][c] = __popcll(b0) + __popcll(b1);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    if (cls[q] < 0) continue;
+    int at = pos[q];
+    for (int c = 0; c < cls[q]; ++c)
+      for (int ww = 0; ww < 8; ++ww) at += sh_c[ww][c];
+    for (int ww = 0; ww < w; ++ww) at += sh_c[ww][cls[q]];
+    perm[at] = (uint16_t)(2 * tid + q);
+    mpre[at] = cnt[q];
+  }
+  __syncthreads();
+  // M-tile counts to prefix sums, in place
+  int tsum = 0;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    cnt[q] = 2 * tid + q < E ? mpre[2 * tid + q] : 0;
+    tsum += cnt[q];
+  }
+  int xs = tsum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(xs, o, 64);
+    if (lane >= o) xs += y;
+  }
+  if (lane == 63) sh_w[w] = xs;
+  __syncthreads();
+  int base = xs - tsum;
+  for (int ww = 0; ww < w; ++ww) base += sh_w[ww];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int e = 2 * tid + q;
+    if (e <= E) mpre[e] = base;
+    base += cnt[q];
+  }
+  if (E == PN_EMAX && tid == PN_THREADS - 1) mpre[E] = base;
+}
+
+// The tile height with the least estimated time: whole rounds of the 256 CUs,
+// each the time of a tile of average height.  The expected number of tiles is
+// that of uniform routing (normal counts per expert).  (160 +- 13 rows on each
+// of 64 experts, 2048 weight rows: 192-row tiles make 520 tiles of them, a third
+// round for eight, and 159 us; 320-row tiles 512 and 117 us.)  ns_of(mf): the
+// ring depth that height leaves room for (< 2: none).
+struct PnHeight {
+  int mf, ns, cg;
+};
+template <typename F>
+inline PnHeight pn_height(int64_t rows, int E, int ntn, F ns_of) {
+  PnHeight h{};
+  const double mean = (double)rows / E, sd = std::max(0.5, sqrt(mean));
+  double best = 0.0;
+  for (const int mf : {1, 2, 3, 5}) {
+    const int ns = ns_of(mf);
+    if (ns < 2) continue;
+    double n = E > 1 ? 0.0 : std::ceil(mean / (64.0 * mf));
+    for (int j = 0; E > 1 && j <= mean / (64.0 * mf) + 4.0; ++j)
+      n += 0.5 * erfc((64.0 * mf * j - mean) / (sd * 1.4142135623730951));
+    n = std::max(n, 1.0 / E);
+    const double rounds = std::max(1.0, std::ceil((n * E - 0.2) * ntn / 256.0));
+    const double t = rounds * (PN_TILE + (mean / 32.0 + 0.5) / n);
+    if (h.mf == 0 || t < 0.999 * best) {     // even: the lower, its ring is deeper
+      best = t;
+      // M-tiles dealt to the XCDs in the number an average expert has
+      h = {mf, ns, std::max(1, std::min(8, (int)(n + 0.5)))};
+    }
+  }
+  return h;
+}
+
+}  // namespace qdp

@@ -8,7 +8,8 @@
 // a bf16 activation times it is exact in f32.  The tensor scale s_dec of the
 // expert multiplies the f32 sum in the epilogue.
 //
-// Kernel: tiles of 128 grouped rows x 256 weight rows (SwiGLU: 128 gate rows
+// gemm_rows.h holds the kernel for all but the smallest K and the largest
+// operands.  The general kernel here: tiles of 128 grouped rows x 256 weight rows (SwiGLU: 128 gate rows
 // and the matching 128 up rows), eight waves in a 2 x 4 grid of 64 x 64 on
 // v_mfma_f32_32x32x16_bf16; the wide weight tile halves how often the bf16
 // activations are re-read (once per weight tile).  K streams in stages of 64 through a double
@@ -20,6 +21,7 @@
 // distinct banks.  M-tiles follow the shared tile scheduler (no tile
 // straddles two experts; tiles contiguous per XCD).
 #include "common.h"
+#include "gemm_rows.h"
 #include "tile_sched.h"
 
 namespace {
@@ -233,6 +235,26 @@ extern "C" qd_status moe_w4a16_grouped_gemm(const void *a, int64_t a_rows,
   if (!qdh::aligned16(a) || !qdh::aligned16(out) || !qdh::aligned16(w->codes))
     return QD_ERR_ALIGN;
   if (qdh::fault_injected()) return QD_ERR_HIP;
+  // the rows kernel wherever its stages and offsets reach (it is the faster one
+  // from 1 row per expert, 42 -> 33 us, to hundreds, 345 -> 239); its scale loads
+  // are 4 bytes wide
+  const qdr::RowsPlan pl = qdr::rows_plan(false, rows, a_rows, E, N, K, epilogue);
+  if (pl.ok && (reinterpret_cast<uintptr_t>(w->scales) & 3) == 0) {
+    qdr::RowsArgs r{};
+    r.a = static_cast<const uint8_t *>(a);
+    r.row_token = row_token;
+    r.offsets = expert_offsets;
+    r.E = E;
+    r.rows = rows;
+    r.w_codes = w->codes;
+    r.w_scales = w->scales;
+    r.w_dec = w->gscale;
+    r.N = (int)N;
+    r.K = (int)K;
+    r.out = static_cast<uint16_t *>(out);
+    qdr::launch_rows<false>(r, epilogue, pl, qdh::S(stream));
+    return qdh::check_launch();
+  }
   W16Args p{};
   p.a = static_cast<const uint16_t *>(a);
   p.row_token = row_token;
