@@ -9,10 +9,12 @@
 // exact in f32; the row scales are applied in the epilogue.
 //
 // GEMM: v_mfma_scale_f32_32x32x64_f8f6f4 with both block scales 1.0 (the
-// f8f6f4 path, twice the f16 MFMA rate), K = 64 per instruction.  The same
-// structure as the NVFP4 prefill kernel: M-tiles inside one expert, tile
-// indices contiguous per XCD, a ring of 64-element stages filled by direct
-// global->LDS loads (six per wave and stage), operands read a stage ahead.
+// f8f6f4 path, twice the f16 MFMA rate), K = 64 per instruction.  gemm_rows.h
+// holds the kernel of most sizes; the one here serves a K of an odd number of
+// 64-element stages and a few rows per expert along a long K: M-tiles inside one
+// expert, tile indices contiguous per XCD, a ring of 64-element stages filled
+// by direct global->LDS loads (six per wave and stage), operands read a stage
+// ahead.
 //  * TM = 256 (many rows per expert): tile 256 x 128 weight rows, 2 x 2 waves
 //    of 128 x 64 (4 x 2 fragments), two workgroups per CU.
 //  * TM = 32 (decode): tile 32 x 256 weight rows, 1 x 4 waves of 32 x 64 (two
@@ -24,6 +26,7 @@
 // K order inside every MFMA).
 #include "common.h"
 #include "lds_dma.h"
+#include "gemm_rows.h"
 #include "tile_sched.h"
 
 namespace {
@@ -300,7 +303,14 @@ __global__ __launch_bounds__(F8_THREADS, 2) void gemm_fp8_kernel(Fp8Args p, int 
   }
 }
 
-// rows per expert above which the 256-row tiles replace the 32-row passes
+// The rows kernel (gemm_rows.h) takes whole 128-byte stages.  The 32-row passes
+// stay ahead of it only for weights streamed once along a long K (64 experts of
+// 3072 x 4096, at most 16 rows each: 149 us against 164; at 37 rows each 255
+// against 160; 128 experts of 1536 x 2048, 16 rows each: 83 against 77).
+constexpr int64_t F8_PASS_ROWS = 16, F8_PASS_K = 4096;
+
+// Elsewhere (K of an odd number of 64-element stages): rows per expert above
+// which the 256-row tiles replace the 32-row passes
 constexpr int64_t F8_DECODE_ROWS = 48;
 
 struct F8Plan {
@@ -384,6 +394,23 @@ extern "C" qd_status moe_fp8_grouped_gemm(const uint8_t *a_codes, const float *a
   if (!pl.ok) return QD_ERR_UNSUPPORTED;
   if (qdh::fault_injected()) return QD_ERR_HIP;
   if (rows == 0) return QD_OK;
+  const qdr::RowsPlan rp = qdr::rows_plan(true, rows, a_rows, E, N, K, epilogue);
+  if (rp.ok && (rows > (int64_t)E * F8_PASS_ROWS || K < F8_PASS_K)) {
+    qdr::RowsArgs r{};
+    r.a = a_codes;
+    r.a_dec = a_dec;
+    r.row_token = row_token;
+    r.offsets = expert_offsets;
+    r.E = E;
+    r.rows = rows;
+    r.w_codes = w_codes;
+    r.w_dec = w_dec;
+    r.N = (int)N;
+    r.K = (int)K;
+    r.out = static_cast<uint16_t *>(out);
+    qdr::launch_rows<true>(r, epilogue, rp, qdh::S(stream));
+    return qdh::check_launch();
+  }
   Fp8Args p{};
   p.a_codes = a_codes;
   p.a_dec = a_dec;
