@@ -75,6 +75,92 @@ __global__ __launch_bounds__(256) void fp8_quantize_rows_kernel(const T *__restr
   }
 }
 
+// Rows of whole 16-byte-aligned groups of eight elements: a lane keeps its
+// groups of the row's first 4096 elements in registers between the two passes
+// (the rest is read again), and the hardware conversion makes the codes (it
+// rounds as e4m3_encode_pos does; the clamp has excluded what it would turn to
+// NaN).  Bound by HBM: 8192 x 4096 bf16 44 -> 17 us (5.9 TB/s) and 32768 x 768 34
+// -> 18 against one element per load in the kernel above, which stays for other
+// widths and alignments.
+template <typename T>
+struct Group8;
+template <>
+struct Group8<uint16_t> {
+  uint4 q;
+  __device__ __forceinline__ void load(const uint16_t *p) { q = *reinterpret_cast<const uint4 *>(p); }
+  __device__ __forceinline__ float at(int j) const {
+    const uint32_t w = j < 2 ? q.x : j < 4 ? q.y : j < 6 ? q.z : q.w;
+    return __uint_as_float(j & 1 ? w & 0xFFFF0000u : w << 16);
+  }
+};
+template <>
+struct Group8<float> {
+  float4 q[2];
+  __device__ __forceinline__ void load(const float *p) {
+    q[0] = reinterpret_cast<const float4 *>(p)[0];
+    q[1] = reinterpret_cast<const float4 *>(p)[1];
+  }
+  __device__ __forceinline__ float at(int j) const {
+    const float4 &f = q[j >> 2];
+    return (j & 3) == 0 ? f.x : (j & 3) == 1 ? f.y : (j & 3) == 2 ? f.z : f.w;
+  }
+};
+
+template <typename T>
+__global__ __launch_bounds__(256) void fp8_quantize_rows8_kernel(const T *__restrict__ x,
+                                                                 int64_t rows, int64_t K,
+                                                                 uint8_t *__restrict__ codes,
+                                                                 float *__restrict__ dec) {
+  constexpr int NG = 8;
+  const int lane = threadIdx.x & 63;
+  const int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (r >= rows) return;
+  const T *xr = x + r * K;
+  const int64_t n8 = K >> 3;
+  Group8<T> g[NG];
+  float m = 0.0f;
+#pragma unroll
+  for (int c = 0; c < NG; ++c)
+    if (64 * c + lane < n8) g[c].load(xr + (64 * c + lane) * 8);
+#pragma unroll
+  for (int c = 0; c < NG; ++c)
+    if (64 * c + lane < n8) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(g[c].at(j)));
+    }
+  for (int64_t i = 64 * NG + lane; i < n8; i += 64) {
+    Group8<T> t;
+    t.load(xr + i * 8);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(t.at(j)));
+  }
+  m = wave_max(m);
+  const bool zero = !(m > 0.0f);
+  const float enc = zero ? 1.0f : 448.0f / m;
+  if (lane == 0) dec[r] = 1.0f / enc;
+  uint2 *cr = reinterpret_cast<uint2 *>(codes + r * K);
+  auto put = [&](const Group8<T> &t, int64_t i) __attribute__((always_inline)) {
+    float v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      v[j] = copysignf(fminf(fabsf(t.at(j) * enc), 448.0f), t.at(j));
+    int lo = 0, hi = 0;
+    lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[0], v[1], lo, false);
+    lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], lo, true);
+    hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[4], v[5], hi, false);
+    hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[6], v[7], hi, true);
+    cr[i] = make_uint2((uint32_t)lo, (uint32_t)hi);
+  };
+#pragma unroll
+  for (int c = 0; c < NG; ++c)
+    if (64 * c + lane < n8) put(g[c], 64 * c + lane);
+  for (int64_t i = 64 * NG + lane; i < n8; i += 64) {
+    Group8<T> t;
+    t.load(xr + i * 8);
+    put(t, i);
+  }
+}
+
 // ---------------------------------------------------------------- GEMM
 struct Fp8Args {
   const uint8_t *a_codes;
@@ -369,12 +455,21 @@ extern "C" qd_status fp8_quantize_rows(const void *x, int32_t dtype, int64_t row
   const int64_t g = (rows + 3) / 4;
   if (g > 0x7fffffffLL) return QD_ERR_UNSUPPORTED;
   hipStream_t s = qdh::S(stream);
-  if (dtype == QD_DTYPE_BF16)
-    hipLaunchKernelGGL(fp8_quantize_rows_kernel<uint16_t>, dim3((unsigned)g), dim3(256), 0, s,
-                       static_cast<const uint16_t *>(x), rows, cols, codes, dec);
-  else
-    hipLaunchKernelGGL(fp8_quantize_rows_kernel<float>, dim3((unsigned)g), dim3(256), 0, s,
-                       static_cast<const float *>(x), rows, cols, codes, dec);
+  const bool wide = cols % 8 == 0 && qdh::aligned16(x) && ((uintptr_t)codes & 7u) == 0;
+  const dim3 grid((unsigned)g), block(256);
+  const uint16_t *xb = static_cast<const uint16_t *>(x);
+  const float *xf = static_cast<const float *>(x);
+  if (dtype == QD_DTYPE_BF16) {
+    if (wide)
+      hipLaunchKernelGGL(fp8_quantize_rows8_kernel<uint16_t>, grid, block, 0, s, xb, rows, cols, codes, dec);
+    else
+      hipLaunchKernelGGL(fp8_quantize_rows_kernel<uint16_t>, grid, block, 0, s, xb, rows, cols, codes, dec);
+  } else {
+    if (wide)
+      hipLaunchKernelGGL(fp8_quantize_rows8_kernel<float>, grid, block, 0, s, xf, rows, cols, codes, dec);
+    else
+      hipLaunchKernelGGL(fp8_quantize_rows_kernel<float>, grid, block, 0, s, xf, rows, cols, codes, dec);
+  }
   return qdh::check_launch();
 }
 

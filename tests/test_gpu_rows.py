@@ -136,6 +136,46 @@ def test_fp8_gemm(case, epi):
     check_close_bf16(np_bf16(out), ref, mag, name, floor=2.0 ** -13)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("K", [8, 504, 512, 520, 4096, 4104, 13, 1001])
+def test_fp8_rows_exact(K, dtype):
+    """Row codes bit for bit at the edges of the 8-element groups, 512-element
+    passes and the 4096 elements kept in registers (13 and 1001: the general
+    kernel), with non-finite elements."""
+    g = torch.Generator().manual_seed(K)
+    x = torch.randn((7, K), generator=g) * torch.exp(3.0 * torch.randn((7, K), generator=g))
+    x[1] = 0.0
+    x[2] *= -1e-30
+    x[3, K // 2] = float("inf")
+    x[4, K - 1] = float("nan")
+    x = x.to(dtype)
+    codes, dec = ops.fp8_quantize_rows(x.to(DEV))
+    fin = [0, 1, 2, 5, 6]
+    rc, rd = OF.quantize_rows(x.float().numpy()[fin])
+    assert np.array_equal(codes.cpu().numpy()[fin], rc)
+    assert np.array_equal(dec.cpu().numpy()[fin].view(np.uint32), rd.view(np.uint32))
+    c = codes.cpu().numpy()
+    # an infinite amax: scale 0, the element itself saturates, the rest is +-0
+    assert c[3, K // 2] & 0x7F == 0x7E and not np.any(np.delete(c[3], K // 2) & 0x7F)
+    # NaN is left out of the amax and saturates
+    assert c[4, K - 1] & 0x7F == 0x7E
+
+
+def test_fp8_rows_thresholds():
+    """Every value of E4M3, every midpoint between two and its f32 neighbours."""
+    grid = np.concatenate([np.arange(0, 9) * 2.0 ** -9,
+                           [(8 + m) * 2.0 ** (e - 3) for e in range(-6, 9) for m in range(8)]])
+    grid = np.unique(grid[grid <= 448.0]).astype(np.float32)
+    mid = ((grid[1:] + grid[:-1]) / 2).astype(np.float32)
+    v = np.concatenate([grid, mid, np.nextafter(mid, np.float32(0)),
+                        np.nextafter(mid, np.float32(1e9)), [448.0] * 8]).astype(np.float32)
+    v = np.concatenate([v, -v])
+    v = v[:len(v) // 8 * 8]
+    v[0] = 448.0                                   # amax 448: the row's scale is 1
+    codes, _ = ops.fp8_quantize_rows(torch.from_numpy(v[None]).to(DEV))
+    assert np.array_equal(codes.cpu().numpy(), OF.quantize_rows(v[None])[0])
+
+
 def test_most_experts():
     """E = 1024, the last entry of the tile schedule: rows on the first, a
     middle and the last expert only."""
