@@ -74,7 +74,7 @@ def parse():
 
 
 GEMM_SRCS = [os.path.join(ROOT, "paper_2607_15810_amd", "csrc", f)
-             for f in ("gemm.hip", "gemm_panel.h", "gemm_args.h")]
+             for f in ("gemm.hip", "gemm_panel.h", "panel_sched.h", "gemm_args.h")]
 PROFILES = os.path.join(ROOT, "profiles")
 
 
@@ -329,10 +329,9 @@ def measure(args, name, ceil, headline):
     step_tflops = alg["step_flops"] / (ms_step * 1e-3) / 1e12
     w13_ms = stage_ms[Q.STAGE_NAMES.index("w13")]
     decode = name in DECODE
-    # the W13 launch runs the decode kernel when the rows per expert are few
-    skinny = Q.lib().moe_w4a4_grouped_gemm_amax_count(
-        wl.T * wl.k, 2 * wl.I, wl.H, wl.E, wl.Ks, Q.QD_EPI_SWIGLU) <= 1024
-    kname = ("gemm_skinny_kernel" if skinny else "gemm_tile_kernel") + \
+    # the W13 launch runs the decode kernel on the decode workloads (few rows per
+    # expert), the panel kernel on the others
+    kname = ("gemm_skinny_kernel" if decode else "gemm_panel_kernel") + \
         " (W13 + fused RAC residual + SwiGLU)"
     traffic = measured_traffic(name)
     if decode:

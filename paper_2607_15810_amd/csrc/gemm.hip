@@ -1362,8 +1362,9 @@ void launch_tile(const GemmArgs &p, const TlPlan &pl, hipStream_t s) {
 }
 
 // The kernel of a grouped GEMM: the few-row kernel for a handful of rows, the
-// decode kernel for few rows per expert, the panel kernel above, the tile kernel for per-expert sets whose table the
-// panel kernel cannot hold, and the generic kernel for sizes none takes.
+// decode kernel for few rows per expert, the panel kernel above, the tile kernel
+// for per-expert sets whose table the panel kernel cannot hold, and the generic
+// kernel for sizes none takes.
 enum class Kern { few, skinny, panel, tile, generic };
 
 struct Choice {

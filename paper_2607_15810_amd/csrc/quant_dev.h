@@ -104,6 +104,15 @@ __device__ __forceinline__ void quantize_act_rows(
     uint8_t *__restrict__ scales, float *__restrict__ gscale, uint64_t *__restrict__ scores,
     float *__restrict__ ramax, uint64_t (*part)[kQuantPartCols], float *red) {
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  const int64_t nbc = cols >> 4;
+  const int64_t cb = (int64_t)bx * 16 + tx;
+  const bool active = cb < nbc;
+  const int64_t step = (int64_t)gy * 16;
+  int64_t r = (int64_t)by * 16 + ty;
+  // the thread's first row is on its way while the partials are looked at, and
+  // its next one while this one is quantised
+  typename Loader<T>::Raw cur = {}, nxt = {};
+  if (active && r < rows) Loader<T>::load_raw(x, r * cols + cb * 16, cur);
   // tensor amax from the partial maxima
   const float amax = block_max(partials_max(amax_part, n_part), red);
   float s_enc, s_dec;
@@ -113,10 +122,6 @@ __device__ __forceinline__ void quantize_act_rows(
     gscale[0] = s_enc;
     gscale[1] = s_dec;
   }
-  const int64_t nbc = cols >> 4;
-  const int64_t cb = (int64_t)bx * 16 + tx;
-  const bool active = cb < nbc;
-
   int F = 0;
   if (RAC) {
     int e;
@@ -131,15 +136,8 @@ __device__ __forceinline__ void quantize_act_rows(
   float rmax = 0.0f;
 
   if (active) {
-    const int64_t step = (int64_t)gy * 16;
-    int64_t r = (int64_t)by * 16 + ty;
-    // with RAC (the longer row body) the thread's next row is loaded while
-    // this one is quantised
-    typename Loader<T>::Raw cur = {}, nxt = {};
-    if (RAC && r < rows) Loader<T>::load_raw(x, r * cols + cb * 16, cur);
     for (; r < rows; r += step) {
-      if (!RAC) Loader<T>::load_raw(x, r * cols + cb * 16, cur);
-      else if (r + step < rows) Loader<T>::load_raw(x, (r + step) * cols + cb * 16, nxt);
+      if (r + step < rows) Loader<T>::load_raw(x, (r + step) * cols + cb * 16, nxt);
       float v[16];
       Loader<T>::unpack(cur, v);
       uint32_t lo, hi;
@@ -160,7 +158,7 @@ __device__ __forceinline__ void quantize_act_rows(
           accd[i] += fixed_point_term_f64(rr * rr, F);   // each term < 2^37
         }
       }
-      if (RAC) cur = nxt;
+      cur = nxt;
     }
   }
   if (RAC) {
@@ -204,12 +202,15 @@ inline int amax_grid(int64_t n16) {
 }
 
 // (gx, gy) grid of the quantiser: 16 column blocks per workgroup along x;
-// with RAC at most 1024 workgroups (one u64 atomic per channel and workgroup)
+// with RAC at most 256 workgroups: each ends in one u64 atomic per channel, and
+// at 2000 x 2048 those cost more than the waves they buy (the layer's step 301
+// us at 1024, 299 at 512, 297 at 256; 1000 rows 232, 232, 229; 8192 rows and
+// 4096 columns within 0.4% of each other)
 inline void quant_grid(int64_t rows, int64_t cols, bool rac, int &gx, int &gy) {
   const int64_t nbc = cols / 16;
   gx = (int)((nbc + 15) / 16);
   int64_t g = (rows + 15) / 16;
-  const int64_t cap = rac ? 1024 : 4096;
+  const int64_t cap = rac ? 256 : 4096;
   int64_t lim = cap / gx;
   if (lim < 1) lim = 1;
   if (g > lim) g = lim;
