@@ -13,8 +13,8 @@
 //    into ceil(f / 2 MF) tiles of equal height (to one fragment): a remainder
 //    of a few rows costs the fragments it has, not a second pass over the
 //    weights with nearly empty tiles.
-//  * Persistent: one workgroup per CU walks a static list of tiles, experts of
-//    tall tiles first, so that the last, partial round of the chip holds the
+//  * Persistent: one workgroup per CU (two with short rings of 64-row tiles)
+//    walks a static list of tiles, experts of tall tiles first, so that the last, partial round of the chip holds the
 //    smallest ones.  An M-tile's weight-row tiles (and the M-tiles of an expert
 //    that has several) go to one XCD, where they share activation rows (and
 //    weights) in its L2.  The stages of all its tiles form one stream through an LDS ring of NS
@@ -132,7 +132,7 @@ __device__ __forceinline__ int pn_wrow(int f, int nt, int N) {
 }
 
 template <int MF, int EPI>
-__global__ __launch_bounds__(PN_THREADS, 2) void gemm_panel_kernel(GemmArgs p, int ntn, int cg,
+__global__ __launch_bounds__(PN_THREADS, MF == 1 ? 4 : 2) void gemm_panel_kernel(GemmArgs p, int ntn, int cg,
                                                                    int ns, int dense) {
   using C = PnCfg<MF>;
   extern __shared__ __align__(16) unsigned char lds[];

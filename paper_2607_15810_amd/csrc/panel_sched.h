@@ -20,6 +20,7 @@ constexpr int PN_EMAX = 1024;
 constexpr int PN_NSMAX = 6;
 constexpr int PN_TILE = 2;               // a tile's fixed time, in that of a 32-row fragment
 constexpr int PN_LDS_MAX = 160 * 1024 - 512;   // dynamic LDS beside the static arrays
+constexpr int PN_LDS_2WG = 80 * 1024 - 512;    // the same for two workgroups per CU
 
 template <int LPS>
 __device__ __forceinline__ void pn_wait(int stages) {

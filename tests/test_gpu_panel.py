@@ -45,6 +45,11 @@ CASES = [
     ("dense_residual", [150, 60, 100], 384, 256, 200, True),
     ("dense_residual_320", [300, 321], 512, 128, 160, False),
     ("largest_table", [90, 70], 256, 256, 144, True),
+    # 64-row tiles on two workgroups per CU, 600 of them for 512: without
+    # and with the dense residual, and beside a table at K of two stages
+    ("two_per_cu", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 384, 768, 0, False),
+    ("two_per_cu_dense", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 384, 768, 200, True),
+    ("two_per_cu_table", [63, 64, 49, 33, 64, 50, 64, 17] * 25, 256, 768, 24, True),
 ]
 
 
