@@ -14,10 +14,13 @@
 //    row-dependent XOR, so the fragment reads are free of bank conflicts.  One
 //    barrier per stage, where the last fragments it needs are in registers, so
 //    that the next stage's first reads run under the last MFMAs.
-//  * W4A16: lane (row r, half h) owns elements 32 h .. 32 h + 31 of a stage, and
-//    MFMA k-step s takes elements 8 s .. 8 s + 7 of each half, for A and B alike.
-//    Each wave decodes its weight fragments in registers: E2M1 x E4M3 has at
-//    most six significant bits, so the f32 product is exact in bf16.
+//  * W4A16: MFMA k-step s takes the stage's elements 16 s .. 16 s + 15, half h
+//    the 8 from 8 h on: the order of the general kernel (w4a16.hip), so that a
+//    row's bits do not depend on which of the two runs.  A lane reads 16 bytes
+//    of weight codes, elements 32 h .. 32 h + 31 of its row, and the two halves
+//    swap words (two v_permlane32_swap per fragment and stage).  Each wave
+//    decodes its weight fragments in registers: E2M1 x E4M3 has at most six
+//    significant bits, so the f32 product is exact in bf16.
 //    FP8: k-step s takes the stage's bytes 64 s .. 64 s + 63, half h 32 of them.
 //
 // What bounds it: for hundreds of rows per expert the wave's own chain of
@@ -288,7 +291,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_rows_kernel(RowsArgs p, in
             o.c[k] = *reinterpret_cast<const uint4 *>(sl + la + i * 4096 +
                                                       (((4 * st + 2 * h + k) ^ sw) << 4));
         } else {
-          o.c[0] = *reinterpret_cast<const uint4 *>(sl + la + i * 4096 + (((4 * h + st) ^ sw) << 4));
+          o.c[0] = *reinterpret_cast<const uint4 *>(sl + la + i * 4096 + (((2 * st + h) ^ sw) << 4));
         }
         return o;
       };
@@ -310,7 +313,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_rows_kernel(RowsArgs p, in
                   sl + C::BOFF + (32 * f + r) * 128 + (((4 * st + 2 * h + k) ^ sw) << 4));
           } else {
             o.c[j] = *reinterpret_cast<const uint4 *>(sl + C::BOFF + f * 1024 + r * 32 + 16 * h);
-            o.s[j] = *reinterpret_cast<const uint16_t *>(sl + C::SOFF + f * 256 + r * 4 + 2 * h);
+            o.s[j] = *reinterpret_cast<const uint32_t *>(sl + C::SOFF + f * 256 + r * 4);
           }
         }
         return o;
@@ -335,6 +338,16 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_rows_kernel(RowsArgs p, in
           issue(sync());
         } else {
           const unsigned char *sl = lds + slot * C::SLOT, *sn = sl;
+          if constexpr (!FP8) {
+            // words 4 h + i of the row's 8 to words 2 st + h (step st)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              const uint4 c = b.c[j];
+              const auto e = __builtin_amdgcn_permlane32_swap(c.x, c.y, false, false);
+              const auto o = __builtin_amdgcn_permlane32_swap(c.z, c.w, false, false);
+              b.c[j] = make_uint4(e[0], o[0], e[1], o[1]);
+            }
+          }
 #pragma unroll
           for (int st = 0; st < STEPS; ++st) {
             if (FP8 && st + 1 < STEPS) bn = rd_b(sl, st + 1);
@@ -342,9 +355,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_rows_kernel(RowsArgs p, in
             if constexpr (!FP8) {
 #pragma unroll
               for (int j = 0; j < 2; ++j) {
-                const f16x2 pr = __builtin_bit_cast(
-                    f16x2, scale_pair_f16(b.s[j] & 0xFFu, b.s[j] >> 8));
-                const float sc = (float)pr[st >> 1];
+                const float sc = (float)scale_pair_of(b.s[j], st >> 1)[st & 1];
                 const uint32_t wd = word_of(b.c[j], st);
                 const f32x2_pair p0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(wd, 256.0f, 0);
                 const f32x2_pair p1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(wd, 256.0f, 1);

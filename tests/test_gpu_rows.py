@@ -82,6 +82,27 @@ def test_w4a16_gemm(case, epi):
     check_close_bf16(np_bf16(out), ref, mag, name)
 
 
+@pytest.mark.parametrize("epi", EPIS, ids=["plain", "swiglu"])
+@pytest.mark.parametrize("case", [c for c in W4A16 if c[0] != "one_stage"] +
+                         [("long_k", [3, 40, 0, 97], 2112, 96, True)],
+                         ids=lambda c: c[0])
+def test_w4a16_order_of_sums(case, epi):
+    """The bits of a result do not depend on which of the two kernels ran: the
+    general one takes over where the activations pass 4 GiB, declared here for
+    a matrix whose later rows no token names."""
+    name, counts, K, N, _ = case
+    x, wb, tok, offsets, tg, og = _inputs(name, counts, K, N, True)
+    w, R, E = ops.quantize_weight(wb.to(DEV)), sum(counts), len(counts)
+    xg = x.to(DEV)
+    outs = []
+    for a_rows in (len(x), 2 ** 32 // (2 * K) + 1):
+        out = torch.empty((R, N // 2 if epi else N), dtype=torch.bfloat16, device=DEV)
+        Q.call("moe_w4a16_grouped_gemm", xg.data_ptr(), a_rows, tg.data_ptr(), og.data_ptr(), E, R,
+               ops._nv(w), epi, out.data_ptr(), ops._stream())
+        outs.append(out)
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
 def test_w4a16_swiglu_range():
     """The SwiGLU epilogue over gates from deep underflow to overflow, zero and
     the non-finite ones (its first 32 rows hold moderate gates only): one weight of 6
