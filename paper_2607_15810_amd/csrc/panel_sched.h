@@ -53,6 +53,14 @@ struct PnTile {
   int e, row0, nrows, nt;
 };
 
+// An expert's nf 32-row fragments in n tiles of equal height to one fragment,
+// q = nf / n: the first fragment of tile i (nf for i = n).  No product of two
+// large counts: one expert may hold 2^19 fragments and more.
+__host__ __device__ inline int pn_cut(int nf, int n, int q, int i) {
+  const int r = nf - q * n;
+  return i * q + (i < r ? i : r);
+}
+
 // The M-tiles run over the experts in the order of perm (mpre: M-tiles before
 // each place of it) and are dealt to the XCDs in groups of cg; XCD x = b % 8
 // walks its groups x, x + 8, .., the weight-row tiles of an M-tile innermost,
@@ -85,8 +93,8 @@ __device__ __forceinline__ PnTile pn_locate(const PnSched &S, int l, int &cur, i
   const int rows = (int)uni((uint32_t)S.offs[tl.e + 1]) - o0;
   const int i = mt - (int)uni((uint32_t)S.mpre[cur]);
   const int nf = (rows + 31) >> 5, n = (nf + 2 * MF - 1) / (2 * MF);
-  const int f0 = (int)uni((uint32_t)(i * nf) / (uint32_t)n);
-  const int f1 = (int)uni((uint32_t)((i + 1) * nf) / (uint32_t)n);
+  const int h = (int)uni((uint32_t)nf / (uint32_t)n);
+  const int f0 = pn_cut(nf, n, h, i), f1 = pn_cut(nf, n, h, i + 1);
   tl.row0 = o0 + 32 * f0;
   tl.nrows = min(32 * f1, rows) - 32 * f0;
   tl.nt = rem - j * S.ntn;

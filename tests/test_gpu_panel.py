@@ -136,3 +136,27 @@ def test_panel_gemm_per_expert_sets(Ks):
     out, _ = ops.grouped_gemm_per_expert(xq, w, R, tg, og, rq, sel, rows)
     ref, mag = OL.w13_stage_per_expert(act["xq"], act["rq"], act["sel_pe"], tok, offsets, W)
     check_close_bf16(np_bf16(out), ref, mag, f"per-expert sets, K_s = {Ks}")
+
+
+def test_panel_gemm_many_rows_of_one_expert():
+    """Eight million rows on one expert (26,215 tiles): row i of the result is
+    that of its token, on the W4A4, W4A16 and FP8 kernels alike."""
+    R, T, K, N = 1 << 23, 997, 256, 128
+    g = torch.Generator().manual_seed(11)
+    x = torch.randn((T, K), generator=g).to(torch.bfloat16).to(DEV)
+    wb = (torch.randn((1, N, K), generator=g) * 0.02).to(torch.bfloat16).to(DEV)
+    tok = (torch.arange(R, device=DEV, dtype=torch.int64) % T).to(torch.int32)
+    w = ops.quantize_weight(wb)
+    xq, _, _ = ops.quantize_act(x)
+    xc, xd = ops.fp8_quantize_rows(x)
+    wc, wd = ops.fp8_quantize_rows(wb)
+    w32 = ops.quantize_weight(wb[:, :32, :128].contiguous())
+    x128 = x[:, :128].contiguous()
+    for name, call in (("W4A4", lambda n, t: ops.grouped_gemm(xq, w, n, t)[0]),
+                       ("W4A16", lambda n, t: ops.w4a16_grouped_gemm(x128, w32, n, t)),
+                       ("FP8", lambda n, t: ops.fp8_grouped_gemm(xc, xd, wc, wd, n, t))):
+        few = call(T, torch.arange(T, dtype=torch.int32, device=DEV))
+        out = call(R, tok)
+        for r0 in range(0, R, 1 << 20):
+            t = tok[r0:r0 + (1 << 20)].long()
+            assert torch.equal(out[r0:r0 + (1 << 20)], few[t]), f"{name}: rows {r0} on"
