@@ -1306,7 +1306,8 @@ inline bool compact_form(int Ks) {
 struct PnPlan {
   bool ok;
   bool dense;
-  int mf, ns, ntn, cg, grid, lds;
+  int mf, ns, grid, lds;
+  qdp::PnDeal deal;
 };
 
 inline PnPlan panel_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, bool per_expert) {
@@ -1323,9 +1324,9 @@ inline PnPlan panel_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, bool
   if ((rows + 1) * K / 2 >= (1LL << 32) || (rows + 1) * ksa * 2 >= (1LL << 32) ||
       (rows + 320) * N * 2 >= (1LL << 32))
     return pl;
-  pl.ntn = (int)((N + qdp::PN_N - 1) / qdp::PN_N);
+  const int ntn = (int)((N + qdp::PN_N - 1) / qdp::PN_N);
   const int nst = (int)(K / qdp::PN_K);
-  const qdp::PnHeight h = qdp::pn_height(rows, E, pl.ntn, [&](int mf) {
+  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, [&](int mf) {
     int ns = std::min(qdp::PN_NSMAX, nst);
     while (ns >= 2 && qdp::pn_layout(mf, ns, ksa, E).total > qdp::PN_LDS_MAX) --ns;
     return ns;
@@ -1333,30 +1334,30 @@ inline PnPlan panel_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, bool
   if (h.mf == 0) return pl;
   pl.mf = h.mf;
   pl.ns = h.ns;
-  pl.cg = h.cg;
   // Persistent: one workgroup per CU (256), a multiple of 8 (the XCDs); two per
   // CU for 64-row tiles where three stages each (two at K = 256) leave room for
   // both, so that one's start, first loads and epilogue run under the other's
   // stages: K = 384, 6 rows on each of 128 experts, N = 2048, the layer around
   // it 94.8 -> 90.1 us; 19 skewed rows on each of 64, N = 4096, 120.8 -> 113.8.
   // A table of the residual beside the ring leaves no room for the second.
-  const int64_t tiles = qdt::tile_grid(rows, E, 64 * pl.mf, pl.ntn);
+  const int64_t tiles = qdt::tile_grid(rows, E, 64 * pl.mf, ntn);
   const int ns2 = std::min(3, h.ns);
   const bool two =
       pl.mf == 1 && tiles > 256 && qdp::pn_layout(1, ns2, ksa, E).total <= qdp::PN_LDS_2WG;
   if (two) pl.ns = ns2;
   pl.lds = qdp::pn_layout(pl.mf, pl.ns, ksa, E).total;
   pl.grid = (int)std::min<int64_t>(two ? 512 : 256, tiles);
+  pl.deal = qdp::pn_deal(h, ntn, pl.grid);
   pl.ok = true;
   return pl;
 }
 
 void launch_pn(const GemmArgs &p, int epi, const PnPlan &pl, hipStream_t s) {
   switch (pl.mf) {
-    case 5: qdp::launch_panel<5>(p, epi, pl.ntn, pl.cg, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
-    case 3: qdp::launch_panel<3>(p, epi, pl.ntn, pl.cg, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
-    case 2: qdp::launch_panel<2>(p, epi, pl.ntn, pl.cg, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
-    default: qdp::launch_panel<1>(p, epi, pl.ntn, pl.cg, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
+    case 5: qdp::launch_panel<5>(p, epi, pl.deal, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
+    case 3: qdp::launch_panel<3>(p, epi, pl.deal, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
+    case 2: qdp::launch_panel<2>(p, epi, pl.deal, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
+    default: qdp::launch_panel<1>(p, epi, pl.deal, pl.grid, pl.ns, pl.dense, pl.lds, s); break;
   }
 }
 

@@ -132,8 +132,8 @@ __device__ __forceinline__ int pn_wrow(int f, int nt, int N) {
 }
 
 template <int MF, int EPI>
-__global__ __launch_bounds__(PN_THREADS, MF == 1 ? 4 : 2) void gemm_panel_kernel(GemmArgs p, int ntn, int cg,
-                                                                   int ns, int dense) {
+__global__ __launch_bounds__(PN_THREADS, MF == 1 ? 4 : 2) void gemm_panel_kernel(
+    GemmArgs p, PnDeal deal, int ns, int dense) {
   using C = PnCfg<MF>;
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int sh_w[8];
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(PN_THREADS, MF == 1 ? 4 : 2) void gemm_panel_kernel
   const int nmain = res_on && dense ? 2 * nst : nst;
   const int nres = res_on && cmp ? (ksa + 31) >> 5 : 0;
   __syncthreads();
-  const PnSched S{offs, mpre, perm, E, ntn, cg, (int)(blockIdx.x & 7)};
+  const PnSched S{offs, mpre, perm, E, deal, (int)(blockIdx.x & 7)};
   const int nsl = gridDim.x >> 3;
   const int t_end = pn_walk(S);            // tiles of this XCD's walk
   int ct = blockIdx.x >> 3;                // the tile being multiplied
@@ -657,20 +657,20 @@ __global__ __launch_bounds__(PN_THREADS, MF == 1 ? 4 : 2) void gemm_panel_kernel
 }
 
 template <int MF, int EPI>
-void launch_panel_epi(const GemmArgs &p, int ntn, int cg, int grid, int ns, int dense, int lds,
+void launch_panel_epi(const GemmArgs &p, const PnDeal &deal, int grid, int ns, int dense, int lds,
                       hipStream_t s) {
   auto kern = gemm_panel_kernel<MF, EPI>;
   static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                                PN_LDS_MAX) == hipSuccess;
   (void)attr;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(PN_THREADS), (size_t)lds, s, p, ntn, cg, ns,
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(PN_THREADS), (size_t)lds, s, p, deal, ns,
                      dense);
 }
 
 // one compiled tile height each (gemm_panel_<MF>.hip)
 template <int MF>
-void launch_panel(const GemmArgs &p, int epi, int ntn, int cg, int grid, int ns, int dense, int lds,
-                  hipStream_t s);
+void launch_panel(const GemmArgs &p, int epi, const PnDeal &deal, int grid, int ns, int dense,
+                  int lds, hipStream_t s);
 
 }  // namespace qdp

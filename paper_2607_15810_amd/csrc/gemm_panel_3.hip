@@ -2,8 +2,8 @@
 #include "gemm_panel.h"
 
 template <>
-void qdp::launch_panel<3>(const GemmArgs &p, int epi, int ntn, int cg, int grid, int ns,
-                          int dense, int lds, hipStream_t s) {
-  if (epi == QD_EPI_SWIGLU) launch_panel_epi<3, QD_EPI_SWIGLU>(p, ntn, cg, grid, ns, dense, lds, s);
-  else launch_panel_epi<3, QD_EPI_NONE>(p, ntn, cg, grid, ns, dense, lds, s);
+void qdp::launch_panel<3>(const GemmArgs &p, int epi, const PnDeal &deal, int grid,
+                          int ns, int dense, int lds, hipStream_t s) {
+  if (epi == QD_EPI_SWIGLU) launch_panel_epi<3, QD_EPI_SWIGLU>(p, deal, grid, ns, dense, lds, s);
+  else launch_panel_epi<3, QD_EPI_NONE>(p, deal, grid, ns, dense, lds, s);
 }

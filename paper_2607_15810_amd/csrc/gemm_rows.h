@@ -124,7 +124,7 @@ __device__ __forceinline__ float rw_swiglu_fp8(float g, float u) {
 }
 
 template <bool FP8, int MF, int EPI>
-__global__ __launch_bounds__(PN_THREADS, 2) void gemm_rows_kernel(RowsArgs p, int ntn, int cg,
+__global__ __launch_bounds__(PN_THREADS, 2) void gemm_rows_kernel(RowsArgs p, PnDeal deal,
                                                                   int ns) {
   using C = RwCfg<FP8, MF>;
   extern __shared__ __align__(16) unsigned char lds[];
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_rows_kernel(RowsArgs p, in
   const int32_t *tokb = reinterpret_cast<const int32_t *>(lds + L.tok);
   pn_schedule<MF>(p.offsets, p.rows, E, offs, mpre, perm, sh_w, sh_c);
   __syncthreads();
-  const PnSched S{offs, mpre, perm, E, ntn, cg, (int)(blockIdx.x & 7)};
+  const PnSched S{offs, mpre, perm, E, deal, (int)(blockIdx.x & 7)};
   const int nsl = gridDim.x >> 3;
   const int t_end = pn_walk(S);
   int ct = blockIdx.x >> 3;                // the tile being multiplied
@@ -476,7 +476,8 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_rows_kernel(RowsArgs p, in
 
 struct RowsPlan {
   bool ok;
-  int mf, ns, ntn, cg, grid, lds;
+  int mf, ns, grid, lds;
+  PnDeal deal;
 };
 
 // for whole stages, two of them or more, and operands that 32-bit byte offsets
@@ -489,8 +490,8 @@ inline RowsPlan rows_plan(bool fp8, int64_t rows, int64_t a_rows, int E, int64_t
   if (kab < 256 || kab % 128 != 0 || N % 32 != 0 || E > PN_EMAX) return pl;
   if ((std::max(a_rows, rows) + 1) * kab >= lim || N * kwb >= lim || rows * 4 >= lim) return pl;
   const int nst = (int)(kab / 128);
-  pl.ntn = epilogue == QD_EPI_SWIGLU ? (int)((N / 2 + 127) / 128) : (int)((N + PN_N - 1) / PN_N);
-  const PnHeight h = pn_height(rows, E, pl.ntn, [&](int mf) {
+  const int ntn = epilogue == QD_EPI_SWIGLU ? (int)((N / 2 + 127) / 128) : (int)((N + PN_N - 1) / PN_N);
+  const PnHeight h = pn_height(rows, E, ntn, [&](int mf) {
     int ns = std::min(5, nst);
     while (ns >= 2 && rw_layout(fp8, mf, ns, E).total > PN_LDS_MAX) --ns;
     return ns;
@@ -498,9 +499,9 @@ inline RowsPlan rows_plan(bool fp8, int64_t rows, int64_t a_rows, int E, int64_t
   if (h.mf == 0) return pl;
   pl.mf = h.mf;
   pl.ns = h.ns;
-  pl.cg = h.cg;
   pl.lds = rw_layout(fp8, h.mf, h.ns, E).total;
-  pl.grid = (int)std::min<int64_t>(256, qdt::tile_grid(rows, E, 64 * pl.mf, pl.ntn));
+  pl.grid = (int)std::min<int64_t>(256, qdt::tile_grid(rows, E, 64 * pl.mf, ntn));
+  pl.deal = pn_deal(h, ntn, pl.grid);
   pl.ok = true;
   return pl;
 }
@@ -512,8 +513,8 @@ void launch_rows_one(const RowsArgs &p, const RowsPlan &pl, hipStream_t s) {
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                                PN_LDS_MAX) == hipSuccess;
   (void)attr;
-  hipLaunchKernelGGL(kern, dim3((unsigned)pl.grid), dim3(PN_THREADS), (size_t)pl.lds, s, p, pl.ntn,
-                     pl.cg, pl.ns);
+  hipLaunchKernelGGL(kern, dim3((unsigned)pl.grid), dim3(PN_THREADS), (size_t)pl.lds, s, p, pl.deal,
+                     pl.ns);
 }
 template <bool FP8, int EPI>
 void launch_rows_epi(const RowsArgs &p, const RowsPlan &pl, hipStream_t s) {

@@ -61,25 +61,56 @@ __host__ __device__ inline int pn_cut(int nf, int n, int q, int i) {
   return i * q + (i < r ? i : r);
 }
 
-// The M-tiles run over the experts in the order of perm (mpre: M-tiles before
-// each place of it) and are dealt to the XCDs in groups of cg; XCD x = b % 8
-// walks its groups x, x + 8, .., the weight-row tiles of an M-tile innermost,
-// and its workgroups (b / 8) take every (G / 8)-th tile of that walk.  Place l
-// of the walk: visited in increasing order, so the cursor into perm advances
-// by a wave ballot over the next 64 places.
+// How the tiles are dealt to the XCDs: units of cg M-tiles x nb weight-row
+// tiles; an M-tile's ntn weight-row tiles make nsp = ntn / nb units (nsp > 1
+// only with cg = 1).  XCD x walks its units x, x + 8, .., the weight-row tiles
+// of an M-tile innermost.
+struct PnDeal {
+  int cg, nb, nsp;
+};
+struct PnPlace {
+  int mt, nt;
+};
 // (Integer divisions run on the vector unit: their results are made scalar.)
+__host__ __device__ inline int pn_div(int a, int b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return (int)uni((uint32_t)a / (uint32_t)b);
+#else
+  return a / b;
+#endif
+}
+// the tile at place l of XCD xcd's walk
+__host__ __device__ inline PnPlace pn_place(const PnDeal &d, int xcd, int l) {
+  const int gt = d.cg * d.nb;
+  const int q = pn_div(l, gt), rem = l - q * gt;
+  const int j = pn_div(rem, d.nb), u = xcd + 8 * q;
+  const int g = d.nsp == 1 ? u : pn_div(u, d.nsp);
+  return {g * d.cg + j, (u - g * d.nsp) * d.nb + rem - j * d.nb};
+}
+// the length of that walk over mts M-tiles
+__host__ __device__ inline int pn_length(const PnDeal &d, int xcd, int mts) {
+  const int ng = pn_div(mts + d.cg - 1, d.cg), nu = ng * d.nsp;
+  const int nq = nu > xcd ? (nu - xcd + 7) >> 3 : 0;
+  const bool last = nu > 0 && ((nu - 1) & 7) == xcd;       // the group that may be short
+  return (nq * d.cg - (last ? ng * d.cg - mts : 0)) * d.nb;
+}
+
+// The M-tiles run over the experts in the order of perm (mpre: M-tiles before
+// each place of it); workgroup b takes every (G / 8)-th tile, from b / 8 on, of
+// the walk of XCD b % 8.  Places of the walk are visited in increasing order, so
+// the cursor into perm advances by a wave ballot over the next 64 places.
 struct PnSched {
   const int32_t *offs, *mpre;
   const uint16_t *perm;
-  int E, ntn, cg, xcd;
+  int E;
+  PnDeal d;
+  int xcd;
 };
 
 template <int MF>
 __device__ __forceinline__ PnTile pn_locate(const PnSched &S, int l, int &cur, int lane) {
-  const int gt = S.cg * S.ntn;
-  const int q = (int)uni((uint32_t)l / (uint32_t)gt), rem = l - q * gt;
-  const int j = (int)uni((uint32_t)rem / (uint32_t)S.ntn);
-  const int mt = (S.xcd + 8 * q) * S.cg + j;
+  const PnPlace pl = pn_place(S.d, S.xcd, l);
+  const int mt = pl.mt;
   for (;;) {
     const int c = cur + 1 + lane;
     const bool le = c <= S.E && S.mpre[c] <= mt;
@@ -97,17 +128,13 @@ __device__ __forceinline__ PnTile pn_locate(const PnSched &S, int l, int &cur, i
   const int f0 = pn_cut(nf, n, h, i), f1 = pn_cut(nf, n, h, i + 1);
   tl.row0 = o0 + 32 * f0;
   tl.nrows = min(32 * f1, rows) - 32 * f0;
-  tl.nt = rem - j * S.ntn;
+  tl.nt = pl.nt;
   return tl;
 }
 
 // tiles of the walk of S's XCD
 __device__ __forceinline__ int pn_walk(const PnSched &S) {
-  const int mts = (int)uni((uint32_t)S.mpre[S.E]);
-  const int ng = (int)uni((uint32_t)(mts + S.cg - 1) / (uint32_t)S.cg);
-  const int nq = ng > S.xcd ? (ng - S.xcd + 7) >> 3 : 0;
-  const bool last = ng > 0 && ((ng - 1) & 7) == S.xcd;     // the group that may be short
-  return (nq * S.cg - (last ? ng * S.cg - mts : 0)) * S.ntn;
+  return pn_length(S.d, S.xcd, (int)uni((uint32_t)S.mpre[S.E]));
 }
 
 // The schedule (two experts per thread, E <= 1024): row offsets, the experts
@@ -190,6 +217,7 @@ __device__ __forceinline__ void pn_schedule(const int32_t *offsets, int64_t rows
 // ring depth that height leaves room for (< 2: none).
 struct PnHeight {
   int mf, ns, cg;
+  double mts;              // M-tiles expected
 };
 template <typename F>
 inline PnHeight pn_height(int64_t rows, int E, int ntn, F ns_of) {
@@ -208,10 +236,29 @@ inline PnHeight pn_height(int64_t rows, int E, int ntn, F ns_of) {
     if (h.mf == 0 || t < 0.999 * best) {     // even: the lower, its ring is deeper
       best = t;
       // M-tiles dealt to the XCDs in the number an average expert has
-      h = {mf, ns, std::max(1, std::min(8, (int)(n + 0.5)))};
+      h = {mf, ns, std::max(1, std::min(8, (int)(n + 0.5))), n * E};
     }
   }
   return h;
+}
+
+// The deal of h's M-tiles over a grid of workgroups.  Whole M-tiles, as many
+// together as an average expert has, share most in an XCD's L2, and from 64 such
+// units on they load the XCDs evenly.  With fewer the largest units are taken
+// that need no more rounds of an XCD's workgroups than single tiles would: one
+// M-tile, or one expert's eight, would otherwise keep seven XCDs idle.
+inline PnDeal pn_deal(const PnHeight &h, int ntn, int grid) {
+  if (h.mts >= 64.0 * h.cg) return {h.cg, ntn, 1};
+  const int m = std::max(1, (int)std::ceil(h.mts - 0.2)), wgs = grid / 8;
+  const auto rounds = [&](int cg, int nb) {
+    const int units = (m + cg - 1) / cg * (ntn / nb);
+    return ((units + 7) / 8 * cg * nb + wgs - 1) / wgs;
+  };
+  const int least = rounds(1, 1);
+  if (rounds(h.cg, ntn) <= least) return {h.cg, ntn, 1};
+  int nb = ntn;
+  while (nb > 1 && (ntn % nb != 0 || rounds(1, nb) > least)) --nb;
+  return {1, nb, ntn / nb};
 }
 
 }  // namespace qdp

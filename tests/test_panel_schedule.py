@@ -18,6 +18,21 @@ SOURCE = """
 extern "C" void cuts(int nf, int n, int *out) {
   for (int i = 0; i <= n; ++i) out[i] = qdp::pn_cut(nf, n, nf / n, i);
 }
+extern "C" void walk(int cg, int nb, int nsp, int mts, int *len, int *seen) {
+  const qdp::PnDeal d{cg, nb, nsp};
+  for (int x = 0; x < 8; ++x) {
+    len[x] = qdp::pn_length(d, x, mts);
+    for (int l = 0; l < len[x]; ++l) {
+      const qdp::PnPlace p = qdp::pn_place(d, x, l);
+      if (p.mt < 0 || p.mt >= mts || p.nt < 0 || p.nt >= nb * nsp) { seen[0] = -1; return; }
+      ++seen[p.mt * nb * nsp + p.nt];
+    }
+  }
+}
+extern "C" void deal(double mts, int cg, int ntn, int grid, int *out) {
+  const qdp::PnDeal d = qdp::pn_deal(qdp::PnHeight{1, 2, cg, mts}, ntn, grid);
+  out[0] = d.cg; out[1] = d.nb; out[2] = d.nsp;
+}
 """
 
 
@@ -50,3 +65,28 @@ def test_tiles_cover_an_expert(host, rows, mf):
     h = np.diff(out)
     assert out[0] == 0 and out[-1] == nf
     assert h.min() >= 1 and h.max() <= 2 * mf and h.max() - h.min() <= 1
+
+
+def _ptr(a):
+    return a.ctypes.data_as(ctypes.c_void_p)
+
+
+@pytest.mark.parametrize("ntn", [1, 2, 3, 6, 12, 16, 35])
+def test_deal_covers_every_tile_evenly(host, ntn):
+    """Each tile is walked once, whatever the units; with few M-tiles no XCD
+    needs more rounds of its workgroups than an even deal would."""
+    for mts in list(range(1, 40)) + [63, 64, 65, 131, 512]:
+        for cg in (1, 2, 3, 8):
+            grid = min(256, -(-(mts + 1) * ntn // 8) * 8)
+            d = np.empty(3, np.int32)
+            host.deal(ctypes.c_double(mts), cg, ntn, grid, _ptr(d))
+            c, nb, nsp = (int(v) for v in d)
+            assert nb * nsp == ntn and (c == 1 or nsp == 1) and c in (1, cg)
+            for real in (mts + 5, mts):          # the routing may make more than expected
+                length, seen = np.zeros(8, np.int32), np.zeros((real, ntn), np.int32)
+                host.walk(c, nb, nsp, real, _ptr(length), _ptr(seen))
+                assert np.all(seen == 1), (real, cg, ntn)
+            if mts < 64 * cg:
+                assert -(-length.max() // (grid // 8)) <= -(-mts * ntn // grid), (mts, cg, ntn)
+            else:
+                assert (c, nb) == (cg, ntn)
