@@ -297,22 +297,33 @@ __global__ __launch_bounds__(64 * FW_WAVES) void gemm_few_kernel(GemmArgs p, int
 
 }  // namespace
 
-// Where this kernel replaces the decode kernel.  That one hands blocks of 256
-// weight rows of the experts with rows to 256 CUs (u of them, if every row has
-// an expert of its own), so it takes the time of whole rounds of the chip:
-//  * u <= 128: half of the chip or more would idle.  K = 2048: 1 token (u =
-//    48 / 64) W13 20.8 -> 10.4 us, W2 10.8 -> 7.3; 2 tokens (96 / 128)
-//    22.4 -> 15.7, 10.8 -> 8.8; above, one round wins: 4 tokens (192 / 256)
-//    22.8 against 26.0, 11.6 against 13.9.
-//  * with the residual, u >= 320: a second round with few units in it.  K =
-//    2048, 8 tokens (u = 384) 40.3 -> 33.0 us, 12 tokens 41.0 -> 37.7; K =
-//    4096, 4 tokens (384) 66.1 -> 51.0, 8 tokens 95.0 -> 76.6, 16 tokens 124
-//    -> 118; even or lost from 32 tokens on.  (6 tokens at K = 2048, u = 288:
-//    24.2 against 26.4.)  Without the residual the decode kernel keeps these:
-//    16 tokens, W2 23.4 against 26.8.
-//  * K no multiple of 256, which the decode kernel does not take.
+// Where this kernel is the faster one.  It streams an expert's weights once per
+// 8 rows, the decode kernel once per 48, the panel kernel once; p is the number of
+// passes an average expert with rows takes (half a pass more than the mean once
+// the rows of an expert vary).
+//
+//  * K a multiple of 256, against the decode kernel, which hands blocks of 256
+//    weight rows of the experts with rows to 256 CUs (u of them, if every row has
+//    an expert of its own) and takes the time of whole rounds of the chip.  Few
+//    blocks leave most of it idle: u * p up to 96, with the residual or K below
+//    1024 up to 128, and at most four passes (two and a half below 1024, where a
+//    pass is mostly its fixed part).  K = 2048, 1536 weight rows, one expert: 16
+//    rows 13.8 against 20.4 us, 32 rows 20.3 against 21.9, 48 rows 26.4 against
+//    21.8; K = 4096, 12288 rows on two experts of 16 rows 52.0 against 34.3; one
+//    token on eight experts (u = 48) 10.4 against 20.8.  (Here and below weights
+//    that no cache holds, except for the token.)
+//  * With the residual also u >= 320 (a second round with few units in it) at up
+//    to four rows per expert: K = 4096, N = 12288, 8 experts: 3 rows each 91
+//    against 98, 12 rows each 122 against 98; 128 experts with one row, N = 3072:
+//    83 against 96.  Without the residual the decode kernel keeps these.
+//  * Other K: up to four passes against the panel kernel where it takes them (K =
+//    384, N = 2048, one expert: 24 rows 14.1 against 15.1, 48 rows 20.5 against
+//    16.4); against the generic kernel two and a half for K of 1024 and more (K =
+//    2112, N = 2048: 64 rows on 4 experts 21.2 against 26.3, 128 rows 29.0
+//    against 26.4), below one, with the residual one and a half (K = 320: 128 rows
+//    on 16 experts 14.4 against 12.0, with it 14.6 against 15.1).
 constexpr int64_t kFewRows = 128;
-constexpr int64_t kFewIdle = 128, kFewSecond = 320;
+constexpr int64_t kFewSecond = 320;
 constexpr int64_t kBitmapKMax = 4096;    // two bitmap words per lane of one wave
 constexpr int64_t kFewWaves = 4096;      // waves that fill the chip's queues
 
@@ -323,7 +334,16 @@ FwPlan few_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, int epilogue,
   const int64_t nblk = epilogue == QD_EPI_SWIGLU ? N / 2 / 16 : N / FW_N;
   const int64_t act = std::min<int64_t>(std::max<int64_t>(rows, 1), E);   // experts with rows
   const int64_t u = act * ((N + 255) / 256);
-  if (!(u <= kFewIdle || K % 256 != 0 || (Ks > 0 && u >= kFewSecond))) return pl;
+  // eight times p
+  const int64_t p8 = E == 1 ? (rows + 7) / 8 * 8 : std::max<int64_t>(8, rows / act + 4);
+  if (K % 256 == 0) {
+    const bool brief = K < 1024;
+    const bool idle = p8 <= (brief ? 20 : 32) && u * p8 <= 8 * (Ks > 0 || brief ? 128 : 96);
+    if (!idle && !(Ks > 0 && u >= kFewSecond && rows <= 4 * act)) return pl;
+  } else {
+    const bool panel = K >= 256 && K % 128 == 0 && N % 128 == 0;
+    if (p8 > (panel ? 32 : K >= 1024 ? 20 : Ks > 0 ? 12 : 9)) return pl;
+  }
   // split K over waves while a wave per block would leave the chip short of
   // waves in flight
   int ls = 0;

@@ -135,6 +135,22 @@ def test_gemm_validation(lib):
     assert lib.moe_w4a4_grouped_gemm_amax_count(8192, 256, 256, 4, 8, 1) % 8 == 0
 
 
+def test_few_row_kernel_by_rows_per_expert(lib):
+    """The kernel that streams the weights once per eight rows takes a call by
+    the rows of an expert, not by their total: 128 rows on one expert, or 16 on
+    each of 8 wide ones, go where 136 go."""
+    form = lib.moe_w4a4_grouped_gemm_residual_form
+    cnt = lib.moe_w4a4_grouped_gemm_amax_count
+    assert form(128, 1536, 2048, 1, 64, 1) == 2            # compact: the panel kernel
+    assert form(128, 2048, 384, 2, 64, 0) == 2
+    for E, N, K, Ks in ((8, 28672, 4096, 128), (8, 1536, 2048, 0), (16, 1536, 2048, 0)):
+        assert cnt(128, N, K, E, Ks, 1) == cnt(136, N, K, E, Ks, 1)
+    assert cnt(128, 96, 320, 1, 24, 0) == 3 * 2            # the generic kernel's grid
+    # one token on eight experts of 128; few rows at a K only the generic kernel takes
+    assert cnt(8, 1536, 2048, 128, 64, 1) == 8 * 48
+    assert cnt(64, 96, 320, 16, 24, 0) == 16 * 2
+
+
 def test_gather_selected_validation(lib):
     rq = _nv(1, 8, 64, FAKE)
     r = lambda *x: Q.raw("rac_gather_selected", *x)
