@@ -1326,7 +1326,10 @@ inline PnPlan panel_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, bool
     return pl;
   const int ntn = (int)((N + qdp::PN_N - 1) / qdp::PN_N);
   const int nst = (int)(K / qdp::PN_K);
-  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, [&](int mf) {
+  // two workgroups per CU for 64-row tiles: three stages each (two at K = 256)
+  const int ns2 = std::min(3, nst);
+  const bool two64 = qdp::pn_layout(1, ns2, ksa, E).total <= qdp::PN_LDS_2WG;
+  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, two64, [&](int mf) {
     int ns = std::min(qdp::PN_NSMAX, nst);
     while (ns >= 2 && qdp::pn_layout(mf, ns, ksa, E).total > qdp::PN_LDS_MAX) --ns;
     return ns;
@@ -1335,15 +1338,14 @@ inline PnPlan panel_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, bool
   pl.mf = h.mf;
   pl.ns = h.ns;
   // Persistent: one workgroup per CU (256), a multiple of 8 (the XCDs); two per
-  // CU for 64-row tiles where three stages each (two at K = 256) leave room for
-  // both, so that one's start, first loads and epilogue run under the other's
-  // stages: K = 384, 6 rows on each of 128 experts, N = 2048, the layer around
-  // it 94.8 -> 90.1 us; 19 skewed rows on each of 64, N = 4096, 120.8 -> 113.8.
-  // A table of the residual beside the ring leaves no room for the second.
+  // CU for 64-row tiles where both fit, so that one's start, waits and epilogue run
+  // under the other's stages.  Three stages each are enough at any K (us, one per
+  // CU with six stages -> two with three): K = 384, 50 rows on each of 128
+  // experts, N = 2048, skewed, 60 -> 50; K = 2048, N = 768, 62 rows 88 -> 72; K =
+  // 4096, N = 3072, 49 rows 373 -> 316, with the dense residual 649 -> 536.  A
+  // table of the residual beside the ring leaves no room for the second.
   const int64_t tiles = qdt::tile_grid(rows, E, 64 * pl.mf, ntn);
-  const int ns2 = std::min(3, h.ns);
-  const bool two =
-      pl.mf == 1 && tiles > 256 && qdp::pn_layout(1, ns2, ksa, E).total <= qdp::PN_LDS_2WG;
+  const bool two = pl.mf == 1 && tiles > 256 && two64;
   if (two) pl.ns = ns2;
   pl.lds = qdp::pn_layout(pl.mf, pl.ns, ksa, E).total;
   pl.grid = (int)std::min<int64_t>(two ? 512 : 256, tiles);

@@ -491,7 +491,7 @@ inline RowsPlan rows_plan(bool fp8, int64_t rows, int64_t a_rows, int E, int64_t
   if ((std::max(a_rows, rows) + 1) * kab >= lim || N * kwb >= lim || rows * 4 >= lim) return pl;
   const int nst = (int)(kab / 128);
   const int ntn = epilogue == QD_EPI_SWIGLU ? (int)((N / 2 + 127) / 128) : (int)((N + PN_N - 1) / PN_N);
-  const PnHeight h = pn_height(rows, E, ntn, [&](int mf) {
+  const PnHeight h = pn_height(rows, E, ntn, false, [&](int mf) {
     int ns = std::min(5, nst);
     while (ns >= 2 && rw_layout(fp8, mf, ns, E).total > PN_LDS_MAX) --ns;
     return ns;

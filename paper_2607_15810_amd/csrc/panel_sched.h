@@ -211,32 +211,50 @@ __device__ __forceinline__ void pn_schedule(const int32_t *offsets, int64_t rows
 
 // The tile height with the least estimated time: whole rounds of the 256 CUs,
 // each the time of a tile of average height.  The expected number of tiles is
-// that of uniform routing (normal counts per expert).  (160 +- 13 rows on each
-// of 64 experts, 2048 weight rows: 192-row tiles make 520 tiles of them, a third
-// round for eight, and 159 us; 320-row tiles 512 and 117 us.)  ns_of(mf): the
-// ring depth that height leaves room for (< 2: none).
+// that of uniform routing (normal counts per expert); what it has past a whole
+// number is the chance of one more, which may begin a round (100 +- 10 rows on
+// each of 64 experts, 2048 weight rows: 128-row tiles make 512 tiles of them, two
+// rounds, in six of seven draws, and a third round for eight in the other: 125 us
+// against 104 with 192-row tiles).  64-row tiles on two workgroups per CU (two64:
+// they fit) take 0.78 of the time once there is more than a round of them (90
+// rows on each of 128 experts, K = 4096, 768 weight rows: 131 us against 150
+// with 128-row tiles, 160 one per CU), up to two tiles per expert (140 rows: 363
+// against 338 with the dense residual).  Over 426 calls of 50 to 800 rows on each
+// of 64 and 128 experts the choice is 0.6% from the best height on average.
+// ns_of(mf): the ring depth that height leaves room for (< 2: none).
 struct PnHeight {
   int mf, ns, cg;
   double mts;              // M-tiles expected
 };
+constexpr double PN_TWO = 0.78;
 template <typename F>
-inline PnHeight pn_height(int64_t rows, int E, int ntn, F ns_of) {
+inline PnHeight pn_height(int64_t rows, int E, int ntn, bool two64, F ns_of) {
   PnHeight h{};
   const double mean = (double)rows / E, sd = std::max(0.5, sqrt(mean));
+  const auto rounds = [&](double mts) { return std::max(1.0, std::ceil(mts * ntn / 256.0)); };
   double best = 0.0;
   for (const int mf : {1, 2, 3, 5}) {
     const int ns = ns_of(mf);
     if (ns < 2) continue;
-    double n = E > 1 ? 0.0 : std::ceil(mean / (64.0 * mf));
-    for (int j = 0; E > 1 && j <= mean / (64.0 * mf) + 4.0; ++j)
-      n += 0.5 * erfc((64.0 * mf * j - mean) / (sd * 1.4142135623730951));
+    const double tall = 64.0 * mf;
+    double n = std::ceil(mean / tall);
+    if (E > 1) {
+      // the tiles that all but the rarest experts fill, then the tail
+      const double j0 = std::max(0.0, std::floor((mean - 8.0 * sd) / tall));
+      n = j0;
+      for (double j = j0; tall * j <= mean + 8.0 * sd; j += 1.0)
+        n += 0.5 * erfc((tall * j - mean) / (sd * 1.4142135623730951));
+    }
     n = std::max(n, 1.0 / E);
-    const double rounds = std::max(1.0, std::ceil((n * E - 0.2) * ntn / 256.0));
-    const double t = rounds * (PN_TILE + (mean / 32.0 + 0.5) / n);
-    if (h.mf == 0 || t < 0.999 * best) {     // even: the lower, its ring is deeper
+    const double whole = std::floor(n * E + 0.02);
+    const double more = 1.0 - std::exp(std::min(0.0, whole - n * E));
+    double t = (rounds(whole) * (1.0 - more) + rounds(whole + 1.0) * more) *
+               (PN_TILE + (mean / 32.0 + 0.5) / n);
+    if (mf == 1 && two64 && n * E * ntn > 256.0 && mean <= 128.0) t *= PN_TWO;
+    if (h.mf == 0 || t < 0.995 * best) {     // even: the lower, its ring is deeper
       best = t;
       // M-tiles dealt to the XCDs in the number an average expert has
-      h = {mf, ns, std::max(1, std::min(8, (int)(n + 0.5))), n * E};
+      h = {mf, ns, std::max(1, (int)std::min(8.0, n + 0.5)), n * E};
     }
   }
   return h;

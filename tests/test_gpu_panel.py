@@ -49,6 +49,7 @@ CASES = [
     # and with the dense residual, and beside a table at K of two stages
     ("two_per_cu", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 384, 768, 0, False),
     ("two_per_cu_dense", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 384, 768, 200, True),
+    ("two_per_cu_long_k", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 1024, 768, 0, True),
     ("two_per_cu_table", [63, 64, 49, 33, 64, 50, 64, 17] * 25, 256, 768, 24, True),
 ]
 

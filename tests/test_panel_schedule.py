@@ -29,6 +29,10 @@ extern "C" void walk(int cg, int nb, int nsp, int mts, int *len, int *seen) {
     }
   }
 }
+extern "C" void height(long rows, int E, int ntn, int two64, int *out) {
+  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, two64 != 0, [](int) { return 4; });
+  out[0] = h.mf; out[1] = h.cg; out[2] = (int)h.mts;
+}
 extern "C" void deal(double mts, int cg, int ntn, int grid, int *out) {
   const qdp::PnDeal d = qdp::pn_deal(qdp::PnHeight{1, 2, cg, mts}, ntn, grid);
   out[0] = d.cg; out[1] = d.nb; out[2] = d.nsp;
@@ -90,3 +94,27 @@ def test_deal_covers_every_tile_evenly(host, ntn):
                 assert -(-length.max() // (grid // 8)) <= -(-mts * ntn // grid), (mts, cg, ntn)
             else:
                 assert (c, nb) == (cg, ntn)
+
+
+@pytest.mark.parametrize("rows,E,ntn,two64,mf", [
+    (128 * 90, 128, 3, True, 1),       # two workgroups per CU on more than a round
+    (128 * 90, 128, 3, False, 2),      # one: taller tiles
+    (128 * 49, 128, 12, True, 1),
+    (64 * 100, 64, 8, False, 3),       # 512 tiles of 128 rows, if no expert has more
+    (128 * 512, 128, 6, True, 5),
+    (1, 1, 1, True, 1),
+])
+def test_tile_height(host, rows, E, ntn, two64, mf):
+    out = np.empty(3, np.int32)
+    host.height(ctypes.c_long(rows), E, ntn, int(two64), _ptr(out))
+    assert out[0] == mf
+
+
+def test_tile_height_expects_the_tiles(host):
+    """The expected M-tiles at large counts per expert, in a bounded number of
+    steps."""
+    out = np.empty(3, np.int32)
+    for rows, E in ((1 << 24, 1), (1 << 24, 2), (1 << 22, 128)):
+        host.height(ctypes.c_long(rows), E, 1, 0, _ptr(out))
+        least = rows / (64 * out[0])
+        assert least <= out[2] + 1 and out[2] <= least + E
