@@ -236,7 +236,8 @@ qd_status rac_residual_gemm(const qd_nvfp4 *rq, const int32_t *sel_idx, int32_t 
  *   accr[r][n] = sum_{k in S} rq[src(r)][k] * w[e(r)][n][k]   (if rq)
  *   v[r][n]    = s_dec_a*s_dec_w[e] * acc - s_dec_r*s_dec_w[e] * accr
  * Products of decoded operands are exact; accumulation is f32.
- *   a               : activations [*][K] (groups 1).
+ *   a               : activations [*][K] (groups 1), of any number of rows;
+ *                     past 4 GiB of codes the generic kernel runs.
  *   row_token       : int32 [rows] gather map (NULL: row r reads a row r).
  *   expert_offsets  : int32 [E+1] row ranges per expert (NULL: E must be 1).
  *   rows            : number of grouped rows (T*k for the MoE layer).
@@ -287,7 +288,8 @@ qd_status moe_w4a4_grouped_gemm(const qd_nvfp4 *a, const int32_t *row_token,
  *                     [moe_w4a4_grouped_gemm_per_expert_amax_count(...)].
  *   Other arguments as moe_w4a4_grouped_gemm.  Runs on the kernel for many
  *   rows per expert at every size: QD_ERR_UNSUPPORTED where it does not
- *   apply (K a multiple of 128 and >= 256, N a multiple of 128, Ks <= ~440).
+ *   apply (K a multiple of 128 and >= 256, N a multiple of 128, Ks <= ~440,
+ *   activation codes below 4 GiB).
  * ------------------------------------------------------------------- */
 int64_t   moe_w4a4_grouped_gemm_per_expert_amax_count(int64_t rows, int64_t N, int64_t K,
                                                       int32_t E, int32_t Ks, int32_t epilogue);
@@ -354,8 +356,8 @@ qd_status fp8_quantize_rows(const void *x, int32_t dtype, int64_t rows, int64_t 
  *                     in moe_w4a4_grouped_gemm.
  *   w_codes, w_dec  : u8 [E][N][K], f32 [E][N].
  * Sizes: K % 64 == 0, K >= 256; N % 256 == 0 (few rows per expert) or
- * N % 128 == 0 (many); otherwise QD_ERR_UNSUPPORTED.  16-byte aligned codes
- * and output.
+ * N % 128 == 0 (many); activation codes below 4 GiB; otherwise
+ * QD_ERR_UNSUPPORTED.  16-byte aligned codes and output.
  * ------------------------------------------------------------------- */
 qd_status moe_fp8_grouped_gemm(const uint8_t *a_codes, const float *a_dec, int64_t a_rows,
                                const int32_t *row_token, const int32_t *expert_offsets,
@@ -401,7 +403,8 @@ qd_status mxfp4_quantize_rows(const void *x, int32_t dtype, int64_t rows, int64_
  *   w_codes, w_scales : u8 [E][N][K/2], u8 [E][N][K/32].
  *   row_token / offsets as in moe_w4a4_grouped_gemm.
  * Sizes: K % 128 == 0, K >= 256; N % 256 == 0 (few rows per expert) or
- * N % 128 == 0 (many); otherwise QD_ERR_UNSUPPORTED.
+ * N % 128 == 0 (many); activation codes below 4 GiB; otherwise
+ * QD_ERR_UNSUPPORTED.
  * ------------------------------------------------------------------- */
 qd_status moe_mxfp4_grouped_gemm(const uint8_t *a_codes, const uint8_t *a_scales, int64_t a_rows,
                                  const int32_t *row_token, const int32_t *expert_offsets,

@@ -404,13 +404,15 @@ struct F8Plan {
   int tm, ntn, grid, lds;
 };
 
-inline F8Plan fp8_plan(int64_t rows, int E, int64_t N, int64_t K, int epilogue) {
+// a_rows: rows of the activations, which row_token may name any of
+inline F8Plan fp8_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, int epilogue) {
   F8Plan pl{};
   pl.tm = rows > (int64_t)E * F8_DECODE_ROWS ? 256 : 32;
   const int nt = pl.tm == 256 ? F8Cfg<256>::NT : F8Cfg<32>::NT;
   if (K < 4 * F8_K || K % F8_K != 0 || N % nt != 0 || E > F8_EMAX) return pl;
   if (epilogue == QD_EPI_SWIGLU && (N / 2) % (nt / 2) != 0) return pl;
-  if (N * K >= (1LL << 32) || (rows + 1) * K >= (1LL << 32) || (rows + 256) * N * 2 >= (1LL << 32))
+  if (N * K >= (1LL << 32) || (std::max(rows, a_rows) + 1) * K >= (1LL << 32) ||
+      (rows + 256) * N * 2 >= (1LL << 32))
     return pl;
   pl.ntn = (int)(N / nt);
   pl.lds = pl.tm == 256 ? F8Cfg<256>::LDS : F8Cfg<32>::LDS;
@@ -485,7 +487,7 @@ extern "C" qd_status moe_fp8_grouped_gemm(const uint8_t *a_codes, const float *a
   if (!row_token && rows > a_rows) return QD_ERR_SHAPE;
   if (!qdh::aligned16(a_codes) || !qdh::aligned16(w_codes) || !qdh::aligned16(out))
     return QD_ERR_ALIGN;
-  const F8Plan pl = fp8_plan(rows, E, N, K, epilogue);
+  const F8Plan pl = fp8_plan(rows, a_rows, E, N, K, epilogue);
   if (!pl.ok) return QD_ERR_UNSUPPORTED;
   if (qdh::fault_injected()) return QD_ERR_HIP;
   if (rows == 0) return QD_OK;
@@ -569,8 +571,8 @@ extern "C" qd_status qd_fp8_moe_layer_forward(const void *x, const float *logits
   if (!ws || ws_bytes < qd_fp8_moe_layer_workspace(T, H, E, k, I)) return QD_ERR_WORKSPACE;
   if (!qdh::aligned16(ws) || !qdh::aligned16(y)) return QD_ERR_ALIGN;
   const int64_t R = T * k;
-  if (!fp8_plan(R > 0 ? R : 1, E, 2 * I, H, QD_EPI_SWIGLU).ok ||
-      !fp8_plan(R > 0 ? R : 1, E, H, I, QD_EPI_NONE).ok)
+  if (!fp8_plan(R > 0 ? R : 1, T, E, 2 * I, H, QD_EPI_SWIGLU).ok ||
+      !fp8_plan(R > 0 ? R : 1, R, E, H, I, QD_EPI_NONE).ok)
     return QD_ERR_UNSUPPORTED;
   if (T == 0) return QD_OK;
   const F8Layout L = fp8_layer_layout(T, H, E, k, I);

@@ -1267,12 +1267,13 @@ struct TlPlan {
   int ntn, grid, lds, grp;
 };
 
-inline TlPlan tile_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks) {
+// a_rows: rows of the activations, which row_token may name any of
+inline TlPlan tile_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, int Ks) {
   TlPlan pl{};
   if (Ks <= 0 || K < 4 * TL_K || K % (2 * TL_K) != 0 || N % TL_N != 0 || E > TL_EMAX) return pl;
   // byte offsets inside one activation matrix or one expert's weights, and
   // output offsets, fit 32 bits
-  if (N * K / 2 >= (1LL << 32) || (rows + 1) * K / 2 >= (1LL << 32)) return pl;
+  if (N * K / 2 >= (1LL << 32) || (std::max(rows, a_rows) + 1) * K / 2 >= (1LL << 32)) return pl;
   if ((rows + TL_M) * N * 2 >= (1LL << 32)) return pl;
   const int ksa = (Ks + 15) / 16 * 16;
   pl.lds = tl_lds_bytes(ksa, false);
@@ -1310,7 +1311,8 @@ struct PnPlan {
   qdp::PnDeal deal;
 };
 
-inline PnPlan panel_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, bool per_expert) {
+inline PnPlan panel_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, int Ks,
+                         bool per_expert) {
   PnPlan pl{};
   if (K < 2 * qdp::PN_K || K % qdp::PN_K != 0 || N % 128 != 0 || E > qdp::PN_EMAX) return pl;
   int ksa = (Ks + 15) / 16 * 16;
@@ -1321,7 +1323,8 @@ inline PnPlan panel_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, bool
     ksa = 0;
   }
   // 32-bit byte offsets into one operand and into the output
-  if ((rows + 1) * K / 2 >= (1LL << 32) || (rows + 1) * ksa * 2 >= (1LL << 32) ||
+  const int64_t src = std::max(rows, a_rows) + 1;
+  if (src * K / 2 >= (1LL << 32) || src * ksa * 2 >= (1LL << 32) ||
       (rows + 320) * N * 2 >= (1LL << 32))
     return pl;
   const int ntn = (int)((N + qdp::PN_N - 1) / qdp::PN_N);
@@ -1388,8 +1391,8 @@ struct Choice {
   TlPlan tl;
 };
 
-inline Choice choose(int64_t rows, int E, int64_t N, int64_t K, int Ks, int epilogue, bool bitmap,
-                     bool per_expert) {
+inline Choice choose(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, int Ks, int epilogue,
+                     bool bitmap, bool per_expert) {
   Choice c{};
   c.k = Kern::generic;
   if (!per_expert) {
@@ -1404,13 +1407,13 @@ inline Choice choose(int64_t rows, int E, int64_t N, int64_t K, int Ks, int epil
     c.k = Kern::skinny;
     return c;
   }
-  c.pn = panel_plan(rows, E, N, K, Ks, per_expert);
+  c.pn = panel_plan(rows, a_rows, E, N, K, Ks, per_expert);
   if (c.pn.ok) {
     c.k = Kern::panel;
     return c;
   }
   if (per_expert) {
-    c.tl = tile_plan(rows, E, N, K, Ks);
+    c.tl = tile_plan(rows, a_rows, E, N, K, Ks);
     if (c.tl.ok) c.k = Kern::tile;
   }
   return c;
@@ -1449,7 +1452,7 @@ void launch_epi(const GemmArgs &p, int epi, dim3 grid, hipStream_t s, const Choi
 bool qdi::gemm_wants_rq_sel(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
                             int32_t epilogue) {
   if (Ks <= 0 || rows <= 0 || E < 1 || N <= 0 || K <= 0) return false;
-  const Choice c = choose(rows, E, N, K, Ks, epilogue, false, false);
+  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, false);
   return c.k == Kern::panel && !c.pn.dense;
 }
 
@@ -1457,7 +1460,7 @@ int64_t qdi::gemm_amax_written(int64_t rows, int32_t E, int64_t N, int64_t K, in
                                int32_t epilogue, bool bitmap) {
   if (rows <= 0 || E < 1 || N <= 0 || K <= 0 || Ks < 0) return 0;
   // the grid of the kernel the grouped GEMM takes
-  const Choice c = choose(rows, E, N, K, Ks, epilogue, bitmap, false);
+  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, bitmap, false);
   if (c.k == Kern::few) return c.fw.grid;
   if (c.k == Kern::skinny) return c.sk.grid;
   if (c.k == Kern::panel) return c.pn.grid;
@@ -1467,7 +1470,7 @@ int64_t qdi::gemm_amax_written(int64_t rows, int32_t E, int64_t N, int64_t K, in
 bool qdi::gemm_takes_bitmap(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
                             int32_t epilogue) {
   if (Ks <= 0 || rows <= 0 || E < 1 || N <= 0 || K <= 0) return false;
-  const Kern k = choose(rows, E, N, K, Ks, epilogue, true, false).k;
+  const Kern k = choose(rows, rows, E, N, K, Ks, epilogue, true, false).k;
   return k == Kern::few || k == Kern::skinny;
 }
 
@@ -1480,7 +1483,7 @@ extern "C" int32_t moe_w4a4_grouped_gemm_residual_form(int64_t rows, int64_t N, 
 extern "C" int64_t moe_w4a4_grouped_gemm_amax_count(int64_t rows, int64_t N, int64_t K,
                                                     int32_t E, int32_t Ks, int32_t epilogue) {
   if (rows < 0 || N <= 0 || K <= 0 || E < 1 || Ks < 0) return 0;
-  const Choice c = choose(rows, E, N, K, Ks, epilogue, false, false);
+  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, false);
   if (c.k == Kern::few) return c.fw.grid;
   if (c.k == Kern::skinny) return c.sk.grid;
   // every kernel writes (or zeroes) every entry, up to the largest grid
@@ -1492,7 +1495,7 @@ extern "C" int64_t moe_w4a4_grouped_gemm_per_expert_amax_count(int64_t rows, int
                                                                int64_t K, int32_t E, int32_t Ks,
                                                                int32_t epilogue) {
   if (rows < 0 || N <= 0 || K <= 0 || E < 1 || Ks < 1) return 0;
-  const Choice c = choose(rows, E, N, K, Ks, epilogue, false, true);
+  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, true);
   return c.k == Kern::panel ? c.pn.grid : c.k == Kern::tile ? c.tl.grid : 0;
 }
 
@@ -1575,7 +1578,10 @@ qd_status grouped_gemm_impl(const qd_nvfp4 *a, const int32_t *row_token,
   if (N > 0x7fffffff || K > 0x7fffffff) return QD_ERR_UNSUPPORTED;
   const int64_t gx = grid_x(rows, E, true), gy = grid_y(N, epilogue);
   if (gx > 0x7fffffffLL || gy > 65535) return QD_ERR_UNSUPPORTED;
-  const Choice c = choose(rows, E, N, K, rac ? Ks : 0, epilogue, bitmap != nullptr, per_expert);
+  // (past 4 GiB of activations the generic kernel, which writes no more partials
+  // than the count for these sizes and reads rq where that names rq_sel)
+  const Choice c = choose(rows, row_token ? a->rows : rows, E, N, K, rac ? Ks : 0, epilogue,
+                          bitmap != nullptr, per_expert);
   if (bitmap && c.k != Kern::few && c.k != Kern::skinny) return QD_ERR_UNSUPPORTED;
   if (per_expert) {
     // per-expert sets take the compact residual (one per grouped row)

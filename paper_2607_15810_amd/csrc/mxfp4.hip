@@ -336,13 +336,14 @@ struct MxPlan {
   int tm, ntn, grid, lds;
 };
 
-inline MxPlan mx_plan(int64_t rows, int E, int64_t N, int64_t K, int epilogue) {
+// a_rows: rows of the activations, which row_token may name any of
+inline MxPlan mx_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, int epilogue) {
   MxPlan pl{};
   pl.tm = rows > (int64_t)E * MX_DECODE_ROWS ? 256 : 32;
   const int nt = pl.tm == 256 ? MxCfg<256>::NT : MxCfg<32>::NT;
   if (K < 4 * MX_K || K % 128 != 0 || N % nt != 0 || E > MX_EMAX) return pl;
   if (epilogue == QD_EPI_SWIGLU && (N / 2) % (nt / 2) != 0) return pl;
-  if (N * K / 2 >= (1LL << 32) || (rows + 1) * K / 2 >= (1LL << 32) ||
+  if (N * K / 2 >= (1LL << 32) || (std::max(rows, a_rows) + 1) * K / 2 >= (1LL << 32) ||
       (rows + 256) * N * 2 >= (1LL << 32))
     return pl;
   pl.ntn = (int)(N / nt);
@@ -413,7 +414,7 @@ extern "C" qd_status moe_mxfp4_grouped_gemm(const uint8_t *a_codes, const uint8_
   if (!qdh::aligned16(a_codes) || !qdh::aligned16(w_codes) || !qdh::aligned16(out) ||
       ((uintptr_t)a_scales & 3u) || ((uintptr_t)w_scales & 3u))
     return QD_ERR_ALIGN;
-  const MxPlan pl = mx_plan(rows, E, N, K, epilogue);
+  const MxPlan pl = mx_plan(rows, a_rows, E, N, K, epilogue);
   if (!pl.ok) return QD_ERR_UNSUPPORTED;
   if (qdh::fault_injected()) return QD_ERR_HIP;
   if (rows == 0) return QD_OK;
@@ -481,8 +482,8 @@ extern "C" qd_status qd_mxfp4_moe_layer_forward(const void *x, const float *logi
   if (!ws || ws_bytes < qd_mxfp4_moe_layer_workspace(T, H, E, k, I)) return QD_ERR_WORKSPACE;
   if (!qdh::aligned16(ws) || !qdh::aligned16(y)) return QD_ERR_ALIGN;
   const int64_t R = T * k;
-  if (!mx_plan(R > 0 ? R : 1, E, 2 * I, H, QD_EPI_SWIGLU).ok ||
-      !mx_plan(R > 0 ? R : 1, E, H, I, QD_EPI_NONE).ok)
+  if (!mx_plan(R > 0 ? R : 1, T, E, 2 * I, H, QD_EPI_SWIGLU).ok ||
+      !mx_plan(R > 0 ? R : 1, R, E, H, I, QD_EPI_NONE).ok)
     return QD_ERR_UNSUPPORTED;
   if (T == 0) return QD_OK;
   const MxLayout L = mx_layer_layout(T, H, E, k, I);

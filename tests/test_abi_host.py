@@ -363,3 +363,19 @@ def test_block_validation(lib):
              None) == Q.QD_ERR_UNSUPPORTED                               # rows past LDS
     assert b(None, None, ctypes.c_float(1e-6), None, 0, H, E, k, I, 8, 0, 1, ctypes.byref(w13),
              ctypes.byref(w2), None, None, 0, None) == Q.QD_OK          # empty batch
+
+
+def test_activations_past_4_gib(lib):
+    """The kernels whose offsets into the activations are 32 bits wide refuse a
+    matrix that these do not span, however few of its rows are named."""
+    E, N, K, rows = 4, 256, 256, 1024
+    w, F = _nv(E, N, K, FAKE), FAKE
+    big = 2 * 2 ** 32 // K                                  # rows of 4 GiB of FP4 codes
+    a, rq = _nv(1, big, K, F), _nv(1, big, K, F)
+    assert lib.moe_w4a4_grouped_gemm_per_expert(
+        ctypes.byref(a), F, F, E, rows, ctypes.byref(w), ctypes.byref(rq), F, 8, F, 0, F, None,
+        None) == Q.QD_ERR_UNSUPPORTED
+    assert lib.moe_fp8_grouped_gemm(F, F, 2 ** 32 // K, F, F, E, rows, F, F, N, K, 0, F,
+                                    None) == Q.QD_ERR_UNSUPPORTED
+    assert lib.moe_mxfp4_grouped_gemm(F, F, big, F, F, E, rows, F, F, N, K, 0, F,
+                                      None) == Q.QD_ERR_UNSUPPORTED

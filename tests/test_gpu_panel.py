@@ -161,3 +161,38 @@ def test_panel_gemm_many_rows_of_one_expert():
         for r0 in range(0, R, 1 << 20):
             t = tok[r0:r0 + (1 << 20)].long()
             assert torch.equal(out[r0:r0 + (1 << 20)], few[t]), f"{name}: rows {r0} on"
+
+
+@pytest.mark.parametrize("Ks", [0, 16, 160], ids=["plain", "compact", "dense"])
+def test_rows_past_4_gib_of_activations(Ks):
+    """row_token names rows whose codes lie past 4 GiB of a larger matrix: what
+    the same rows give on their own.  Two kernels, so two roundings of sums in
+    another order: each within half a bf16 ulp of nearly the same value."""
+    K, N, n, E = 256, 256, 300, 2
+    A = 2 * 2 ** 32 // K + n
+    g = torch.Generator().manual_seed(13)
+    x = torch.randn((n, K), generator=g)
+    x[:, ::17] *= 20.0
+    xg = x.to(torch.bfloat16).to(DEV)
+    w = ops.quantize_weight((torch.randn((E, N, K), generator=g) * 0.02).to(torch.bfloat16).to(DEV))
+    xq, scores, ramax = ops.quantize_act(xg, rac=True)
+    sel = rq = None
+    if Ks:
+        sel, rq, _, _ = ops.select_channels(xg, xq, Ks, scores, ramax)
+
+    def far(t):
+        big = ops.NVFP4Tensor.empty(1, A, K, DEV)
+        big.codes.zero_()
+        big.scales.zero_()
+        big.codes[0, -n:] = t.codes[0]
+        big.scales[0, -n:] = t.scales[0]
+        big.gscale.copy_(t.gscale)
+        return big
+
+    tok = torch.arange(n, dtype=torch.int32, device=DEV)
+    offs = torch.tensor([0, n // 2, n], dtype=torch.int32, device=DEV)
+    near, _ = ops.grouped_gemm(xq, w, n, tok, offs, rq, sel)
+    out, _ = ops.grouped_gemm(far(xq), w, n, tok + (A - n), offs, far(rq) if Ks else None, sel,
+                              rq_sel=ops.gather_selected(rq, sel) if Ks else None)
+    d = (out.double() - near.double()).norm() / near.double().norm()
+    assert d <= 2.0 ** -8, float(d)
