@@ -111,7 +111,8 @@ qd_status nvfp4_quantize_act(const void *x, int x_dtype, int64_t rows, int64_t c
  *   w   : bf16 [groups][rows][cols].
  *   out : groups, rows, cols; written, and with them out->scales_frag where
  *         it is not NULL and the sizes have a fragment-ordered copy (rows % 16
- *         == 0, cols % 256 == 0; what nvfp4_pack_frag_scales writes).
+ *         == 0, cols % 256 == 0; what nvfp4_pack_frag_scales writes; 16-byte
+ *         aligned then, ignored for other sizes).
  *   ws  : at least nvfp4_quantize_weight_workspace(groups, rows, cols) bytes.
  * ------------------------------------------------------------------- */
 size_t    nvfp4_quantize_weight_workspace(int64_t groups, int64_t rows, int64_t cols);

@@ -266,7 +266,10 @@ extern "C" qd_status nvfp4_quantize_weight(const void *w, int64_t groups, int64_
   if (st) return st;
   if (rows == 0) return QD_OK;
   if (!w) return QD_ERR_NULL;
-  if (!qdh::aligned16(w)) return QD_ERR_ALIGN;
+  // the fragment-ordered copy of the scales, where the caller gave it room
+  // and the sizes have one
+  const bool frag = out->scales_frag != nullptr && rows % 16 == 0 && cols % 256 == 0;
+  if (!qdh::aligned16(w) || (frag && !qdh::aligned16(out->scales_frag))) return QD_ERR_ALIGN;
   if (!ws || ws_bytes < nvfp4_quantize_weight_workspace(groups, rows, cols)) return QD_ERR_WORKSPACE;
   if (!qdh::aligned16(ws)) return QD_ERR_ALIGN;
   if (groups > 65535) return QD_ERR_UNSUPPORTED;
@@ -276,10 +279,6 @@ extern "C" qd_status nvfp4_quantize_weight(const void *w, int64_t groups, int64_
   const int64_t n16 = rows * cols / 16;
   float *part = static_cast<float *>(ws);
   constexpr int P = 64;
-  // the fragment-ordered copy of the scales, where the caller gave it room
-  // and the sizes have one
-  const bool frag = out->scales_frag != nullptr && qdh::aligned16(out->scales_frag) &&
-                    rows % 16 == 0 && cols % 256 == 0;
   const dim3 grid((unsigned)std::min<int64_t>((n16 + 255) / 256, 256), (unsigned)groups);
   const uint16_t *wb = static_cast<const uint16_t *>(w);
   hipLaunchKernelGGL(amax_group_kernel, dim3(P, (unsigned)groups), dim3(256), 0, s, wb, n16, part);

@@ -230,6 +230,17 @@ def test_frag_scales_validation(lib):
     assert r(ctypes.byref(_nv(2, 32, 512, FAKE)), FAKE + 4, None) == Q.QD_ERR_ALIGN
 
 
+def test_quantize_weight_rejects_misaligned_frag_scales(lib):
+    q = lib.nvfp4_quantize_weight
+    ws = lib.nvfp4_quantize_weight_workspace(2, 32, 512)
+    out = _nv(2, 32, 512, FAKE)
+    out.scales_frag = FAKE + 8
+    assert q(FAKE, 2, 32, 512, ctypes.byref(out), FAKE, ws, None) == Q.QD_ERR_ALIGN
+    out = _nv(2, 0, 512, FAKE)                     # nothing to write
+    out.scales_frag = FAKE + 8
+    assert q(FAKE, 2, 0, 512, ctypes.byref(out), FAKE, ws, None) == Q.QD_OK
+
+
 def test_gemm_rejects_misaligned_frag_scales(lib):
     a = _nv(1, 16, 256, FAKE)
     w = _nv(4, 128, 256, FAKE)
