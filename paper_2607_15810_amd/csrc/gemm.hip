@@ -20,6 +20,7 @@
 #include "gemm_args.h"
 #include "gemm_few.h"
 #include "gemm_panel.h"
+#include "gemm_wide.h"
 #include "lds_dma.h"
 #include "tile_sched.h"
 
@@ -1309,6 +1310,7 @@ struct PnPlan {
   bool dense;
   int mf, ns, grid, lds;
   qdp::PnDeal deal;
+  double time;
 };
 
 inline PnPlan panel_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, int Ks,
@@ -1340,6 +1342,7 @@ inline PnPlan panel_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t
   if (h.mf == 0) return pl;
   pl.mf = h.mf;
   pl.ns = h.ns;
+  pl.time = h.time;
   // Persistent: one workgroup per CU (256), a multiple of 8 (the XCDs); two per
   // CU for 64-row tiles where both fit, so that one's start, waits and epilogue run
   // under the other's stages.  Three stages each are enough at any K (us, one per
@@ -1378,21 +1381,24 @@ void launch_tile(const GemmArgs &p, const TlPlan &pl, hipStream_t s) {
 }
 
 // The kernel of a grouped GEMM: the few-row kernel for a handful of rows, the
-// decode kernel for few rows per expert, the panel kernel above, the tile kernel
+// decode kernel for few rows per expert, the panel kernel above (the wide one
+// where no residual is fused and its tiles come out nearly full), the tile kernel
 // for per-expert sets whose table the panel kernel cannot hold, and the generic
 // kernel for sizes none takes.
-enum class Kern { few, skinny, panel, tile, generic };
+enum class Kern { few, skinny, wide, panel, tile, generic };
 
 struct Choice {
   Kern k;
   qdf::FwPlan fw;
   SkPlan sk;
+  qdw::WdPlan wd;
   PnPlan pn;
   TlPlan tl;
 };
 
+// sfrag: the weights carry fragment-ordered scales
 inline Choice choose(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, int Ks, int epilogue,
-                     bool bitmap, bool per_expert) {
+                     bool bitmap, bool per_expert, bool sfrag) {
   Choice c{};
   c.k = Kern::generic;
   if (!per_expert) {
@@ -1410,6 +1416,10 @@ inline Choice choose(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, 
   c.pn = panel_plan(rows, a_rows, E, N, K, Ks, per_expert);
   if (c.pn.ok) {
     c.k = Kern::panel;
+    if (Ks <= 0 && sfrag) {
+      c.wd = qdw::wide_plan(rows, a_rows, E, N, K, c.pn.time);
+      if (c.wd.ok) c.k = Kern::wide;
+    }
     return c;
   }
   if (per_expert) {
@@ -1429,6 +1439,9 @@ void launch_epi(const GemmArgs &p, int epi, dim3 grid, hipStream_t s, const Choi
     case Kern::skinny:
       if (sw) launch_skinny<GATHER, RAC, QD_EPI_SWIGLU>(p, c.sk, s);
       else launch_skinny<GATHER, RAC, QD_EPI_NONE>(p, c.sk, s);
+      return;
+    case Kern::wide:
+      qdw::launch_wide(p, epi, c.wd, s);
       return;
     case Kern::panel:
       launch_pn(p, epi, c.pn, s);
@@ -1452,25 +1465,26 @@ void launch_epi(const GemmArgs &p, int epi, dim3 grid, hipStream_t s, const Choi
 bool qdi::gemm_wants_rq_sel(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
                             int32_t epilogue) {
   if (Ks <= 0 || rows <= 0 || E < 1 || N <= 0 || K <= 0) return false;
-  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, false);
+  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, false, true);
   return c.k == Kern::panel && !c.pn.dense;
 }
 
 int64_t qdi::gemm_amax_written(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
                                int32_t epilogue, bool bitmap) {
   if (rows <= 0 || E < 1 || N <= 0 || K <= 0 || Ks < 0) return 0;
-  // the grid of the kernel the grouped GEMM takes
-  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, bitmap, false);
+  // the grid of the kernel the grouped GEMM takes (of both that it may take: the
+  // wide one depends on the weights' scales)
+  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, bitmap, false, true);
   if (c.k == Kern::few) return c.fw.grid;
   if (c.k == Kern::skinny) return c.sk.grid;
-  if (c.k == Kern::panel) return c.pn.grid;
+  if (c.pn.ok) return std::max(c.pn.grid, c.wd.grid);
   return grid_x(rows, E, true) * grid_y(N, epilogue);
 }
 
 bool qdi::gemm_takes_bitmap(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
                             int32_t epilogue) {
   if (Ks <= 0 || rows <= 0 || E < 1 || N <= 0 || K <= 0) return false;
-  const Kern k = choose(rows, rows, E, N, K, Ks, epilogue, true, false).k;
+  const Kern k = choose(rows, rows, E, N, K, Ks, epilogue, true, false, true).k;
   return k == Kern::few || k == Kern::skinny;
 }
 
@@ -1483,11 +1497,11 @@ extern "C" int32_t moe_w4a4_grouped_gemm_residual_form(int64_t rows, int64_t N, 
 extern "C" int64_t moe_w4a4_grouped_gemm_amax_count(int64_t rows, int64_t N, int64_t K,
                                                     int32_t E, int32_t Ks, int32_t epilogue) {
   if (rows < 0 || N <= 0 || K <= 0 || E < 1 || Ks < 0) return 0;
-  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, false);
+  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, false, true);
   if (c.k == Kern::few) return c.fw.grid;
   if (c.k == Kern::skinny) return c.sk.grid;
   // every kernel writes (or zeroes) every entry, up to the largest grid
-  return std::max<int64_t>(c.k == Kern::panel ? c.pn.grid : 0,
+  return std::max<int64_t>(std::max(c.pn.grid, c.wd.grid),
                            grid_x(rows, E, true) * grid_y(N, epilogue));
 }
 
@@ -1495,7 +1509,7 @@ extern "C" int64_t moe_w4a4_grouped_gemm_per_expert_amax_count(int64_t rows, int
                                                                int64_t K, int32_t E, int32_t Ks,
                                                                int32_t epilogue) {
   if (rows < 0 || N <= 0 || K <= 0 || E < 1 || Ks < 1) return 0;
-  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, true);
+  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, true, true);
   return c.k == Kern::panel ? c.pn.grid : c.k == Kern::tile ? c.tl.grid : 0;
 }
 
@@ -1581,7 +1595,7 @@ qd_status grouped_gemm_impl(const qd_nvfp4 *a, const int32_t *row_token,
   // (past 4 GiB of activations the generic kernel, which writes no more partials
   // than the count for these sizes and reads rq where that names rq_sel)
   const Choice c = choose(rows, row_token ? a->rows : rows, E, N, K, rac ? Ks : 0, epilogue,
-                          bitmap != nullptr, per_expert);
+                          bitmap != nullptr, per_expert, w->scales_frag != nullptr);
   if (bitmap && c.k != Kern::few && c.k != Kern::skinny) return QD_ERR_UNSUPPORTED;
   if (per_expert) {
     // per-expert sets take the compact residual (one per grouped row)

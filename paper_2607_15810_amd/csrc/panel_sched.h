@@ -209,10 +209,23 @@ __device__ __forceinline__ void pn_schedule(const int32_t *offsets, int64_t rows
   if (E == PN_EMAX && tid == PN_THREADS - 1) mpre[E] = base;
 }
 
+// Expected experts with more than x rows, of one with a normal count (E = 1: its
+// rows are known), and rounds of the 256 CUs that mts expected M-tiles of ntn
+// tiles each take: what mts has past a whole number is the chance of one more.
+inline double pn_above(double x, double mean, double sd, int E) {
+  if (E == 1) return mean > x ? 1.0 : 0.0;
+  return 0.5 * erfc((x - mean) / (sd * 1.4142135623730951));
+}
+inline double pn_rounds(double mts, int ntn) {
+  const double whole = std::floor(mts + 0.02), more = 1.0 - std::exp(std::min(0.0, whole - mts));
+  const auto rounds = [&](double m) { return std::max(1.0, std::ceil(m * ntn / 256.0)); };
+  return rounds(whole) * (1.0 - more) + rounds(whole + 1.0) * more;
+}
+
 // The tile height with the least estimated time: whole rounds of the 256 CUs,
 // each the time of a tile of average height.  The expected number of tiles is
-// that of uniform routing (normal counts per expert); what it has past a whole
-// number is the chance of one more, which may begin a round (100 +- 10 rows on
+// that of uniform routing (normal counts per expert).  One tile more may begin a
+// round (100 +- 10 rows on
 // each of 64 experts, 2048 weight rows: 128-row tiles make 512 tiles of them, two
 // rounds, in six of seven draws, and a third round for eight in the other: 125 us
 // against 104 with 192-row tiles).  64-row tiles on two workgroups per CU (two64:
@@ -225,36 +238,29 @@ __device__ __forceinline__ void pn_schedule(const int32_t *offsets, int64_t rows
 struct PnHeight {
   int mf, ns, cg;
   double mts;              // M-tiles expected
+  double time;             // in that of a 32-row fragment of a tile
 };
 constexpr double PN_TWO = 0.78;
 template <typename F>
 inline PnHeight pn_height(int64_t rows, int E, int ntn, bool two64, F ns_of) {
   PnHeight h{};
   const double mean = (double)rows / E, sd = std::max(0.5, sqrt(mean));
-  const auto rounds = [&](double mts) { return std::max(1.0, std::ceil(mts * ntn / 256.0)); };
   double best = 0.0;
   for (const int mf : {1, 2, 3, 5}) {
     const int ns = ns_of(mf);
     if (ns < 2) continue;
     const double tall = 64.0 * mf;
-    double n = std::ceil(mean / tall);
-    if (E > 1) {
-      // the tiles that all but the rarest experts fill, then the tail
-      const double j0 = std::max(0.0, std::floor((mean - 8.0 * sd) / tall));
-      n = j0;
-      for (double j = j0; tall * j <= mean + 8.0 * sd; j += 1.0)
-        n += 0.5 * erfc((tall * j - mean) / (sd * 1.4142135623730951));
-    }
+    // the tiles that all but the rarest experts fill, then the tail
+    const double j0 = std::max(0.0, std::floor((mean - 8.0 * sd) / tall));
+    double n = j0;
+    for (double j = j0; tall * j <= mean + 8.0 * sd; j += 1.0) n += pn_above(tall * j, mean, sd, E);
     n = std::max(n, 1.0 / E);
-    const double whole = std::floor(n * E + 0.02);
-    const double more = 1.0 - std::exp(std::min(0.0, whole - n * E));
-    double t = (rounds(whole) * (1.0 - more) + rounds(whole + 1.0) * more) *
-               (PN_TILE + (mean / 32.0 + 0.5) / n);
+    double t = pn_rounds(n * E, ntn) * (PN_TILE + (mean / 32.0 + 0.5) / n);
     if (mf == 1 && two64 && n * E * ntn > 256.0 && mean <= 128.0) t *= PN_TWO;
     if (h.mf == 0 || t < 0.995 * best) {     // even: the lower, its ring is deeper
       best = t;
       // M-tiles dealt to the XCDs in the number an average expert has
-      h = {mf, ns, std::max(1, (int)std::min(8.0, n + 0.5)), n * E};
+      h = {mf, ns, std::max(1, (int)std::min(8.0, n + 0.5)), n * E, t};
     }
   }
   return h;

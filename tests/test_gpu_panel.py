@@ -50,6 +50,12 @@ CASES = [
     ("two_per_cu", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 384, 768, 0, False),
     ("two_per_cu_dense", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 384, 768, 200, True),
     ("two_per_cu_long_k", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 1024, 768, 0, True),
+    # tiles of 256 x 256 rows (no residual, K a multiple of 256): remainders of
+    # one and two such tiles, half tiles, and counts far from the mean
+    ("wide_full", [255, 256, 250, 225] * 6, 512, 1536, 0, True),
+    ("wide_halves", [128, 127, 97, 64, 65, 96] * 4, 256, 1536, 0, False),
+    ("wide_uneven", [600, 0, 130, 129, 1, 512, 257, 200] * 3, 768, 1536, 0, True),
+    ("wide_one_expert", [13 * 256], 256, 4096, 0, False),
     ("two_per_cu_table", [63, 64, 49, 33, 64, 50, 64, 17] * 25, 256, 768, 24, True),
 ]
 

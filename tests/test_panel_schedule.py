@@ -15,6 +15,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCE = """
 #include "panel_sched.h"
+#include "gemm_wide.h"
 extern "C" void cuts(int nf, int n, int *out) {
   for (int i = 0; i <= n; ++i) out[i] = qdp::pn_cut(nf, n, nf / n, i);
 }
@@ -33,8 +34,12 @@ extern "C" void height(long rows, int E, int ntn, int two64, int *out) {
   const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, two64 != 0, [](int) { return 4; });
   out[0] = h.mf; out[1] = h.cg; out[2] = (int)h.mts;
 }
+extern "C" double wide(long rows, int E, int ntn) {
+  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, true, [](int) { return 4; });
+  return qdw::wide_time(rows, E, ntn) / h.time;
+}
 extern "C" void deal(double mts, int cg, int ntn, int grid, int *out) {
-  const qdp::PnDeal d = qdp::pn_deal(qdp::PnHeight{1, 2, cg, mts}, ntn, grid);
+  const qdp::PnDeal d = qdp::pn_deal(qdp::PnHeight{1, 2, cg, mts, 0.0}, ntn, grid);
   out[0] = d.cg; out[1] = d.nb; out[2] = d.nsp;
 }
 """
@@ -52,7 +57,9 @@ def host(tmp_path_factory):
                         "-fPIC", "-shared", "-I", CSRC, src, "-o", so],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
-    return ctypes.CDLL(so)
+    lib = ctypes.CDLL(so)
+    lib.wide.restype = ctypes.c_double
+    return lib
 
 
 @pytest.mark.parametrize("mf", [1, 2, 3, 5])
@@ -118,3 +125,20 @@ def test_tile_height_expects_the_tiles(host):
         host.height(ctypes.c_long(rows), E, 1, 0, _ptr(out))
         least = rows / (64 * out[0])
         assert least <= out[2] + 1 and out[2] <= least + E
+
+
+@pytest.mark.parametrize("rows,E,ntn,wide", [
+    (128 * 200, 128, 12, True),        # one tile of 256 rows each, nearly full
+    (64 * 225, 64, 3, True),
+    (128 * 100, 128, 12, True),
+    (64 * 90, 64, 12, True),
+    (64 * 110, 64, 3, False),          # one round, and a tall tile in it
+    (128 * 256, 128, 12, False),       # half of the experts need a second tile
+    (128 * 512, 128, 6, False),
+    (256, 1, 4, False),                # an idle chip: lower tiles, more of them
+    (13 * 256, 1, 16, True),
+    (14 * 256 + 1, 1, 20, False),
+])
+def test_wide_tiles_where_they_are_full(host, rows, E, ntn, wide):
+    assert (host.wide(ctypes.c_long(rows), E, ntn) < 0.9) == wide, \
+        host.wide(ctypes.c_long(rows), E, ntn)
