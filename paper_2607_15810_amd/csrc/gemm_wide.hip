@@ -467,8 +467,8 @@ void launch_one(const GemmArgs &p, const WdPlan &pl, hipStream_t s) {
 
 // Where the estimate is a tenth below the panel kernel's: over 373 calls without a
 // residual (1 to 128 experts, 50 to 5000 rows each) that takes 67, 9% slower at
-// worst and 20% faster at best; the choice is 0.9% from the faster of the two on
-// average, the panel kernel alone 2.8%.
+// worst and 25% faster at best; the choice is 0.9% from the faster of the two on
+// average, the panel kernel alone 2.5%.
 WdPlan wide_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, double panel_time) {
   WdPlan pl{};
   if (K < 2 * TW_K || K % (2 * TW_K) != 0 || N % TW_N != 0 || E > qdp::PN_EMAX) return pl;

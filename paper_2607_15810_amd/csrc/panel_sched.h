@@ -231,9 +231,10 @@ inline double pn_rounds(double mts, int ntn) {
 // against 104 with 192-row tiles).  64-row tiles on two workgroups per CU (two64:
 // they fit) take 0.78 of the time once there is more than a round of them (90
 // rows on each of 128 experts, K = 4096, 768 weight rows: 131 us against 150
-// with 128-row tiles, 160 one per CU), up to two tiles per expert (140 rows: 363
-// against 338 with the dense residual).  Over 426 calls of 50 to 800 rows on each
-// of 64 and 128 experts the choice is 0.6% from the best height on average.
+// with 128-row tiles, 160 one per CU), below two tiles per expert (128 rows on
+// each of 32, K = 2048, N = 1536: 69 us against 62 with 192-row tiles).  Over 426
+// calls of 50 to 800 rows on each of 64 and 128 experts the choice is 0.7% from
+// the best height on average.
 // ns_of(mf): the ring depth that height leaves room for (< 2: none).
 struct PnHeight {
   int mf, ns, cg;
@@ -256,7 +257,7 @@ inline PnHeight pn_height(int64_t rows, int E, int ntn, bool two64, F ns_of) {
     for (double j = j0; tall * j <= mean + 8.0 * sd; j += 1.0) n += pn_above(tall * j, mean, sd, E);
     n = std::max(n, 1.0 / E);
     double t = pn_rounds(n * E, ntn) * (PN_TILE + (mean / 32.0 + 0.5) / n);
-    if (mf == 1 && two64 && n * E * ntn > 256.0 && mean <= 128.0) t *= PN_TWO;
+    if (mf == 1 && two64 && n * E * ntn > 256.0 && mean <= 112.0) t *= PN_TWO;
     if (h.mf == 0 || t < 0.995 * best) {     // even: the lower, its ring is deeper
       best = t;
       // M-tiles dealt to the XCDs in the number an average expert has
