@@ -312,6 +312,10 @@ __global__ __launch_bounds__(64 * FW_WAVES) void gemm_few_kernel(GemmArgs p, int
 //    21.8; K = 4096, 12288 rows on two experts of 16 rows 52.0 against 34.3; one
 //    token on eight experts (u = 48) 10.4 against 20.8.  (Here and below weights
 //    that no cache holds, except for the token.)
+//  * Above the decode kernel's 48 rows per expert, against the panel kernel: one or
+//    two experts of K >= 2048 and a few blocks each, up to 64 rows (one expert, K =
+//    4096, N = 3072: 50 rows 40 against 59 us, 64 rows 46 against 59; two of 64, 52
+//    against 58; K = 1536, N = 4096: 64 rows 36 either way).
 //  * With the residual also u >= 320 (a second round with few units in it) at up
 //    to four rows per expert: K = 4096, N = 12288, 8 experts: 3 rows each 91
 //    against 98, 12 rows each 122 against 98; 128 experts with one row, N = 3072:
@@ -339,7 +343,8 @@ FwPlan few_plan(int64_t rows, int E, int64_t N, int64_t K, int Ks, int epilogue,
   if (K % 256 == 0) {
     const bool brief = K < 1024;
     const bool idle = p8 <= (brief ? 20 : 32) && u * p8 <= 8 * (Ks > 0 || brief ? 128 : 96);
-    if (!idle && !(Ks > 0 && u >= kFewSecond && rows <= 4 * act)) return pl;
+    const bool dense = rows > 48 * (int64_t)E && K >= 2048 && u <= 24 && p8 <= 68;
+    if (!idle && !dense && !(Ks > 0 && u >= kFewSecond && rows <= 4 * act)) return pl;
   } else {
     const bool panel = K >= 256 && K % 128 == 0 && N % 128 == 0;
     if (p8 > (panel ? 32 : K >= 1024 ? 20 : Ks > 0 ? 12 : 9)) return pl;

@@ -146,6 +146,7 @@ def test_few_row_kernel_by_rows_per_expert(lib):
     for E, N, K, Ks in ((8, 28672, 4096, 128), (8, 1536, 2048, 0), (16, 1536, 2048, 0)):
         assert cnt(128, N, K, E, Ks, 1) == cnt(136, N, K, E, Ks, 1)
     assert cnt(128, 96, 320, 1, 24, 0) == 3 * 2            # the generic kernel's grid
+    assert form(64, 3072, 4096, 1, 64, 1) == 1 and form(72, 3072, 4096, 1, 64, 1) == 2
     # one token on eight experts of 128; few rows at a K only the generic kernel takes
     assert cnt(8, 1536, 2048, 128, 64, 1) == 8 * 48
     assert cnt(64, 96, 320, 16, 24, 0) == 16 * 2
