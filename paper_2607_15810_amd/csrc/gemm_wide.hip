@@ -228,6 +228,11 @@ __global__ __launch_bounds__(TW_THREADS, 1) void gemm_wide_kernel(GemmArgs p, in
       if (e <= E) mpre[e] = base;
       base += cnt[q];
     }
+    // the end of 1024 experts is no thread's own entry
+    if (E == 4 * TW_THREADS && tid == TW_THREADS - 1) {
+      offs[E] = p.offsets[E];
+      mpre[E] = base;
+    }
   }
   const float a_dec = p.a_gs[1];
   __syncthreads();

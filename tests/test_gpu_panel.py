@@ -119,6 +119,26 @@ def test_panel_gemm_most_experts():
     check_close_bf16(np_bf16(out), ref, mag, "E = 1024")
 
 
+def test_wide_gemm_most_experts():
+    """E = 1024 on the tiles of 256 x 256, about 200 rows each: the bits of the
+    panel kernel, which weights without fragment-ordered scales take."""
+    E, K, N = 1024, 256, 256
+    rng = np.random.default_rng(17)
+    counts = rng.integers(190, 211, E)
+    counts[:2] = (255, 0)
+    counts[-1] = 256
+    offsets = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).to(DEV)
+    R = int(counts.sum())
+    g = torch.Generator(device=DEV).manual_seed(17)
+    x = torch.randn((R, K), generator=g, device=DEV).to(torch.bfloat16)
+    wb = (torch.randn((E, N, K), generator=g, device=DEV) * 0.02).to(torch.bfloat16)
+    xq, _, _ = ops.quantize_act(x)
+    out, amax = ops.grouped_gemm(xq, ops.quantize_weight(wb), R, None, offsets, want_amax=True)
+    ref, _ = ops.grouped_gemm(xq, ops.quantize_weight(wb, frag_scales=False), R, None, offsets)
+    assert torch.equal(out, ref)
+    assert amax.max().item() == ref.float().abs().max().item()
+
+
 @pytest.mark.parametrize("Ks", [24, 250], ids=["panel", "tile"])
 def test_panel_gemm_per_expert_sets(Ks):
     """One channel set per expert: the panel kernel, and above its largest

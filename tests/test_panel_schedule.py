@@ -138,6 +138,7 @@ def test_tile_height_expects_the_tiles(host):
     (256, 1, 4, False),                # an idle chip: lower tiles, more of them
     (13 * 256, 1, 16, True),
     (14 * 256 + 1, 1, 20, False),
+    (1024 * 200, 1024, 1, True),
 ])
 def test_wide_tiles_where_they_are_full(host, rows, E, ntn, wide):
     assert (host.wide(ctypes.c_long(rows), E, ntn) < 0.9) == wide, \
