@@ -269,6 +269,13 @@ int64_t   moe_w4a4_grouped_gemm_amax_count(int64_t rows, int64_t N, int64_t K, i
  * (with rq's tensor scale).  Pure host function, no error path. */
 int32_t   moe_w4a4_grouped_gemm_residual_form(int64_t rows, int64_t N, int64_t K, int32_t E,
                                               int32_t Ks, int32_t epilogue);
+/* the kernel that a call of these sizes runs (per_expert: of
+ * moe_w4a4_grouped_gemm_per_expert; frag_scales: w->scales_frag is given):
+ * "few", "decode", "wide", "panel", "tile" or "generic", NULL for sizes that are
+ * refused.  Pure host function, no error path. */
+const char *moe_w4a4_grouped_gemm_kernel(int64_t rows, int64_t N, int64_t K, int32_t E,
+                                         int32_t Ks, int32_t epilogue, int32_t per_expert,
+                                         int32_t frag_scales);
 qd_status moe_w4a4_grouped_gemm(const qd_nvfp4 *a, const int32_t *row_token,
                                 const int32_t *expert_offsets, int32_t E, int64_t rows,
                                 const qd_nvfp4 *w, const qd_nvfp4 *rq,

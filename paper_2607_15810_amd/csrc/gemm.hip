@@ -802,9 +802,12 @@ __global__ __launch_bounds__(SK_THREADS) void gemm_skinny_kernel(GemmArgs p, int
 }
 
 // ---------------------------------------------------------------------------
-// Grouped GEMM with per-expert channel sets whose compact table (256 weight
-// rows x K_s) leaves the panel kernel (gemm_panel.h) no room for its ring:
-// 128 weight rows per tile here hold tables of up to about 440 channels.
+// Grouped GEMM of up to a few hundred rows per expert whose panel-kernel tiles
+// (gemm_panel.h, 256 weight rows) would leave much of a round of the chip idle, and
+// of per-expert channel sets whose compact table leaves that kernel no room for its
+// ring: 128 weight rows per tile here, two workgroups per CU up to K_s = 144, hold
+// tables of up to about 440 channels.  What bounds it is the operand decode, as
+// there, with fewer MFMAs per decoded operand.
 //
 //  * Workgroup tile 256 rows x 128 weight rows (SwiGLU: 64 gate rows and
 //    the matching 64 up rows); four waves in a 2 x 2 grid, each 128 x 64 on
@@ -818,11 +821,11 @@ __global__ __launch_bounds__(SK_THREADS) void gemm_skinny_kernel(GemmArgs p, int
 //    offsets, and tile indices run contiguously within an XCD (workgroups
 //    are dealt to the eight XCDs in turn), so the tiles in flight on an
 //    XCD share an expert's weights or a block of activation rows in its L2.
-//  * K goes through a ring of TL_NS LDS slots of 64-element stages filled
-//    by direct global->LDS loads TL_NS - 1 stages ahead.  A wave reads a
+//  * K goes through a ring of NS LDS slots of 64-element stages (three beside a
+//    compact table, else four) filled by direct global->LDS loads NS - 1 stages ahead.  A wave reads a
 //    stage's raw codes and scales into registers one stage before it
 //    multiplies them: halfway through stage s it waits for stage s + 1, meets
-//    the other waves at a barrier, issues the loads of stage s + TL_NS - 1
+//    the other waves at a barrier, issues the loads of stage s + NS - 1
 //    into the slot of stage s - 1 (read during stage s - 2) and reads stage
 //    s + 1 while the MFMAs of stage s drain.
 //  * The residual: while a stage is in LDS the workgroup copies the selected
@@ -861,14 +864,19 @@ constexpr int TL_PAD = 4;                // f16 columns past each compact table 
 constexpr int TL_EMAX = 1024;            // experts handled by the tile scan (4 per thread)
 constexpr int TL_LDS_MAX = 160 * 1024 - 1024;   // dynamic LDS beside the static arrays
 
-constexpr int TL_NS = 3;                 // ring depth
+// ring depth: four slots, or three beside a compact table (cmp)
+__host__ __device__ constexpr int tl_ns(bool cmp) { return cmp ? 3 : 4; }
 // stage slot size and the B-scale offset inside it (grp: the A-scale ring is on)
-__host__ __device__ constexpr int tl_stage(bool grp) { return grp ? TL_STAGE_G : TL_STAGE; }
-__host__ __device__ constexpr int tl_bscl(bool grp) { return grp ? TL_BSCL_G : TL_BSCL; }
-// LDS: ring, then the compact weight table [128][ksa + TL_PAD] f16 and the
+__host__ __device__ constexpr int tl_slot(bool cmp, bool grp) {
+  return cmp && grp ? TL_STAGE_G : TL_STAGE;
+}
+__host__ __device__ constexpr int tl_bscl(bool cmp, bool grp) {
+  return cmp && grp ? TL_BSCL_G : TL_BSCL;
+}
+// LDS: ring, then (cmp) the compact weight table [128][ksa + TL_PAD] f16 and the
 // selected channels [ksa], then (grp) the A-scale ring
-__host__ __device__ inline int tl_lds_bytes(int ksa, bool grp) {
-  return TL_NS * tl_stage(grp) + TL_N * (ksa + TL_PAD) * 2 + ksa * 4;
+__host__ __device__ inline int tl_lds_bytes(bool cmp, int ksa, bool grp) {
+  return tl_ns(cmp) * tl_slot(cmp, grp) + (cmp ? TL_N * (ksa + TL_PAD) * 2 + ksa * 4 : 0);
 }
 constexpr int TL_AGRP = 2 * TL_M * 16;   // the A-scale ring: 2 slots x 256 rows x 16 B
 constexpr int TL_LDS_2WG = TL_LDS_MAX / 2;   // two workgroups per CU
@@ -943,9 +951,14 @@ __device__ __forceinline__ void tl_stage(const TlRaw &R, f32x16 (&acc)[4][2], in
   }
 }
 
-template <bool GATHER, int EPI>
+// the residual: none, the compact table, or a second pass over K with the masked
+// residual codes as the A operand
+enum { TL_PLAIN, TL_COMPACT, TL_DENSE };
+
+template <bool GATHER, int FORM, int EPI>
 __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, int ntn, int grp) {
-  constexpr int NS = TL_NS;
+  constexpr bool CMP = FORM == TL_COMPACT;
+  constexpr int NS = tl_ns(CMP);
   extern __shared__ __align__(16) unsigned char lds[];
   __shared__ int sh_w[4];
   __shared__ int sh_t[4];
@@ -983,25 +996,30 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
     const int bsstep = sfrag ? 64 : 4;
     const int nst = K / TL_K;
     // stage slots, and the A-scale ring (grp) after them and the compact table
-    const int tls = tl_stage(grp != 0), bsc = tl_bscl(grp != 0);
-    const uint32_t agrp = lds0 + (uint32_t)tl_lds_bytes(p.ksa, grp != 0);
+    const int tls = tl_slot(CMP, grp != 0), bsc = tl_bscl(CMP, grp != 0);
+    const uint32_t agrp = lds0 + (uint32_t)tl_lds_bytes(CMP, p.ksa, grp != 0);
     const uint32_t oag = arow(64 * w + lane) * (uint32_t)kb16;
-    // five loads per wave and stage, four between A-scale groups (waves 0 / 2
-    // and 1 / 3 load the same B scale half: equal bytes to equal places)
+    // five loads per wave and stage, with three slots four between A-scale groups
+    // (waves 0 / 2 and 1 / 3 load the same B scale half: equal bytes to equal places)
+    const uint8_t *a_cod = p.a_codes, *a_scl = p.a_scales;
     auto issue = [&](int s, int q) __attribute__((always_inline)) {
       s = min(s, nst - 1);
       const uint32_t sb = uni(lds0 + q * tls);
-      const uint8_t *ac = uni_ptr(p.a_codes + s * 32), *as_ = uni_ptr(p.a_scales + s * 4);
+      const uint8_t *ac = uni_ptr(a_cod + s * 32), *as_ = uni_ptr(a_scl + s * 4);
       const uint8_t *bc = uni_ptr(wc + s * 32), *bs_ = uni_ptr(ws + s * bsstep);
       dma16s(ac, oa0, sb + TL_ACODE + (2 * w) * 1024);
       dma16s(ac, oa1, sb + TL_ACODE + (2 * w + 1) * 1024);
       dma16s(bc, ob, sb + TL_BCODE + w * 1024);
       if (grp) {
         // stage 4G brings group G's A scales (rows 64 w .. 64 w + 63, 16 B
-        // each) into ring slot G % 2
+        // each) into ring slot G % 2; with four slots the other stages load one
+        // line of them into the unused A-scale area of their slot, so that the
+        // waits can count
         if ((s & 3) == 0)
-          dma16s(uni_ptr(p.a_scales + (s >> 2) * 16), oag,
+          dma16s(uni_ptr(a_scl + (s >> 2) * 16), oag,
                  uni(agrp + ((s >> 2) & 1) * (TL_AGRP / 2) + w * 1024));
+        else if constexpr (!CMP)
+          dma16s(uni_ptr(a_scl + (s >> 2) * 16), uni(oag), sb + TL_ASCL);
       } else {
         dma4s(as_, oas, sb + TL_ASCL + w * 256);
       }
@@ -1018,20 +1036,26 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
     // acc -> acc * inv_c + accr, then alpha = -s_dec_r * s_dec_w.  A residual
     // whose tensor scale is below 2^-60 of the activation's is left out (its
     // share of any output is far below f32 resolution).
-    const int ksa = p.ksa, ksp = ksa + TL_PAD;
+    const int ksa = CMP ? p.ksa : 0, ksp = ksa + TL_PAD;
     unsigned char *bres = lds + NS * tls;
     int32_t *sel_l = reinterpret_cast<int32_t *>(bres + TL_N * ksp * 2);
-    const float r_dec = p.r_gs[1];
-    const float inv_c = -(a_dec / r_dec);
-    const bool res_on = r_dec > 0.0f && fabsf(inv_c) <= 0x1p60f;
-    if (res_on) alpha = -r_dec * sw;
-    for (int i = tid; i < ksa; i += TL_THREADS)
-      sel_l[i] = i < p.Ks ? p.sel[(int64_t)e * p.sel_stride + i] : 0;
-    // pad columns of the compact table are zero (the residual's are too)
-    const int pad = ksa - p.Ks;
-    for (int i = tid; i < TL_N * pad; i += TL_THREADS)
-      *reinterpret_cast<_Float16 *>(bres + ((i / pad) * ksp + p.Ks + i % pad) * 2) =
-          (_Float16)0.0f;
+    float inv_c = 0.0f;
+    bool res_on = false;
+    if constexpr (FORM != TL_PLAIN) {
+      const float r_dec = p.r_gs[1];
+      inv_c = -(a_dec / r_dec);
+      res_on = r_dec > 0.0f && fabsf(inv_c) <= 0x1p60f;
+      if (res_on) alpha = -r_dec * sw;
+    }
+    if constexpr (CMP) {
+      for (int i = tid; i < ksa; i += TL_THREADS)
+        sel_l[i] = i < p.Ks ? p.sel[(int64_t)e * p.sel_stride + i] : 0;
+      // pad columns of the compact table are zero (the residual's are too)
+      const int pad = ksa - p.Ks;
+      for (int i = tid; i < TL_N * pad; i += TL_THREADS)
+        *reinterpret_cast<_Float16 *>(bres + ((i / pad) * ksp + p.Ks + i % pad) * 2) =
+            (_Float16)0.0f;
+    }
     const int wm = w & 1, wn = w >> 1;
     const bool wide = nrows > 128;
     const int fa0 = wide ? 4 * wm : 2 * wm;
@@ -1054,7 +1078,7 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
       // RAC: the tokens of this lane's residual rows, loaded before the K
       // loop so the residual steps after it wait for one load, not two
       int32_t tkr[MTV > 0 ? MTV : 1];
-      if constexpr (MTV > 0) {
+      if constexpr (CMP && MTV > 0) {
 #pragma unroll
         for (int i = 0; i < MTV; ++i) {
           const int rr = 32 * (fa0 + i) + (lane & 31);
@@ -1076,7 +1100,7 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
           if constexpr (MTV > 0)
             tl_read<MTV>(Rn, lds + ((s + 1) % NS) * tls, a_src(s + 1), astr, bsc, fa0, fb0, fbs,
                          lane);
-          {
+          if constexpr (CMP) {
             // selected channels of stage s (slot s % NS holds it until the
             // next barrier): decoded weight values into the compact table
             // (the hardware FP4 conversion with a power-of-two scale and one
@@ -1106,11 +1130,11 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
 #pragma unroll
         for (int t = 0; t < NS - 1; ++t) issue(t, t);
         // stage 0 has landed once at most stage NS - 2's loads are in flight
-        // (with the A-scale ring: stage 1 issues four)
-        if (grp) wait_vm<4>();
+        // (three slots with the A-scale ring: stage 1 issues four)
+        if (CMP && grp) wait_vm<4>();
         else wait_vm<(NS - 2) * 5>();
         __syncthreads();
-        nsel = nk < p.Ks ? (int)uni((uint32_t)sel_l[nk]) : 0x7fffffff;
+        if constexpr (CMP) nsel = nk < p.Ks ? (int)uni((uint32_t)sel_l[nk]) : 0x7fffffff;
         if constexpr (MTV > 0) tl_read<MTV>(R0, lds, a_src(0), astr, bsc, fa0, fb0, fbs, lane);
         for (int s = 0; s < nst; s += 2) {     // nst is even
           body(R0, R1, s);
@@ -1119,7 +1143,21 @@ __global__ __launch_bounds__(TL_THREADS, 2) void gemm_tile_kernel(GemmArgs p, in
         wait_vm<0>();
       };
       kpass();
-      {
+      if constexpr (FORM == TL_DENSE) {
+        if (res_on) {
+          __syncthreads();                     // every wave is done with the ring
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+              for (int q = 0; q < 16; ++q) acc[i][j][q] *= inv_c;
+          a_cod = p.r_codes;
+          a_scl = p.r_scales;
+          kpass();
+        }
+      }
+      if constexpr (CMP) {
         if (res_on) {
           __syncthreads();                     // the compact table is complete
           if constexpr (MTV > 0) {
@@ -1265,23 +1303,27 @@ void launch_skinny(const GemmArgs &p, const SkPlan &pl, hipStream_t s) {
 // host-side plan of the tile kernel
 struct TlPlan {
   bool ok;
-  int ntn, grid, lds, grp;
+  int form, ntn, grid, lds, grp;
+  double time;
 };
 
 // a_rows: rows of the activations, which row_token may name any of
-inline TlPlan tile_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, int Ks) {
+inline TlPlan tile_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, int Ks,
+                        int form) {
   TlPlan pl{};
-  if (Ks <= 0 || K < 4 * TL_K || K % (2 * TL_K) != 0 || N % TL_N != 0 || E > TL_EMAX) return pl;
+  pl.form = form;
+  const bool cmp = form == TL_COMPACT;
+  if (K < 4 * TL_K || K % (2 * TL_K) != 0 || N % TL_N != 0 || E > TL_EMAX) return pl;
   // byte offsets inside one activation matrix or one expert's weights, and
   // output offsets, fit 32 bits
   if (N * K / 2 >= (1LL << 32) || (std::max(rows, a_rows) + 1) * K / 2 >= (1LL << 32)) return pl;
   if ((rows + TL_M) * N * 2 >= (1LL << 32)) return pl;
-  const int ksa = (Ks + 15) / 16 * 16;
-  pl.lds = tl_lds_bytes(ksa, false);
+  const int ksa = cmp ? (Ks + 15) / 16 * 16 : 0;
+  pl.lds = tl_lds_bytes(cmp, ksa, false);
   if (pl.lds > TL_LDS_MAX) return pl;
   // the A-scale ring where it keeps the workgroups per CU (groups of four
   // stages: K a multiple of 256, so no group reads past a row's scales)
-  const int lg = tl_lds_bytes(ksa, true) + TL_AGRP;
+  const int lg = tl_lds_bytes(cmp, ksa, true) + TL_AGRP;
   if (K % 256 == 0 && ((pl.lds <= TL_LDS_2WG && lg <= TL_LDS_2WG) ||
                        (pl.lds > TL_LDS_2WG && lg <= TL_LDS_MAX))) {
     pl.lds = lg;
@@ -1291,17 +1333,22 @@ inline TlPlan tile_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t 
   const int64_t g = qdt::tile_grid(rows, E, TL_M, pl.ntn);
   if (g > 0x7fffffffLL) return pl;
   pl.grid = (int)g;
+  const double nst = (double)K / qdp::PN_K;
+  pl.time = qdp::tile_time(rows, E, pl.ntn, form == TL_DENSE ? 2 * nst : nst);
   pl.ok = true;
   return pl;
 }
 
-// The form of the residual outside the decode kernel: compact (rq_sel) while
-// two workgroups of the tile kernel's table and ring would fit a CU (K_s <=
-// 144), else the masked residual rq (the dense second pass).  The table costs
-// about 7% of the GEMM at K_s = 128, the second pass 100%, but a larger table
-// leaves the panel kernel's ring no room.
+// The form of the residual outside the decode kernel: compact (rq_sel) up to the
+// K_s whose table leaves the tile kernel two workgroups per CU, else the masked
+// residual rq (the dense second pass).  Callers learn the form from a query and
+// prepare what it names, so the line is where it has always been; the panel kernel
+// alone would cross over later (dense over compact time, 60 to 500 rows on each of
+// 64 and 128 experts, K = 2048 and 4096: 1.21 to 1.61 at K_s = 144, 1.17 to 1.58 at
+// 176, 0.92 to 1.6 at 192 and 0.65 to 1.28 at 208).
+constexpr int kCompactMax = 144;
 inline bool compact_form(int Ks) {
-  return Ks > 0 && tl_lds_bytes((Ks + 15) / 16 * 16, false) <= TL_LDS_2WG;
+  return Ks > 0 && Ks <= kCompactMax;
 }
 
 // host-side plan of the panel kernel
@@ -1334,7 +1381,8 @@ inline PnPlan panel_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t
   // two workgroups per CU for 64-row tiles: three stages each (two at K = 256)
   const int ns2 = std::min(3, nst);
   const bool two64 = qdp::pn_layout(1, ns2, ksa, E).total <= qdp::PN_LDS_2WG;
-  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, two64, [&](int mf) {
+  const double fixed = qdp::panel_fixed(pl.dense ? 2 * nst : nst);
+  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, fixed, two64, [&](int mf) {
     int ns = std::min(qdp::PN_NSMAX, nst);
     while (ns >= 2 && qdp::pn_layout(mf, ns, ksa, E).total > qdp::PN_LDS_MAX) --ns;
     return ns;
@@ -1369,9 +1417,9 @@ void launch_pn(const GemmArgs &p, int epi, const PnPlan &pl, hipStream_t s) {
   }
 }
 
-template <bool GATHER, int EPI>
-void launch_tile(const GemmArgs &p, const TlPlan &pl, hipStream_t s) {
-  auto kern = gemm_tile_kernel<GATHER, EPI>;
+template <bool GATHER, int FORM, int EPI>
+void launch_tile_one(const GemmArgs &p, const TlPlan &pl, hipStream_t s) {
+  auto kern = gemm_tile_kernel<GATHER, FORM, EPI>;
   static const bool attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                                hipFuncAttributeMaxDynamicSharedMemorySize,
                                                TL_LDS_MAX) == hipSuccess;
@@ -1380,11 +1428,18 @@ void launch_tile(const GemmArgs &p, const TlPlan &pl, hipStream_t s) {
                      pl.grp);
 }
 
+template <bool GATHER, int EPI>
+void launch_tile(const GemmArgs &p, const TlPlan &pl, hipStream_t s) {
+  if (pl.form == TL_COMPACT) launch_tile_one<GATHER, TL_COMPACT, EPI>(p, pl, s);
+  else if (pl.form == TL_DENSE) launch_tile_one<GATHER, TL_DENSE, EPI>(p, pl, s);
+  else launch_tile_one<GATHER, TL_PLAIN, EPI>(p, pl, s);
+}
+
 // The kernel of a grouped GEMM: the few-row kernel for a handful of rows, the
-// decode kernel for few rows per expert, the panel kernel above (the wide one
-// where no residual is fused and its tiles come out nearly full), the tile kernel
-// for per-expert sets whose table the panel kernel cannot hold, and the generic
-// kernel for sizes none takes.
+// decode kernel for few rows per expert, above that the panel, tile or wide kernel
+// (the last without a residual) by their estimated times, the tile kernel for
+// per-expert sets whose table the panel kernel cannot hold, and the generic kernel
+// for sizes none takes.
 enum class Kern { few, skinny, wide, panel, tile, generic };
 
 struct Choice {
@@ -1416,14 +1471,27 @@ inline Choice choose(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, 
   c.pn = panel_plan(rows, a_rows, E, N, K, Ks, per_expert);
   if (c.pn.ok) {
     c.k = Kern::panel;
+    double time = c.pn.time;
+    // The tile kernel for up to two rounds of its workgroups, where the panel
+    // kernel's 256 x 256 tiles fill a last round badly: 145 rows on each of 128
+    // experts, K = 2048, N = 768, K_s = 64: 97 us against 104 (384 tiles of 192
+    // rows in two rounds); 80 rows on each of 32, K = 4096, N = 3072, K_s = K / 2:
+    // 209 against 226; 32 x 30 rows, K = 640, N = 2048: 13.3 against 16.0.
+    c.tl = tile_plan(rows, a_rows, E, N, K, Ks,
+                     Ks <= 0 ? TL_PLAIN : c.pn.dense ? TL_DENSE : TL_COMPACT);
+    if (c.tl.ok && c.tl.lds <= TL_LDS_2WG && c.tl.time < time &&
+        qdp::tile_rounds(rows, E, c.tl.ntn) <= 2.1) {
+      c.k = Kern::tile;
+      time = c.tl.time;
+    }
     if (Ks <= 0 && sfrag) {
-      c.wd = qdw::wide_plan(rows, a_rows, E, N, K, c.pn.time);
-      if (c.wd.ok) c.k = Kern::wide;
+      c.wd = qdw::wide_plan(rows, a_rows, E, N, K);
+      if (c.wd.ok && c.wd.time < time) c.k = Kern::wide;
     }
     return c;
   }
   if (per_expert) {
-    c.tl = tile_plan(rows, a_rows, E, N, K, Ks);
+    c.tl = tile_plan(rows, a_rows, E, N, K, Ks, TL_COMPACT);
     if (c.tl.ok) c.k = Kern::tile;
   }
   return c;
@@ -1447,10 +1515,8 @@ void launch_epi(const GemmArgs &p, int epi, dim3 grid, hipStream_t s, const Choi
       launch_pn(p, epi, c.pn, s);
       return;
     case Kern::tile:
-      if constexpr (RAC) {
-        if (sw) launch_tile<GATHER, QD_EPI_SWIGLU>(p, c.tl, s);
-        else launch_tile<GATHER, QD_EPI_NONE>(p, c.tl, s);
-      }
+      if (sw) launch_tile<GATHER, QD_EPI_SWIGLU>(p, c.tl, s);
+      else launch_tile<GATHER, QD_EPI_NONE>(p, c.tl, s);
       return;
     default:
       if (sw)
@@ -1466,18 +1532,19 @@ bool qdi::gemm_wants_rq_sel(int64_t rows, int32_t E, int64_t N, int64_t K, int32
                             int32_t epilogue) {
   if (Ks <= 0 || rows <= 0 || E < 1 || N <= 0 || K <= 0) return false;
   const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, false, true);
-  return c.k == Kern::panel && !c.pn.dense;
+  return (c.k == Kern::panel || c.k == Kern::tile) && !c.pn.dense;
 }
 
 int64_t qdi::gemm_amax_written(int64_t rows, int32_t E, int64_t N, int64_t K, int32_t Ks,
-                               int32_t epilogue, bool bitmap) {
+                               int32_t epilogue, bool sfrag, bool bitmap) {
   if (rows <= 0 || E < 1 || N <= 0 || K <= 0 || Ks < 0) return 0;
-  // the grid of the kernel the grouped GEMM takes (of both that it may take: the
-  // wide one depends on the weights' scales)
-  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, bitmap, false, true);
+  // the grid of the kernel the grouped GEMM takes
+  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, bitmap, false, sfrag);
   if (c.k == Kern::few) return c.fw.grid;
   if (c.k == Kern::skinny) return c.sk.grid;
-  if (c.pn.ok) return std::max(c.pn.grid, c.wd.grid);
+  if (c.k == Kern::wide) return c.wd.grid;
+  if (c.k == Kern::panel) return c.pn.grid;
+  if (c.k == Kern::tile) return c.tl.grid;
   return grid_x(rows, E, true) * grid_y(N, epilogue);
 }
 
@@ -1494,6 +1561,20 @@ extern "C" int32_t moe_w4a4_grouped_gemm_residual_form(int64_t rows, int64_t N, 
   return qdi::gemm_wants_rq_sel(rows, E, N, K, Ks, epilogue) ? 2 : 1;
 }
 
+extern "C" const char *moe_w4a4_grouped_gemm_kernel(int64_t rows, int64_t N, int64_t K, int32_t E,
+                                                    int32_t Ks, int32_t epilogue,
+                                                    int32_t per_expert, int32_t frag_scales) {
+  if (rows <= 0 || E < 1 || N <= 0 || K <= 0 || Ks < (per_expert ? 1 : 0)) return nullptr;
+  switch (choose(rows, rows, E, N, K, Ks, epilogue, false, per_expert != 0, frag_scales != 0).k) {
+    case Kern::few: return "few";
+    case Kern::skinny: return "decode";
+    case Kern::wide: return "wide";
+    case Kern::panel: return "panel";
+    case Kern::tile: return "tile";
+    default: return per_expert ? nullptr : "generic";
+  }
+}
+
 extern "C" int64_t moe_w4a4_grouped_gemm_amax_count(int64_t rows, int64_t N, int64_t K,
                                                     int32_t E, int32_t Ks, int32_t epilogue) {
   if (rows < 0 || N <= 0 || K <= 0 || E < 1 || Ks < 0) return 0;
@@ -1501,7 +1582,7 @@ extern "C" int64_t moe_w4a4_grouped_gemm_amax_count(int64_t rows, int64_t N, int
   if (c.k == Kern::few) return c.fw.grid;
   if (c.k == Kern::skinny) return c.sk.grid;
   // every kernel writes (or zeroes) every entry, up to the largest grid
-  return std::max<int64_t>(std::max(c.pn.grid, c.wd.grid),
+  return std::max<int64_t>(std::max({c.pn.grid, c.wd.grid, c.tl.grid}),
                            grid_x(rows, E, true) * grid_y(N, epilogue));
 }
 
@@ -1641,7 +1722,7 @@ qd_status grouped_gemm_impl(const qd_nvfp4 *a, const int32_t *row_token,
                           : moe_w4a4_grouped_gemm_amax_count(rows, N, K, E, rac ? Ks : 0, epilogue);
   // the panel kernel takes the residual in its compact form unless its plan
   // is the dense second pass (which reads the masked residual rq)
-  if (rac && ((c.k == Kern::panel && !c.pn.dense) || c.k == Kern::tile) &&
+  if (rac && (c.k == Kern::panel || c.k == Kern::tile) && !c.pn.dense &&
       (!rq_sel || !qdh::aligned16(rq_sel)))
     return rq_sel ? QD_ERR_ALIGN : QD_ERR_NULL;
   dim3 grid((unsigned)gx, (unsigned)gy);

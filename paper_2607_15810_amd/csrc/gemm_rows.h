@@ -474,6 +474,8 @@ __global__ __launch_bounds__(PN_THREADS, 2) void gemm_rows_kernel(RowsArgs p, Pn
   wait_vm<0>();
 }
 
+constexpr double RW_TILE = 2.0;          // a tile's fixed time, in that of a 32-row fragment
+
 struct RowsPlan {
   bool ok;
   int mf, ns, grid, lds;
@@ -491,7 +493,7 @@ inline RowsPlan rows_plan(bool fp8, int64_t rows, int64_t a_rows, int E, int64_t
   if ((std::max(a_rows, rows) + 1) * kab >= lim || N * kwb >= lim || rows * 4 >= lim) return pl;
   const int nst = (int)(kab / 128);
   const int ntn = epilogue == QD_EPI_SWIGLU ? (int)((N / 2 + 127) / 128) : (int)((N + PN_N - 1) / PN_N);
-  const PnHeight h = pn_height(rows, E, ntn, false, [&](int mf) {
+  const PnHeight h = pn_height(rows, E, ntn, RW_TILE, false, [&](int mf) {
     int ns = std::min(5, nst);
     while (ns >= 2 && rw_layout(fp8, mf, ns, E).total > PN_LDS_MAX) --ns;
     return ns;

@@ -470,17 +470,18 @@ void launch_one(const GemmArgs &p, const WdPlan &pl, hipStream_t s) {
 
 }  // namespace
 
-// Where the estimate is a tenth below the panel kernel's: over 373 calls without a
-// residual (1 to 128 experts, 50 to 5000 rows each) that takes 67, 9% slower at
-// worst and 25% faster at best; the choice is 0.9% from the faster of the two on
-// average, the panel kernel alone 2.5%.
-WdPlan wide_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K, double panel_time) {
+// Short K is left out: a tile's start and epilogue run beside nothing here (K = 768,
+// N = 2048, 128 experts of 170 rows 109 us against 96 with the panel kernel, of 95
+// rows 67.7 against 68.8).
+constexpr int64_t TW_KMIN = 1024;
+
+WdPlan wide_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t K) {
   WdPlan pl{};
-  if (K < 2 * TW_K || K % (2 * TW_K) != 0 || N % TW_N != 0 || E > qdp::PN_EMAX) return pl;
+  if (K < TW_KMIN || K % (2 * TW_K) != 0 || N % TW_N != 0 || E > qdp::PN_EMAX) return pl;
   if (N * K / 2 >= (1LL << 32) || (std::max(rows, a_rows) + 1) * K / 2 >= (1LL << 32)) return pl;
   if ((rows + TW_M) * N * 2 >= (1LL << 32)) return pl;
   pl.ntn = (int)(N / TW_N);
-  if (wide_time(rows, E, pl.ntn) >= 0.9 * panel_time) return pl;
+  pl.time = wide_time(rows, E, pl.ntn, (double)K / TW_K);
   pl.lds = tw_lds_bytes(E);
   // persistent: one workgroup per CU, a multiple of 8 (the XCDs), at most the
   // tile count's upper bound

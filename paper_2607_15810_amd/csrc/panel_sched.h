@@ -18,7 +18,6 @@ constexpr int PN_THREADS = 512;
 constexpr int PN_N = 256;
 constexpr int PN_EMAX = 1024;
 constexpr int PN_NSMAX = 6;
-constexpr int PN_TILE = 2;               // a tile's fixed time, in that of a 32-row fragment
 constexpr int PN_LDS_MAX = 160 * 1024 - 512;   // dynamic LDS beside the static arrays
 constexpr int PN_LDS_2WG = 80 * 1024 - 512;    // the same for two workgroups per CU
 
@@ -222,6 +221,17 @@ inline double pn_rounds(double mts, int ntn) {
   return rounds(whole) * (1.0 - more) + rounds(whole + 1.0) * more;
 }
 
+// Expected tiles of `tall` rows that an expert has with more than `cut` rows in
+// them (cut 0: all of its tiles): those that all but the rarest experts fill, then
+// the tail.
+inline double pn_tiles(double mean, double sd, int E, double tall, double cut) {
+  const double j0 = std::max(0.0, std::floor((mean - 8.0 * sd) / tall));
+  double n = j0;
+  for (double j = j0; tall * j <= mean + 8.0 * sd; j += 1.0)
+    n += pn_above(tall * j + cut, mean, sd, E);
+  return n;
+}
+
 // The tile height with the least estimated time: whole rounds of the 256 CUs,
 // each the time of a tile of average height.  The expected number of tiles is
 // that of uniform routing (normal counts per expert).  One tile more may begin a
@@ -229,35 +239,29 @@ inline double pn_rounds(double mts, int ntn) {
 // each of 64 experts, 2048 weight rows: 128-row tiles make 512 tiles of them, two
 // rounds, in six of seven draws, and a third round for eight in the other: 125 us
 // against 104 with 192-row tiles).  64-row tiles on two workgroups per CU (two64:
-// they fit) take 0.78 of the time once there is more than a round of them (90
+// they fit) take 0.71 of the time once there is more than a round of them (90
 // rows on each of 128 experts, K = 4096, 768 weight rows: 131 us against 150
 // with 128-row tiles, 160 one per CU), below two tiles per expert (128 rows on
-// each of 32, K = 2048, N = 1536: 69 us against 62 with 192-row tiles).  Over 426
-// calls of 50 to 800 rows on each of 64 and 128 experts the choice is 0.7% from
-// the best height on average.
+// each of 32, K = 2048, N = 1536: 69 us against 62 with 192-row tiles).
+// fixed: a tile's fixed time, in that of a 32-row fragment.
 // ns_of(mf): the ring depth that height leaves room for (< 2: none).
 struct PnHeight {
   int mf, ns, cg;
   double mts;              // M-tiles expected
   double time;             // in that of a 32-row fragment of a tile
 };
-constexpr double PN_TWO = 0.78;
+constexpr double PN_TWO = 0.71;
 template <typename F>
-inline PnHeight pn_height(int64_t rows, int E, int ntn, bool two64, F ns_of) {
+inline PnHeight pn_height(int64_t rows, int E, int ntn, double fixed, bool two64, F ns_of) {
   PnHeight h{};
   const double mean = (double)rows / E, sd = std::max(0.5, sqrt(mean));
   double best = 0.0;
   for (const int mf : {1, 2, 3, 5}) {
     const int ns = ns_of(mf);
     if (ns < 2) continue;
-    const double tall = 64.0 * mf;
-    // the tiles that all but the rarest experts fill, then the tail
-    const double j0 = std::max(0.0, std::floor((mean - 8.0 * sd) / tall));
-    double n = j0;
-    for (double j = j0; tall * j <= mean + 8.0 * sd; j += 1.0) n += pn_above(tall * j, mean, sd, E);
-    n = std::max(n, 1.0 / E);
-    double t = pn_rounds(n * E, ntn) * (PN_TILE + (mean / 32.0 + 0.5) / n);
-    if (mf == 1 && two64 && n * E * ntn > 256.0 && mean <= 112.0) t *= PN_TWO;
+    const double n = std::max(pn_tiles(mean, sd, E, 64.0 * mf, 0.0), 1.0 / E);
+    double t = pn_rounds(n * E, ntn) * (fixed + (mean / 32.0 + 0.5) / n);
+    if (mf == 1 && two64 && n * E * ntn > 256.0 && mean <= 90.0) t *= PN_TWO;
     if (h.mf == 0 || t < 0.995 * best) {     // even: the lower, its ring is deeper
       best = t;
       // M-tiles dealt to the XCDs in the number an average expert has
@@ -265,6 +269,37 @@ inline PnHeight pn_height(int64_t rows, int E, int ntn, bool two64, F ns_of) {
     }
   }
   return h;
+}
+
+// Prices of the W4A4 kernels' tiles, in the time of one 32-row fragment through
+// one 128-element stage of K; nst: those stages (of both passes with the dense
+// residual).  Fitted to 706 GEMMs (1 to 128 experts of 4 to 3000 rows, K 384 to
+// 4096, N 768 to 8192, no residual, K_s = K / 32 and K / 2, each on every kernel and
+// tile height): the choice is 0.7% above the fastest on average, 14% at worst.
+// The panel kernel's fixed part is the decode of its weights and barriers of every
+// stage, and once per tile its start and epilogue.
+inline double panel_fixed(double nst) { return 4.4 + 6.0 / nst; }
+
+// The tile kernel: 256 x 128 tiles, each cut at 256 rows and priced by its fullest
+// 32, 64, 128 or 256, on 512 workgroups at a time.  A round of at most half of
+// them runs one per CU, the faster for it.
+inline double tile_time(int64_t rows, int E, int ntn, double nst) {
+  const double mean = (double)rows / E, sd = std::max(0.5, sqrt(mean));
+  const auto with = [&](double cut) { return pn_tiles(mean, sd, E, 256.0, cut); };
+  const double n = std::max(with(0.0), 1.0 / E);
+  const double price = (5.6 * n + 1.4 * with(32.0) + 1.3 * with(64.0) + 3.7 * with(128.0)) / n;
+  const auto rounds = [&](double mts) {
+    const double x = std::max(mts, 1.0) * ntn / 512.0, whole = std::floor(x), r = x - whole;
+    return whole + (r <= 0.0 ? 0.0 : r > 0.5 ? 1.0 : whole > 0.0 ? 0.6 : 0.68);
+  };
+  const double mts = n * E, whole = std::floor(mts + 0.02);
+  const double more = 1.0 - std::exp(std::min(0.0, whole - mts));
+  return (rounds(whole) * (1.0 - more) + rounds(whole + 1.0) * more) * (price + 1.8 / nst);
+}
+// rounds of its workgroups
+inline double tile_rounds(int64_t rows, int E, int ntn) {
+  const double mean = (double)rows / E, sd = std::max(0.5, sqrt(mean));
+  return pn_tiles(mean, sd, E, 256.0, 0.0) * E * ntn / 512.0;
 }
 
 // The deal of h's M-tiles over a grid of workgroups.  Whole M-tiles, as many

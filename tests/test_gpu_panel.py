@@ -1,6 +1,6 @@
-"""GPU parity of the grouped GEMM's panel kernel at the edges of its tiles:
-row counts around its 32-row fragments and around each tile height (64, 128,
-192, 320 rows), widths that are no multiple of its 256 weight rows, K of two
+"""GPU parity of the grouped GEMM's panel, tile and wide kernels at the edges of
+their tiles: row counts around its 32-row fragments and around each tile height (64, 128,
+192, 256, 320 rows), widths that are no multiple of 256 weight rows, K of two
 and three stages (three: no fragment-ordered scales), every form of the
 residual, and the largest expert count of its schedule.
 
@@ -49,13 +49,29 @@ CASES = [
     # and with the dense residual, and beside a table at K of two stages
     ("two_per_cu", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 384, 768, 0, False),
     ("two_per_cu_dense", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 384, 768, 200, True),
-    ("two_per_cu_long_k", [9, 33, 0, 64, 65, 1, 31, 32] * 25, 1024, 768, 0, True),
-    # tiles of 256 x 256 rows (no residual, K a multiple of 256): remainders of
+    ("two_per_cu_long_k", [63, 64, 49, 53, 64, 50, 64, 57] * 12, 1024, 768, 0, True),
+    # tiles of 256 x 256 rows (no residual, K a multiple of 256, 1024 or more): remainders of
     # one and two such tiles, half tiles, and counts far from the mean
-    ("wide_full", [255, 256, 250, 225] * 6, 512, 1536, 0, True),
-    ("wide_halves", [128, 127, 97, 64, 65, 96] * 4, 256, 1536, 0, False),
-    ("wide_uneven", [600, 0, 130, 129, 1, 512, 257, 200] * 3, 768, 1536, 0, True),
-    ("wide_one_expert", [13 * 256], 256, 4096, 0, False),
+    ("wide_full", [200, 190, 225, 180] * 4, 1024, 4096, 0, True),
+    ("wide_halves", [128, 127, 97, 64, 65, 96] * 4, 1024, 1536, 0, False),
+    ("wide_uneven", [600, 0, 130, 129, 1, 512, 257, 200] * 3, 1280, 1536, 0, True),
+    ("wide_one_expert", [13 * 256], 1024, 4096, 0, False),
+    # the panel kernel's heights on more than two rounds of the chip, which the
+    # tile kernel leaves to it
+    ("panel_around_64", [63, 64, 65, 70] * 30, 256, 1152, 24, True),
+    ("panel_around_128", [127, 128, 129, 97] * 25, 384, 1408, 40, True),
+    ("panel_around_192", [191, 192, 193, 129] * 24, 256, 1536, 8, True),
+    ("panel_around_320", [319, 320, 321, 289] * 12, 256, 1920, 16, True),
+    ("panel_one_expert", [6001], 256, 6016, 48, False),
+    ("panel_largest_table", [90, 70] * 50, 256, 1408, 144, True),
+    ("panel_dense", [150, 60, 100] * 32, 256, 1536, 200, True),
+    ("panel_dense_320", [300, 321] * 24, 256, 1920, 200, False),
+    ("panel_plain", [130, 97, 190, 200] * 25, 384, 1408, 0, True),
+    # the tile kernel's ring of four slots with the A-scale ring, two passes of it,
+    # and a table at K of no whole 256
+    ("tile_plain_k512", [128, 120, 257, 0, 60], 512, 256, 0, True),
+    ("tile_dense_k512", [100, 129, 33], 512, 256, 200, True),
+    ("tile_table_k640", [63, 97, 200], 640, 128, 100, False),
     ("two_per_cu_table", [63, 64, 49, 33, 64, 50, 64, 17] * 25, 256, 768, 24, True),
 ]
 
@@ -75,6 +91,11 @@ def test_panel_gemm(case, epi):
     tok = rng.integers(0, T, R).astype(np.int32) if gather else np.arange(R, dtype=np.int32)
     offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     w, W = ops.quantize_weight(wb.to(DEV)), oracle_bank(wb)
+    kind = Q.lib().moe_w4a4_grouped_gemm_kernel(R, N, K, E, Ks, epi, 0,
+                                                int(w.scales_frag is not None)).decode()
+    for k in ("panel", "tile", "wide"):
+        assert kind == k or not name.startswith(k)
+    assert kind == "panel" or not name.startswith("two_per_cu")
     xg = x.to(DEV)
     xq, scores, ramax = ops.quantize_act(xg, rac=True)
     act = OR.rac_activation(np_bf16(x), Ks)
@@ -122,7 +143,7 @@ def test_panel_gemm_most_experts():
 def test_wide_gemm_most_experts():
     """E = 1024 on the tiles of 256 x 256, about 200 rows each: the bits of the
     panel kernel, which weights without fragment-ordered scales take."""
-    E, K, N = 1024, 256, 256
+    E, K, N = 1024, 1024, 256
     rng = np.random.default_rng(17)
     counts = rng.integers(190, 211, E)
     counts[:2] = (255, 0)
@@ -133,17 +154,52 @@ def test_wide_gemm_most_experts():
     x = torch.randn((R, K), generator=g, device=DEV).to(torch.bfloat16)
     wb = (torch.randn((E, N, K), generator=g, device=DEV) * 0.02).to(torch.bfloat16)
     xq, _, _ = ops.quantize_act(x)
+    kernel = Q.lib().moe_w4a4_grouped_gemm_kernel
+    assert [kernel(R, N, K, E, 0, 0, 0, f) for f in (1, 0)] == [b"wide", b"panel"]
     out, amax = ops.grouped_gemm(xq, ops.quantize_weight(wb), R, None, offsets, want_amax=True)
     ref, _ = ops.grouped_gemm(xq, ops.quantize_weight(wb, frag_scales=False), R, None, offsets)
     assert torch.equal(out, ref)
     assert amax.max().item() == ref.float().abs().max().item()
 
 
-@pytest.mark.parametrize("Ks", [24, 250], ids=["panel", "tile"])
-def test_panel_gemm_per_expert_sets(Ks):
-    """One channel set per expert: the panel kernel, and above its largest
-    table the tile kernel."""
-    counts, K, N = [130, 0, 65, 33], 512, 256
+@pytest.mark.parametrize("Ks", [0, 48, 200], ids=["plain", "compact", "dense"])
+def test_panel_and_tile_kernels_agree(Ks):
+    """The rows of a few experts in a small call (tile kernel) and among those of
+    many (panel kernel): the same up to the order of the f32 sums, so within half a
+    bf16 ulp of nearly the same value."""
+    few, many, K, N = 4, 120, 512, 1536
+    rng = np.random.default_rng(23)
+    counts = rng.integers(100, 140, many)
+    n = int(counts[:few].sum())
+    offs = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).to(DEV)
+    R = int(counts.sum())
+    g = torch.Generator(device=DEV).manual_seed(23)
+    x = torch.randn((R, K), generator=g, device=DEV)
+    x[:, ::17] *= 20.0
+    x = x.to(torch.bfloat16)
+    w = ops.quantize_weight((torch.randn((many, N, K), generator=g, device=DEV) * 0.02)
+                            .to(torch.bfloat16), frag_scales=False)
+    v = ops.NVFP4Tensor(w.codes[:few], w.scales[:few], w.gscale[:few], few, N, K)
+    kernel = Q.lib().moe_w4a4_grouped_gemm_kernel
+    assert kernel(n, N, K, few, Ks, 0, 0, 0) == b"tile"
+    assert kernel(R, N, K, many, Ks, 0, 0, 0) == b"panel"
+    xq, scores, ramax = ops.quantize_act(x, rac=True)
+    sel = rq = None
+    if Ks:
+        sel, rq, _, _ = ops.select_channels(x, xq, Ks, scores, ramax)
+    a, _ = ops.grouped_gemm(xq, v, n, None, offs[:few + 1].contiguous(), rq, sel)
+    b, _ = ops.grouped_gemm(xq, w, R, None, offs, rq, sel)
+    a, b = a.double(), b[:n].double()
+    assert (a - b).norm() / b.norm() <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("Ks,n", [(24, 1), (250, 1), (24, 40)], ids=["tile", "tile_250", "panel"])
+def test_panel_gemm_per_expert_sets(Ks, n):
+    """One channel set per expert: the tile kernel, also above the panel kernel's
+    largest table, and the panel kernel."""
+    counts, K, N = [130, 0, 65, 33] * n, 512, 256 if n == 1 else 1152
+    assert Q.lib().moe_w4a4_grouped_gemm_kernel(sum(counts), N, K, len(counts), Ks, 0, 1, 1) == (
+        b"tile" if n == 1 else b"panel")
     E, R = len(counts), sum(counts)
     T = R // 2
     rng = np.random.default_rng(5)
@@ -189,7 +245,7 @@ def test_panel_gemm_many_rows_of_one_expert():
             assert torch.equal(out[r0:r0 + (1 << 20)], few[t]), f"{name}: rows {r0} on"
 
 
-@pytest.mark.parametrize("Ks", [0, 16, 160], ids=["plain", "compact", "dense"])
+@pytest.mark.parametrize("Ks", [0, 16, 200], ids=["plain", "compact", "dense"])
 def test_rows_past_4_gib_of_activations(Ks):
     """row_token names rows whose codes lie past 4 GiB of a larger matrix: what
     the same rows give on their own.  Two kernels, so two roundings of sums in

@@ -30,13 +30,16 @@ extern "C" void walk(int cg, int nb, int nsp, int mts, int *len, int *seen) {
     }
   }
 }
-extern "C" void height(long rows, int E, int ntn, int two64, int *out) {
-  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, two64 != 0, [](int) { return 4; });
+extern "C" void height(long rows, int E, int ntn, double nst, int two64, int *out) {
+  const qdp::PnHeight h =
+      qdp::pn_height(rows, E, ntn, qdp::panel_fixed(nst), two64 != 0, [](int) { return 4; });
   out[0] = h.mf; out[1] = h.cg; out[2] = (int)h.mts;
 }
-extern "C" double wide(long rows, int E, int ntn) {
-  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, true, [](int) { return 4; });
-  return qdw::wide_time(rows, E, ntn) / h.time;
+// times of the panel kernel, of the tile kernel (no residual) and of the wide one
+extern "C" void times(long rows, int E, int ntn, double nst, double *out) {
+  out[0] = qdp::pn_height(rows, E, ntn, qdp::panel_fixed(nst), true, [](int) { return 4; }).time;
+  out[1] = qdp::tile_time(rows, E, 2 * ntn, nst);
+  out[2] = qdw::wide_time(rows, E, ntn, nst);
 }
 extern "C" void deal(double mts, int cg, int ntn, int grid, int *out) {
   const qdp::PnDeal d = qdp::pn_deal(qdp::PnHeight{1, 2, cg, mts, 0.0}, ntn, grid);
@@ -58,7 +61,6 @@ def host(tmp_path_factory):
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     lib = ctypes.CDLL(so)
-    lib.wide.restype = ctypes.c_double
     return lib
 
 
@@ -103,17 +105,18 @@ def test_deal_covers_every_tile_evenly(host, ntn):
                 assert (c, nb) == (cg, ntn)
 
 
-@pytest.mark.parametrize("rows,E,ntn,two64,mf", [
-    (128 * 90, 128, 3, True, 1),       # two workgroups per CU on more than a round
-    (128 * 90, 128, 3, False, 2),      # one: taller tiles
-    (128 * 49, 128, 12, True, 1),
-    (64 * 100, 64, 8, False, 3),       # 512 tiles of 128 rows, if no expert has more
-    (128 * 512, 128, 6, True, 5),
-    (1, 1, 1, True, 1),
+@pytest.mark.parametrize("rows,E,ntn,nst,two64,mf", [
+    (128 * 90, 128, 3, 32, True, 1),       # two workgroups per CU on more than a round
+    (128 * 90, 128, 3, 32, False, 2),      # one: taller tiles
+    (128 * 49, 128, 12, 32, True, 1),
+    (64 * 100, 64, 8, 16, False, 3),       # 512 tiles of 128 rows, if no expert has more
+    (128 * 145, 128, 3, 16, False, 3),     # two rounds, where 128-row tiles make three
+    (128 * 512, 128, 6, 16, True, 5),
+    (1, 1, 1, 16, True, 1),
 ])
-def test_tile_height(host, rows, E, ntn, two64, mf):
+def test_tile_height(host, rows, E, ntn, nst, two64, mf):
     out = np.empty(3, np.int32)
-    host.height(ctypes.c_long(rows), E, ntn, int(two64), _ptr(out))
+    host.height(ctypes.c_long(rows), E, ntn, ctypes.c_double(nst), int(two64), _ptr(out))
     assert out[0] == mf
 
 
@@ -122,24 +125,26 @@ def test_tile_height_expects_the_tiles(host):
     steps."""
     out = np.empty(3, np.int32)
     for rows, E in ((1 << 24, 1), (1 << 24, 2), (1 << 22, 128)):
-        host.height(ctypes.c_long(rows), E, 1, 0, _ptr(out))
+        host.height(ctypes.c_long(rows), E, 1, ctypes.c_double(16), 0, _ptr(out))
         least = rows / (64 * out[0])
         assert least <= out[2] + 1 and out[2] <= least + E
 
 
-@pytest.mark.parametrize("rows,E,ntn,wide", [
-    (128 * 200, 128, 12, True),        # one tile of 256 rows each, nearly full
-    (64 * 225, 64, 3, True),
-    (128 * 100, 128, 12, True),
-    (64 * 90, 64, 12, True),
-    (64 * 110, 64, 3, False),          # one round, and a tall tile in it
-    (128 * 256, 128, 12, False),       # half of the experts need a second tile
-    (128 * 512, 128, 6, False),
-    (256, 1, 4, False),                # an idle chip: lower tiles, more of them
-    (13 * 256, 1, 16, True),
-    (14 * 256 + 1, 1, 20, False),
-    (1024 * 200, 1024, 1, True),
+@pytest.mark.parametrize("rows,E,ntn,nst,fastest", [
+    # measured fastest by 4% or more (us: panel, tile, wide kernel)
+    (128 * 80, 128, 12, 32, 2),        # 403, 412, 371
+    (64 * 80, 64, 3, 16, 2),           # 42, 38, 35
+    (64 * 80, 64, 12, 32, 2),          # 206, 210, 191
+    (128 * 125, 128, 6, 16, 0),
+    (128 * 512, 128, 6, 16, 0),        # half of the experts need a third tile of 256
+    (32 * 30, 32, 8, 5, 1),            # 16.0, 13.3
+    (16 * 80, 16, 8, 7, 1),            # a few tiles: twice as many of half the width
+    (256, 1, 4, 16, 0),                # an idle chip: lower tiles, more of them
+    (1024 * 200, 1024, 1, 8, 2),
 ])
-def test_wide_tiles_where_they_are_full(host, rows, E, ntn, wide):
-    assert (host.wide(ctypes.c_long(rows), E, ntn) < 0.9) == wide, \
-        host.wide(ctypes.c_long(rows), E, ntn)
+def test_fastest_kernel_by_estimate(host, rows, E, ntn, nst, fastest):
+    t = np.empty(3)
+    host.times(ctypes.c_long(rows), E, ntn, ctypes.c_double(nst), _ptr(t))
+    if nst % 2:
+        t[2] = np.inf                  # the wide kernel takes whole 256-element stages
+    assert int(np.argmin(t)) == fastest, t
