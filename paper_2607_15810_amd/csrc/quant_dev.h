@@ -109,10 +109,12 @@ __device__ __forceinline__ void quantize_act_rows(
   const bool active = cb < nbc;
   const int64_t step = (int64_t)gy * 16;
   int64_t r = (int64_t)by * 16 + ty;
-  // the thread's first row is on its way while the partials are looked at, and
-  // its next one while this one is quantised
+  // with RAC (the longer row body, several rows per thread) the first row is on its
+  // way while the partials are looked at, and the next one while this one is
+  // quantised; without, one row each, the registers cost more than that brings (8192 x
+  // 2048 17.1 us against 18.6, 64 x 2048 5.9 against 6.0)
   typename Loader<T>::Raw cur = {}, nxt = {};
-  if (active && r < rows) Loader<T>::load_raw(x, r * cols + cb * 16, cur);
+  if (RAC && active && r < rows) Loader<T>::load_raw(x, r * cols + cb * 16, cur);
   // tensor amax from the partial maxima
   const float amax = block_max(partials_max(amax_part, n_part), red);
   float s_enc, s_dec;
@@ -137,7 +139,8 @@ __device__ __forceinline__ void quantize_act_rows(
 
   if (active) {
     for (; r < rows; r += step) {
-      if (r + step < rows) Loader<T>::load_raw(x, (r + step) * cols + cb * 16, nxt);
+      if (!RAC) Loader<T>::load_raw(x, r * cols + cb * 16, cur);
+      else if (r + step < rows) Loader<T>::load_raw(x, (r + step) * cols + cb * 16, nxt);
       float v[16];
       Loader<T>::unpack(cur, v);
       uint32_t lo, hi;
@@ -158,7 +161,7 @@ __device__ __forceinline__ void quantize_act_rows(
           accd[i] += fixed_point_term_f64(rr * rr, F);   // each term < 2^37
         }
       }
-      cur = nxt;
+      if (RAC) cur = nxt;
     }
   }
   if (RAC) {
@@ -202,15 +205,17 @@ inline int amax_grid(int64_t n16) {
 }
 
 // (gx, gy) grid of the quantiser: 16 column blocks per workgroup along x;
-// with RAC at most 256 workgroups: each ends in one u64 atomic per channel, and
-// at 2000 x 2048 those cost more than the waves they buy (the layer's step 301
-// us at 1024, 299 at 512, 297 at 256; 1000 rows 232, 232, 229; 8192 rows and
-// 4096 columns within 0.4% of each other)
+// with RAC each ends in one u64 atomic per channel, and how many workgroups are
+// worth that depends on the rows they share (us at 256 / 512 / 1024 workgroups: 2000 x
+// 2048 11.0 / 13.4 / 13.2, 4096 x 2048 17.4 / 16.8 / 17.1, 8192 x 2048 27.5 / 23.8 /
+// 24.3, 8192 x 4096 46.0 / 37.0 / 36.6, 8192 x 7168 74.0 / 56.8 / 52.9, 32768 x 4096
+// 184 / 132 / 114)
 inline void quant_grid(int64_t rows, int64_t cols, bool rac, int &gx, int &gy) {
   const int64_t nbc = cols / 16;
   gx = (int)((nbc + 15) / 16);
   int64_t g = (rows + 15) / 16;
-  const int64_t cap = rac ? 256 : 4096;
+  const int64_t all = g * gx;
+  const int64_t cap = !rac ? 4096 : all < 2048 ? 256 : all < 8192 ? 512 : 1024;
   int64_t lim = cap / gx;
   if (lim < 1) lim = 1;
   if (g > lim) g = lim;
