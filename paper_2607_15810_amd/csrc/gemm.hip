@@ -1382,7 +1382,7 @@ inline PnPlan panel_plan(int64_t rows, int64_t a_rows, int E, int64_t N, int64_t
   const int ns2 = std::min(3, nst);
   const bool two64 = qdp::pn_layout(1, ns2, ksa, E).total <= qdp::PN_LDS_2WG;
   const double fixed = qdp::panel_fixed(pl.dense ? 2 * nst : nst);
-  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, fixed, two64, [&](int mf) {
+  const qdp::PnHeight h = qdp::pn_height(rows, E, ntn, fixed, false, two64, [&](int mf) {
     int ns = std::min(qdp::PN_NSMAX, nst);
     while (ns >= 2 && qdp::pn_layout(mf, ns, ksa, E).total > qdp::PN_LDS_MAX) --ns;
     return ns;

@@ -221,14 +221,35 @@ inline double pn_rounds(double mts, int ntn) {
   return rounds(whole) * (1.0 - more) + rounds(whole + 1.0) * more;
 }
 
+// The same where the M-tiles vary by sd about mts: few experts of a count near a
+// whole number of tiles may all need one more.
+inline double pn_rounds(double mts, double sd, int ntn) {
+  const auto rounds = [&](double m) { return std::max(1.0, std::ceil(m * ntn / 256.0)); };
+  if (sd < 0.15) return rounds(std::floor(mts + 0.5));
+  if (sd > 20.0) return rounds(mts);
+  const double last = std::ceil(mts + 3.0 * sd);
+  double t = 0.0, below = 0.0;
+  for (double m = std::max(1.0, std::floor(mts - 3.0 * sd)); m <= last; m += 1.0) {
+    const double upto = m < last ? 0.5 * erfc((mts - m - 0.5) / (sd * 1.4142135623730951)) : 1.0;
+    t += (upto - below) * rounds(m);
+    below = upto;
+  }
+  return t;
+}
+
 // Expected tiles of `tall` rows that an expert has with more than `cut` rows in
 // them (cut 0: all of its tiles): those that all but the rarest experts fill, then
-// the tail.
-inline double pn_tiles(double mean, double sd, int E, double tall, double cut) {
+// the tail.  *var: the variance of their number.
+inline double pn_tiles(double mean, double sd, int E, double tall, double cut,
+                       double *var = nullptr) {
   const double j0 = std::max(0.0, std::floor((mean - 8.0 * sd) / tall));
-  double n = j0;
-  for (double j = j0; tall * j <= mean + 8.0 * sd; j += 1.0)
-    n += pn_above(tall * j + cut, mean, sd, E);
+  double n = j0, v = 0.0;
+  for (double j = j0; tall * j <= mean + 8.0 * sd; j += 1.0) {
+    const double p = pn_above(tall * j + cut, mean, sd, E);
+    n += p;
+    v += p * (1.0 - p);
+  }
+  if (var) *var = v;
   return n;
 }
 
@@ -243,7 +264,8 @@ inline double pn_tiles(double mean, double sd, int E, double tall, double cut) {
 // rows on each of 128 experts, K = 4096, 768 weight rows: 131 us against 150
 // with 128-row tiles, 160 one per CU), below two tiles per expert (128 rows on
 // each of 32, K = 2048, N = 1536: 69 us against 62 with 192-row tiles).
-// fixed: a tile's fixed time, in that of a 32-row fragment.
+// fixed: a tile's fixed time, in that of a 32-row fragment; spread: rounds with the
+// spread of the tiles' number.
 // ns_of(mf): the ring depth that height leaves room for (< 2: none).
 struct PnHeight {
   int mf, ns, cg;
@@ -252,15 +274,18 @@ struct PnHeight {
 };
 constexpr double PN_TWO = 0.71;
 template <typename F>
-inline PnHeight pn_height(int64_t rows, int E, int ntn, double fixed, bool two64, F ns_of) {
+inline PnHeight pn_height(int64_t rows, int E, int ntn, double fixed, bool spread, bool two64,
+                          F ns_of) {
   PnHeight h{};
   const double mean = (double)rows / E, sd = std::max(0.5, sqrt(mean));
   double best = 0.0;
   for (const int mf : {1, 2, 3, 5}) {
     const int ns = ns_of(mf);
     if (ns < 2) continue;
-    const double n = std::max(pn_tiles(mean, sd, E, 64.0 * mf, 0.0), 1.0 / E);
-    double t = pn_rounds(n * E, ntn) * (fixed + (mean / 32.0 + 0.5) / n);
+    double var;
+    const double n = std::max(pn_tiles(mean, sd, E, 64.0 * mf, 0.0, &var), 1.0 / E);
+    const double r = spread ? pn_rounds(n * E, sqrt(var * E), ntn) : pn_rounds(n * E, ntn);
+    double t = r * (fixed + (mean / 32.0 + 0.5) / n);
     if (mf == 1 && two64 && n * E * ntn > 256.0 && mean <= 90.0) t *= PN_TWO;
     if (h.mf == 0 || t < 0.995 * best) {     // even: the lower, its ring is deeper
       best = t;

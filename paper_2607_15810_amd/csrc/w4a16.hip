@@ -8,8 +8,8 @@
 // a bf16 activation times it is exact in f32.  The tensor scale s_dec of the
 // expert multiplies the f32 sum in the epilogue.
 //
-// gemm_rows.h holds the kernel for all but the smallest K and the largest
-// operands.  The general kernel here: tiles of 128 grouped rows x 256 weight rows (SwiGLU: 128 gate rows
+// gemm_rows.h holds the kernel of most calls.  The general kernel here, for the
+// smallest K, the largest operands and up to two rounds of full tiles: tiles of 128 grouped rows x 256 weight rows (SwiGLU: 128 gate rows
 // and the matching 128 up rows), eight waves in a 2 x 4 grid of 64 x 64 on
 // v_mfma_f32_32x32x16_bf16; the wide weight tile halves how often the bf16
 // activations are re-read (once per weight tile).  K streams in stages of 64 through a double
@@ -213,6 +213,22 @@ __global__ __launch_bounds__(WA_THREADS) void gemm_w4a16_kernel(W16Args p, int n
   }
 }
 
+// Whether this kernel's tiles, 128 rows at one price (in the time of one 32-row
+// fragment of the rows kernel), beat the rows kernel's.  They do on up to two rounds
+// of the chip that they fill: 32 experts of 100 rows, K = 2048, N = 1536, SwiGLU: 42
+// us against 52; 128 of 100, K = 4096, N = 768: 148 against 172; one expert of 1400,
+// K = N = 4096: 71 against 87.  In more rounds the rows kernel's persistent walk
+// is ahead again (64 of 50, K = 4096, N = 3072: 271 against 236).
+inline bool general_faster(int64_t rows, int E, int64_t N, int64_t K, int epilogue, double time) {
+  const int ntn = (int)(epilogue == QD_EPI_SWIGLU ? (N / 2 + 127) / 128 : (N + WA_N - 1) / WA_N);
+  const double mean = (double)rows / E, sd = std::max(0.5, sqrt(mean));
+  double var;
+  const double n =
+      std::max(qdp::pn_tiles(mean, sd, E, (double)WA_M, 0.0, &var), 1.0 / E) * E;
+  if (n * ntn > 2.1 * 256.0) return false;
+  return qdp::pn_rounds(n, sqrt(var * E), ntn) * (8.2 + 12.0 * WA_K / K) < time;
+}
+
 }  // namespace
 
 extern "C" qd_status moe_w4a16_grouped_gemm(const void *a, int64_t a_rows,
@@ -235,11 +251,11 @@ extern "C" qd_status moe_w4a16_grouped_gemm(const void *a, int64_t a_rows,
   if (!qdh::aligned16(a) || !qdh::aligned16(out) || !qdh::aligned16(w->codes))
     return QD_ERR_ALIGN;
   if (qdh::fault_injected()) return QD_ERR_HIP;
-  // the rows kernel wherever its stages and offsets reach (it is the faster one
-  // from 1 row per expert, 42 -> 33 us, to hundreds, 345 -> 239); its scale loads
-  // are 4 bytes wide
+  // the rows kernel where its stages and offsets reach (from 1 row per expert, 42 ->
+  // 33 us, to hundreds, 345 -> 239), unless the general kernel's estimate is lower;
+  // its scale loads are 4 bytes wide
   const qdr::RowsPlan pl = qdr::rows_plan(false, rows, a_rows, E, N, K, epilogue);
-  if (pl.ok && (reinterpret_cast<uintptr_t>(w->scales) & 3) == 0) {
+  if (pl.ok && !general_faster(rows, E, N, K, epilogue, pl.time) && (reinterpret_cast<uintptr_t>(w->scales) & 3) == 0) {
     qdr::RowsArgs r{};
     r.a = static_cast<const uint8_t *>(a);
     r.row_token = row_token;

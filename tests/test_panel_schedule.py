@@ -32,14 +32,22 @@ extern "C" void walk(int cg, int nb, int nsp, int mts, int *len, int *seen) {
 }
 extern "C" void height(long rows, int E, int ntn, double nst, int two64, int *out) {
   const qdp::PnHeight h =
-      qdp::pn_height(rows, E, ntn, qdp::panel_fixed(nst), two64 != 0, [](int) { return 4; });
+      qdp::pn_height(rows, E, ntn, qdp::panel_fixed(nst), false, two64 != 0,
+                     [](int) { return 4; });
   out[0] = h.mf; out[1] = h.cg; out[2] = (int)h.mts;
 }
 // times of the panel kernel, of the tile kernel (no residual) and of the wide one
 extern "C" void times(long rows, int E, int ntn, double nst, double *out) {
-  out[0] = qdp::pn_height(rows, E, ntn, qdp::panel_fixed(nst), true, [](int) { return 4; }).time;
+  out[0] = qdp::pn_height(rows, E, ntn, qdp::panel_fixed(nst), false, true,
+                          [](int) { return 4; }).time;
   out[1] = qdp::tile_time(rows, E, 2 * ntn, nst);
   out[2] = qdw::wide_time(rows, E, ntn, nst);
+}
+extern "C" int spread_height(long rows, int E, int ntn, double fixed) {
+  return qdp::pn_height(rows, E, ntn, fixed, true, false, [](int) { return 4; }).mf;
+}
+extern "C" double spread_rounds(double mts, double sd, int ntn) {
+  return qdp::pn_rounds(mts, sd, ntn);
 }
 extern "C" void deal(double mts, int cg, int ntn, int grid, int *out) {
   const qdp::PnDeal d = qdp::pn_deal(qdp::PnHeight{1, 2, cg, mts, 0.0}, ntn, grid);
@@ -61,6 +69,7 @@ def host(tmp_path_factory):
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
     lib = ctypes.CDLL(so)
+    lib.spread_rounds.restype = ctypes.c_double
     return lib
 
 
@@ -148,3 +157,23 @@ def test_fastest_kernel_by_estimate(host, rows, E, ntn, nst, fastest):
     if nst % 2:
         t[2] = np.inf                  # the wide kernel takes whole 256-element stages
     assert int(np.argmin(t)) == fastest, t
+
+
+@pytest.mark.parametrize("rows,E,ntn,fixed,mf", [
+    (8 * 264, 8, 12, 2.0, 3),          # 128-row tiles: 192 to 288 of them for 256 CUs
+    (64 * 260, 64, 3, 2.0, 5),
+    (128 * 512, 128, 6, 2.0, 5),
+    (128 * 4, 128, 6, 7.0, 1),
+])
+def test_rows_height_with_the_spread(host, rows, E, ntn, fixed, mf):
+    assert host.spread_height(ctypes.c_long(rows), E, ntn, ctypes.c_double(fixed)) == mf
+
+
+def test_rounds_with_the_spread(host):
+    """The expected rounds of a normal number of M-tiles, by sampling."""
+    rng = np.random.default_rng(3)
+    for mts, sd, ntn in ((20.0, 1.4, 12), (85.0, 3.0, 3), (40.3, 0.5, 6), (128.0, 0.0, 6)):
+        m = np.maximum(np.rint(mts + sd * rng.standard_normal(200_000)), 1)
+        ref = np.maximum(np.ceil(m * ntn / 256), 1).mean()
+        got = host.spread_rounds(ctypes.c_double(mts), ctypes.c_double(sd), ntn)
+        assert abs(got - ref) < 0.02, (mts, sd, ntn, got, ref)
