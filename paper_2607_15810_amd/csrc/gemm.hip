@@ -1565,11 +1565,17 @@ extern "C" const char *moe_w4a4_grouped_gemm_kernel(int64_t rows, int64_t N, int
                                                     int32_t Ks, int32_t epilogue,
                                                     int32_t per_expert, int32_t frag_scales) {
   if (rows <= 0 || E < 1 || N <= 0 || K <= 0 || Ks < (per_expert ? 1 : 0)) return nullptr;
-  switch (choose(rows, rows, E, N, K, Ks, epilogue, false, per_expert != 0, frag_scales != 0).k) {
+  const Choice c = choose(rows, rows, E, N, K, Ks, epilogue, false, per_expert != 0,
+                          frag_scales != 0);
+  switch (c.k) {
     case Kern::few: return "few";
     case Kern::skinny: return "decode";
     case Kern::wide: return "wide";
-    case Kern::panel: return "panel";
+    case Kern::panel:
+      return c.pn.mf == 5   ? "panel320"
+             : c.pn.mf == 3 ? "panel192"
+             : c.pn.mf == 2 ? "panel128"
+                            : "panel64";
     case Kern::tile: return "tile";
     default: return per_expert ? nullptr : "generic";
   }

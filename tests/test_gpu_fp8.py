@@ -61,9 +61,10 @@ def test_fp8_quantize_rows_exact():
 
 
 FP8_CASES = [
-    # name, T, H, E, k, I, kwargs -- few rows per expert (32-row passes) and many
+    # name, T, H, E, k, I, kwargs -- few rows per expert (16: 32-row passes at H = 256;
+    # 48: the rows kernel) and many
     ("decode", 64, 256, 8, 2, 256, {}),
-    ("decode_zipf_passes", 96, 512, 8, 4, 256, dict(routing="zipf")),
+    ("decode_zipf", 96, 512, 8, 4, 256, dict(routing="zipf")),
     ("prefill", 512, 256, 4, 2, 256, {}),
     ("prefill_ragged", 300, 512, 4, 2, 256, dict(routing="zipf")),
 ]

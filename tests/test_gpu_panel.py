@@ -58,15 +58,15 @@ CASES = [
     ("wide_one_expert", [13 * 256], 1024, 4096, 0, False),
     # the panel kernel's heights on more than two rounds of the chip, which the
     # tile kernel leaves to it
-    ("panel_around_64", [63, 64, 65, 70] * 30, 256, 1152, 24, True),
-    ("panel_around_128", [127, 128, 129, 97] * 25, 384, 1408, 40, True),
-    ("panel_around_192", [191, 192, 193, 129] * 24, 256, 1536, 8, True),
-    ("panel_around_320", [319, 320, 321, 289] * 12, 256, 1920, 16, True),
-    ("panel_one_expert", [6001], 256, 6016, 48, False),
-    ("panel_largest_table", [90, 70] * 50, 256, 1408, 144, True),
-    ("panel_dense", [150, 60, 100] * 32, 256, 1536, 200, True),
-    ("panel_dense_320", [300, 321] * 24, 256, 1920, 200, False),
-    ("panel_plain", [130, 97, 190, 200] * 25, 384, 1408, 0, True),
+    ("panel64_edges", [63, 64, 65, 70] * 30, 256, 1152, 24, True),
+    ("panel128_edges", [127, 128, 129, 97] * 25, 384, 1408, 40, True),
+    ("panel192_edges", [191, 192, 193, 129] * 24, 256, 1536, 8, True),
+    ("panel320_edges", [319, 320, 321, 289] * 12, 256, 1920, 16, True),
+    ("panel320_one_expert", [6001], 256, 6016, 48, False),
+    ("panel128_largest_table", [90, 70] * 50, 256, 1408, 144, True),
+    ("panel128_dense", [150, 60, 100] * 32, 256, 1536, 200, True),
+    ("panel320_dense", [300, 321] * 24, 256, 1920, 200, False),
+    ("panel192_plain", [130, 97, 190, 200] * 25, 384, 1408, 0, True),
     # the tile kernel's ring of four slots with the A-scale ring, two passes of it,
     # and a table at K of no whole 256
     ("tile_plain_k512", [128, 120, 257, 0, 60], 512, 256, 0, True),
@@ -93,9 +93,9 @@ def test_panel_gemm(case, epi):
     w, W = ops.quantize_weight(wb.to(DEV)), oracle_bank(wb)
     kind = Q.lib().moe_w4a4_grouped_gemm_kernel(R, N, K, E, Ks, epi, 0,
                                                 int(w.scales_frag is not None)).decode()
-    for k in ("panel", "tile", "wide"):
+    for k in ("panel64", "panel128", "panel192", "panel320", "tile", "wide"):
         assert kind == k or not name.startswith(k)
-    assert kind == "panel" or not name.startswith("two_per_cu")
+    assert kind == "panel64" or not name.startswith("two_per_cu")
     xg = x.to(DEV)
     xq, scores, ramax = ops.quantize_act(xg, rac=True)
     act = OR.rac_activation(np_bf16(x), Ks)
@@ -155,7 +155,7 @@ def test_wide_gemm_most_experts():
     wb = (torch.randn((E, N, K), generator=g, device=DEV) * 0.02).to(torch.bfloat16)
     xq, _, _ = ops.quantize_act(x)
     kernel = Q.lib().moe_w4a4_grouped_gemm_kernel
-    assert [kernel(R, N, K, E, 0, 0, 0, f) for f in (1, 0)] == [b"wide", b"panel"]
+    assert [kernel(R, N, K, E, 0, 0, 0, f) for f in (1, 0)] == [b"wide", b"panel320"]
     out, amax = ops.grouped_gemm(xq, ops.quantize_weight(wb), R, None, offsets, want_amax=True)
     ref, _ = ops.grouped_gemm(xq, ops.quantize_weight(wb, frag_scales=False), R, None, offsets)
     assert torch.equal(out, ref)
@@ -182,7 +182,7 @@ def test_panel_and_tile_kernels_agree(Ks):
     v = ops.NVFP4Tensor(w.codes[:few], w.scales[:few], w.gscale[:few], few, N, K)
     kernel = Q.lib().moe_w4a4_grouped_gemm_kernel
     assert kernel(n, N, K, few, Ks, 0, 0, 0) == b"tile"
-    assert kernel(R, N, K, many, Ks, 0, 0, 0) == b"panel"
+    assert kernel(R, N, K, many, Ks, 0, 0, 0).startswith(b"panel")
     xq, scores, ramax = ops.quantize_act(x, rac=True)
     sel = rq = None
     if Ks:
@@ -198,8 +198,8 @@ def test_panel_gemm_per_expert_sets(Ks, n):
     """One channel set per expert: the tile kernel, also above the panel kernel's
     largest table, and the panel kernel."""
     counts, K, N = [130, 0, 65, 33] * n, 512, 256 if n == 1 else 1152
-    assert Q.lib().moe_w4a4_grouped_gemm_kernel(sum(counts), N, K, len(counts), Ks, 0, 1, 1) == (
-        b"tile" if n == 1 else b"panel")
+    kind = Q.lib().moe_w4a4_grouped_gemm_kernel(sum(counts), N, K, len(counts), Ks, 0, 1, 1)
+    assert kind.startswith(b"tile" if n == 1 else b"panel")
     E, R = len(counts), sum(counts)
     T = R // 2
     rng = np.random.default_rng(5)

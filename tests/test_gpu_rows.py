@@ -67,6 +67,7 @@ W4A16 = [
     ("one_expert", [333], 384, 256, False),
     ("one_row", [1], 768, 256, False),
     ("one_stage", [40, 90], 64, 256, True),             # K of one stage: the other kernel
+    ("full_tiles", [100, 128, 64, 1], 2048, 256, True), # full tiles in one round: the other one
 ]
 
 
@@ -103,6 +104,59 @@ def test_w4a16_order_of_sums(case, epi):
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
 
 
+def _height_case(mean):
+    """128 experts of about `mean` rows each, N = 1536, K = 256: the tile height
+    follows the mean (test_panel_schedule.py); counts around it, among them none, one
+    row and a tile of every other height."""
+    E, K, N = 128, 256, 1536
+    rng = np.random.default_rng(mean)
+    counts = rng.integers(mean - 6, mean + 7, E)
+    counts[[3, 40, 90, 127]] = (0, 1, 2 * mean, mean + mean - 1)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    R = int(offsets[-1])
+    T = R // 4
+    tok = rng.integers(0, T, R).astype(np.int32)
+    g = torch.Generator().manual_seed(mean)
+    x = torch.randn((T, K), generator=g)
+    x[:, ::29] *= 20.0
+    wb = (torch.randn((E, N, K), generator=g) * 0.02).to(torch.bfloat16)
+    return E, K, N, R, counts, offsets, tok, x.to(torch.bfloat16), wb
+
+
+@pytest.mark.parametrize("epi", EPIS, ids=["plain", "swiglu"])
+@pytest.mark.parametrize("mean", [30, 88, 145, 250])
+def test_w4a16_heights(mean, epi):
+    """Every tile height on several rounds of the chip: the general kernel's bits."""
+    E, K, N, R, _, offsets, tok, x, wb = _height_case(mean)
+    w, xg = ops.quantize_weight(wb.to(DEV)), x.to(DEV)
+    tg, og = torch.from_numpy(tok).to(DEV), torch.from_numpy(offsets).to(DEV)
+    outs = []
+    for a_rows in (len(x), 2 ** 32 // (2 * K) + 1):
+        out = torch.empty((R, N // 2 if epi else N), dtype=torch.bfloat16, device=DEV)
+        Q.call("moe_w4a16_grouped_gemm", xg.data_ptr(), a_rows, tg.data_ptr(), og.data_ptr(), E, R,
+               ops._nv(w), epi, out.data_ptr(), ops._stream())
+        outs.append(out)
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
+@pytest.mark.parametrize("epi", EPIS, ids=["plain", "swiglu"])
+@pytest.mark.parametrize("mean", [30, 88, 145, 250])
+def test_fp8_heights(mean, epi):
+    """The same for FP8, against the oracle on six of the experts."""
+    E, K, N, R, counts, offsets, tok, x, wb = _height_case(mean)
+    ac, ad = ops.fp8_quantize_rows(x.to(DEV))
+    wc, wd = ops.fp8_quantize_rows(wb.to(DEV))
+    out = np_bf16(ops.fp8_grouped_gemm(ac, ad, wc, wd, R, torch.from_numpy(tok).to(DEV),
+                                       torch.from_numpy(offsets).to(DEV), epi))
+    pick = [0, 40, 64, 90, 101, 127]
+    rows = np.concatenate([np.arange(offsets[e], offsets[e + 1]) for e in pick])
+    offs = np.concatenate([[0], np.cumsum(counts[pick])]).astype(np.int32)
+    bank = OF.quantize_bank(wb[pick].float().numpy())
+    gu, mag = OF.grouped_gemm(*OF.quantize_rows(np_bf16(x)), tok[rows], offs, bank)
+    ref, mag = _reference(gu, mag, epi)
+    check_close_bf16(out[rows], ref, mag, f"{mean} rows per expert", floor=2.0 ** -13)
+
+
 def test_w4a16_swiglu_range():
     """The SwiGLU epilogue over gates from deep underflow to overflow, zero and
     the non-finite ones (its first 32 rows hold moderate gates only): one weight of 6
@@ -130,7 +184,8 @@ def test_w4a16_swiglu_range():
 
 
 FP8 = [
-    # name, rows per expert, K, N, gathered rows (above 48 rows per expert on average)
+    # name, rows per expert, K, N, gathered rows (above 48 rows per expert on average, but
+    # for the last)
     ("two_stages", [1, 131, 32, 133, 0, 95], 256, 256, True),
     ("odd_stages", [63, 64, 65, 0, 90], 384, 256, False),
     ("around_128", [127, 128, 129, 97], 512, 768, True),
@@ -139,6 +194,12 @@ FP8 = [
     ("two_tiles", [640, 641, 1, 330], 256, 512, True),
     ("one_expert", [333], 384, 256, False),
     ("half_stage", [100, 90], 320, 256, True),          # K of whole and a half: the other kernel
+    # the other kernel's passes of 32 rows: K of whole and a half stages, a short K and
+    # few tiles, and a long K
+    ("passes_half_stage", [1, 31, 32, 33, 0, 48], 320, 256, True),
+    ("passes_short_k", [1, 16, 0, 33, 5], 384, 512, False),
+    ("passes_few_tiles", [31, 0, 1, 9], 1024, 768, True),
+    ("passes_long_k", [1, 16, 31, 0, 9], 4096, 256, True),
 ]
 
 

@@ -159,6 +159,17 @@ def test_fastest_kernel_by_estimate(host, rows, E, ntn, nst, fastest):
     assert int(np.argmin(t)) == fastest, t
 
 
+# test_gpu_rows.py's calls of each height: rows per expert on 128 experts, N = 1536
+ROWS_HEIGHTS = [(30, 1), (88, 2), (145, 3), (250, 5)]
+
+
+@pytest.mark.parametrize("fixed", [2.0, 7.0], ids=["fp8", "w4a16"])
+@pytest.mark.parametrize("mean,mf", ROWS_HEIGHTS)
+def test_rows_height(host, mean, mf, fixed):
+    for rows in (128 * mean - 60, 128 * mean + 60):
+        assert host.spread_height(ctypes.c_long(rows), 128, 6, ctypes.c_double(fixed)) == mf
+
+
 @pytest.mark.parametrize("rows,E,ntn,fixed,mf", [
     (8 * 264, 8, 12, 2.0, 3),          # 128-row tiles: 192 to 288 of them for 256 CUs
     (64 * 260, 64, 3, 2.0, 5),
