@@ -73,8 +73,12 @@ def parse():
     return ap.parse_args()
 
 
+# the W4A4 GEMM kernels and every header they include
 GEMM_SRCS = [os.path.join(ROOT, "paper_2607_15810_amd", "csrc", f)
-             for f in ("gemm.hip", "gemm_panel.h", "panel_sched.h", "gemm_args.h")]
+             for f in ("gemm.hip", "gemm_args.h", "gemm_few.h", "gemm_few.hip", "gemm_panel.h",
+                       "gemm_panel_1.hip", "gemm_panel_2.hip", "gemm_panel_3.hip",
+                       "gemm_panel_5.hip", "gemm_wide.h", "gemm_wide.hip", "panel_sched.h",
+                       "tile_sched.h", "lds_dma.h", "common.h")]
 PROFILES = os.path.join(ROOT, "profiles")
 
 
@@ -114,6 +118,15 @@ def copy_only(nbytes):
         b.copy_(a)
     torch.cuda.synchronize()
     print(json.dumps({"copy_bytes": n * 4, "launches": 5}))
+
+
+def w13_kernel(wl):
+    """The kernel of the workload's W13 launch, as the library names it."""
+    from paper_2607_15810_amd import quads as Q
+    k = Q.lib().moe_w4a4_grouped_gemm_kernel(wl.T * wl.k, 2 * wl.I, wl.H, wl.E, wl.Ks,
+                                             Q.QD_EPI_SWIGLU, 0, 1).decode()
+    return {"few": "gemm_few_kernel", "decode": "gemm_skinny_kernel", "wide": "gemm_wide_kernel",
+            "tile": "gemm_tile_kernel", "generic": "gemm_w4a4_kernel"}.get(k, "gemm_panel_kernel")
 
 
 def algorithmic(wl, counts):
@@ -329,10 +342,7 @@ def measure(args, name, ceil, headline):
     step_tflops = alg["step_flops"] / (ms_step * 1e-3) / 1e12
     w13_ms = stage_ms[Q.STAGE_NAMES.index("w13")]
     decode = name in DECODE
-    # the W13 launch runs the decode kernel on the decode workloads (few rows per
-    # expert), the panel kernel on the others
-    kname = ("gemm_skinny_kernel" if decode else "gemm_panel_kernel") + \
-        " (W13 + fused RAC residual + SwiGLU)"
+    kname = w13_kernel(wl) + " (W13 + fused RAC residual + SwiGLU)"
     traffic = measured_traffic(name)
     if decode:
         achieved = alg["w13_bytes"] / (w13_ms * 1e-3) / 1e9

@@ -822,20 +822,21 @@ __global__ __launch_bounds__(SK_THREADS) void gemm_skinny_kernel(GemmArgs p, int
 //    are dealt to the eight XCDs in turn), so the tiles in flight on an
 //    XCD share an expert's weights or a block of activation rows in its L2.
 //  * K goes through a ring of NS LDS slots of 64-element stages (three beside a
-//    compact table, else four) filled by direct global->LDS loads NS - 1 stages ahead.  A wave reads a
-//    stage's raw codes and scales into registers one stage before it
-//    multiplies them: halfway through stage s it waits for stage s + 1, meets
-//    the other waves at a barrier, issues the loads of stage s + NS - 1
+//    compact table, else four) filled by direct global->LDS loads NS - 1 stages
+//    ahead.  A wave reads a stage's raw codes and scales into registers one stage
+//    before it multiplies them: halfway through stage s it waits for stage s + 1,
+//    meets the other waves at a barrier, issues the loads of stage s + NS - 1
 //    into the slot of stage s - 1 (read during stage s - 2) and reads stage
 //    s + 1 while the MFMAs of stage s drain.
-//  * The residual: while a stage is in LDS the workgroup copies the selected
+//  * The residual, compact form: while a stage is in LDS the workgroup copies the selected
 //    channels of its weight rows out of it, decoded to f16, into the compact
 //    table; after the K loop the accumulators are rescaled by
 //    -s_dec_x / s_dec_r and the residual (compacted per row, f16, from the
 //    caller) is multiplied onto them against that table, so the epilogue's
 //    single scale -s_dec_r * s_dec_w yields
 //    s_dec_x s_dec_w acc - s_dec_r s_dec_w accr with one extra f32 rounding
-//    of the main sum.
+//    of the main sum.  Dense form: a second pass over K with the masked residual
+//    as the A operand, after the same rescale.
 //
 // Stage slot: A codes [8 fragments][64 lanes][16 B], B codes [4 fragments]
 // likewise, then A scale dwords [256 rows] and B scale dwords [128 rows].
@@ -844,8 +845,9 @@ __global__ __launch_bounds__(SK_THREADS) void gemm_skinny_kernel(GemmArgs p, int
 // fragment-ordered copy when present (64 contiguous bytes per 16 rows), and
 // where LDS allows (grp), the A scales of four stages at a time (16 contiguous
 // bytes per row, one load per 16-byte piece) go into a two-slot ring of their
-// own; the stages between those loads issue none, the wait before each stage
-// covering every outstanding load, and the stage slot drops its A-scale area.
+// own; beside a table the stages between those loads issue none, the wait before
+// each stage covering every outstanding load, and the stage slot drops its A-scale
+// area.
 // Lane l of a fragment holds row l % 32, elements 32 (l / 32) .. +31 of the
 // stage; MFMA k-step s (0..3) takes elements 8s .. 8s+7 of each half, for A
 // and B alike.

@@ -312,10 +312,11 @@ __global__ __launch_bounds__(64 * FW_WAVES) void gemm_few_kernel(GemmArgs p, int
 //    21.8; K = 4096, 12288 rows on two experts of 16 rows 52.0 against 34.3; one
 //    token on eight experts (u = 48) 10.4 against 20.8.  (Here and below weights
 //    that no cache holds, except for the token.)
-//  * Above the decode kernel's 48 rows per expert, against the panel kernel: one or
-//    two experts of K >= 2048 and a few blocks each, up to 64 rows (one expert, K =
-//    4096, N = 3072: 50 rows 40 against 59 us, 64 rows 46 against 59; two of 64, 52
-//    against 58; K = 1536, N = 4096: 64 rows 36 either way).
+//  * Above the decode kernel's 48 rows per expert, against the tile and panel
+//    kernels: one or two experts of K >= 2048 and a few blocks each, up to 64 rows
+//    (two experts of 64, K = 4096, N = 3072: 43 against 55 us, with K_s = 128 50
+//    against 55, K / 2 50 against 88; one of 64, K = 2048, N = 1536: 27 against 32,
+//    with K_s = 64 30 either way; K = 1536, N = 4096: 64 rows 36 either way).
 //  * With the residual also u >= 320 (a second round with few units in it) at up
 //    to four rows per expert: K = 4096, N = 12288, 8 experts: 3 rows each 91
 //    against 98, 12 rows each 122 against 98; 128 experts with one row, N = 3072:

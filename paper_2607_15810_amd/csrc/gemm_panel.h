@@ -14,11 +14,14 @@
 //    of a few rows costs the fragments it has, not a second pass over the
 //    weights with nearly empty tiles.
 //  * Persistent: one workgroup per CU (two with short rings of 64-row tiles)
-//    walks a static list of tiles, experts of tall tiles first, so that the last, partial round of the chip holds the
-//    smallest ones.  An M-tile's weight-row tiles (and the M-tiles of an expert
+//    walks a static list of tiles, experts of tall tiles first, so that the last,
+//    partial round of the chip holds the smallest ones.  An M-tile's weight-row tiles (and the M-tiles of an expert
 //    that has several) go to one XCD, where they share activation rows (and
-//    weights) in its L2.  The stages of all its tiles form one stream through an LDS ring of NS
-//    slots, so the loads of the next tile run under the end of this one.
+//    weights) in its L2.  The stages of all its tiles form one stream through an
+//    LDS ring of NS slots, so the loads of the next tile run under the end of this
+//    one.  (At 320 rows the kernel spills nine registers, 40 bytes of scratch per
+//    lane; their reload before the epilogue waits for the loads in flight too, so
+//    there they run under the last stages but not under the epilogue.)
 //  * A stage is 128 K-elements of the tile's rows, codes and scales of both
 //    operands, filled by direct global->LDS loads (16 rows x 64 contiguous
 //    bytes each, the 16-byte pieces of a row placed by a row-dependent XOR, so

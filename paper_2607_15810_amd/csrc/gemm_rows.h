@@ -7,7 +7,9 @@
 //    each up to 32 MF rows x 64 weight rows of 32 x 32 fragments.  The tile
 //    schedule is the NVFP4 panel kernel's (panel_sched.h): equal tiles to one
 //    32-row fragment, experts of tall tiles first, one persistent workgroup per
-//    CU, the stages of all its tiles one stream through an LDS ring.
+//    CU, the stages of all its tiles one stream through an LDS ring.  (FP8 at 320
+//    rows spills nine registers: the reload before the epilogue waits for the loads
+//    in flight.)
 //  * A stage is 128 bytes of each activation row (64 bf16 or 128 FP8 elements)
 //    and the same elements of the weight rows, filled by direct global->LDS
 //    loads of whole 128-byte lines.  The 16-byte pieces of a row are placed by a
