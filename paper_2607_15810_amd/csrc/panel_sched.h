@@ -256,14 +256,13 @@ inline double pn_tiles(double mean, double sd, int E, double tall, double cut,
 // The tile height with the least estimated time: whole rounds of the 256 CUs,
 // each the time of a tile of average height.  The expected number of tiles is
 // that of uniform routing (normal counts per expert).  One tile more may begin a
-// round (100 +- 10 rows on
-// each of 64 experts, 2048 weight rows: 128-row tiles make 512 tiles of them, two
-// rounds, in six of seven draws, and a third round for eight in the other: 125 us
-// against 104 with 192-row tiles).  64-row tiles on two workgroups per CU (two64:
-// they fit) take 0.71 of the time once there is more than a round of them (90
-// rows on each of 128 experts, K = 4096, 768 weight rows: 131 us against 150
-// with 128-row tiles, 160 one per CU), below two tiles per expert (128 rows on
-// each of 32, K = 2048, N = 1536: 69 us against 62 with 192-row tiles).
+// round (100 +- 10 rows on each of 64 experts, 2048 weight rows: 128-row tiles make
+// 512 tiles of them, two rounds, in six of seven draws, and a third round for eight
+// in the other: 125 us against 104 with 192-row tiles).  64-row tiles on two
+// workgroups per CU (two64: they fit) take 0.74 of the time once there is more than a
+// round of them, as long as they hold an average expert (56 rows on each of 128
+// experts, K = 4096, 768 weight rows: 86 us against 109 with the wide kernel; 80 rows,
+// K = 2048 twice: 120 against 111 with the tile kernel).
 // fixed: a tile's fixed time, in that of a 32-row fragment; spread: rounds with the
 // spread of the tiles' number.
 // ns_of(mf): the ring depth that height leaves room for (< 2: none).
@@ -272,7 +271,7 @@ struct PnHeight {
   double mts;              // M-tiles expected
   double time;             // in that of a 32-row fragment of a tile
 };
-constexpr double PN_TWO = 0.71;
+constexpr double PN_TWO = 0.74;
 template <typename F>
 inline PnHeight pn_height(int64_t rows, int E, int ntn, double fixed, bool spread, bool two64,
                           F ns_of) {
@@ -286,7 +285,7 @@ inline PnHeight pn_height(int64_t rows, int E, int ntn, double fixed, bool sprea
     const double n = std::max(pn_tiles(mean, sd, E, 64.0 * mf, 0.0, &var), 1.0 / E);
     const double r = spread ? pn_rounds(n * E, sqrt(var * E), ntn) : pn_rounds(n * E, ntn);
     double t = r * (fixed + (mean / 32.0 + 0.5) / n);
-    if (mf == 1 && two64 && n * E * ntn > 256.0 && mean <= 90.0) t *= PN_TWO;
+    if (mf == 1 && two64 && n * E * ntn > 256.0 && mean <= 64.0) t *= PN_TWO;
     if (h.mf == 0 || t < 0.995 * best) {     // even: the lower, its ring is deeper
       best = t;
       // M-tiles dealt to the XCDs in the number an average expert has

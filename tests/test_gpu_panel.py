@@ -58,7 +58,7 @@ CASES = [
     ("wide_one_expert", [13 * 256], 1024, 4096, 0, False),
     # the panel kernel's heights on more than two rounds of the chip, which the
     # tile kernel leaves to it
-    ("panel64_edges", [63, 64, 65, 70] * 30, 256, 1152, 24, True),
+    ("panel64_edges", [63, 64, 65, 49] * 30, 256, 1152, 24, True),
     ("panel128_edges", [127, 128, 129, 97] * 25, 384, 1408, 40, True),
     ("panel192_edges", [191, 192, 193, 129] * 24, 256, 1536, 8, True),
     ("panel320_edges", [319, 320, 321, 289] * 12, 256, 1920, 16, True),

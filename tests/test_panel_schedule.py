@@ -115,8 +115,9 @@ def test_deal_covers_every_tile_evenly(host, ntn):
 
 
 @pytest.mark.parametrize("rows,E,ntn,nst,two64,mf", [
-    (128 * 90, 128, 3, 32, True, 1),       # two workgroups per CU on more than a round
-    (128 * 90, 128, 3, 32, False, 2),      # one: taller tiles
+    (128 * 56, 128, 3, 32, True, 1),       # two workgroups per CU on more than a round
+    (128 * 90, 128, 3, 32, True, 2),       # more than one such tile per expert: taller ones
+    (128 * 90, 128, 3, 32, False, 2),
     (128 * 49, 128, 12, 32, True, 1),
     (64 * 100, 64, 8, 16, False, 3),       # 512 tiles of 128 rows, if no expert has more
     (128 * 145, 128, 3, 16, False, 3),     # two rounds, where 128-row tiles make three
