@@ -206,16 +206,16 @@ inline int amax_grid(int64_t n16) {
 
 // (gx, gy) grid of the quantiser: 16 column blocks per workgroup along x;
 // with RAC each ends in one u64 atomic per channel, and how many workgroups are
-// worth that depends on the rows they share (us at 256 / 512 / 1024 workgroups: 2000 x
-// 2048 11.0 / 13.4 / 13.2, 4096 x 2048 17.4 / 16.8 / 17.1, 8192 x 2048 27.5 / 23.8 /
-// 24.3, 8192 x 4096 46.0 / 37.0 / 36.6, 8192 x 7168 74.0 / 56.8 / 52.9, 32768 x 4096
-// 184 / 132 / 114)
+// worth that depends on the rows they share (us at 256 / 512 / 1024 workgroups: 2000
+// x 2048 11.0 / 13.4 / 13.2, 4096 x 1536 16.3 / 14.0 / 14.6, 4096 x 2048 17.4 / 16.8 /
+// 17.1, 8192 x 2048 27.5 / 23.8 / 24.3, 8192 x 4096 46.0 / 37.0 / 36.6, 8192 x 7168 74.0
+// / 56.8 / 52.9, 32768 x 4096 184 / 132 / 114)
 inline void quant_grid(int64_t rows, int64_t cols, bool rac, int &gx, int &gy) {
   const int64_t nbc = cols / 16;
   gx = (int)((nbc + 15) / 16);
   int64_t g = (rows + 15) / 16;
   const int64_t all = g * gx;
-  const int64_t cap = !rac ? 4096 : all < 2048 ? 256 : all < 8192 ? 512 : 1024;
+  const int64_t cap = !rac ? 4096 : all < 1536 ? 256 : all < 8192 ? 512 : 1024;
   int64_t lim = cap / gx;
   if (lim < 1) lim = 1;
   if (g > lim) g = lim;
