@@ -391,12 +391,13 @@ __global__ __launch_bounds__(F8_THREADS, 2) void gemm_fp8_kernel(Fp8Args p, int 
 
 // The rows kernel (gemm_rows.h) takes whole 128-byte stages.  The 32-row passes
 // stay ahead of it only for weights streamed once along a long K (64 experts of
-// 3072 x 4096, at most 16 rows each: 149 us against 164; at 37 rows each 255
-// against 160; 128 experts of 1536 x 2048, 16 rows each: 83 against 77).
+// 3072 x 4096, at most 16 rows each: 149 us against 164, 17 rows 157 against 179, 24
+// rows 195 against 173; 128 experts of 1536 x 2048, 16 rows each: 83 against 77).
 // A short K or a few tiles make a call that is mostly its start, which is shorter
 // there too: 64 experts of 4 rows, K = 384, N = 2048: 14.2 us against 15.6; 4 of 4, K =
 // 2048, N = 1536: 13.8 against 15.1.
 constexpr int64_t F8_PASS_ROWS = 16, F8_PASS_K = 4096, F8_SHORT_K = 512, F8_FEW_TILES = 64;
+constexpr int64_t F8_MANY_ROWS = 20, F8_MANY_TILES = 512;
 
 // Elsewhere (K of an odd number of 64-element stages): rows per expert above
 // which the 256-row tiles replace the 32-row passes
@@ -495,8 +496,11 @@ extern "C" qd_status moe_fp8_grouped_gemm(const uint8_t *a_codes, const float *a
   if (qdh::fault_injected()) return QD_ERR_HIP;
   if (rows == 0) return QD_OK;
   const qdr::RowsPlan rp = qdr::rows_plan(true, rows, a_rows, E, N, K, epilogue);
-  const bool passes = rows <= (int64_t)E * F8_PASS_ROWS &&
-                      (K >= F8_PASS_K || K < F8_SHORT_K || E * (N / 256) <= F8_FEW_TILES);
+  const int64_t tiles = E * (N / 256);
+  const bool passes =
+      (rows <= (int64_t)E * F8_PASS_ROWS &&
+       (K >= F8_PASS_K || K < F8_SHORT_K || tiles <= F8_FEW_TILES)) ||
+      (rows <= (int64_t)E * F8_MANY_ROWS && K >= F8_PASS_K && tiles >= F8_MANY_TILES);
   if (rp.ok && !passes) {
     qdr::RowsArgs r{};
     r.a = a_codes;
