@@ -272,7 +272,9 @@ int32_t   moe_w4a4_grouped_gemm_residual_form(int64_t rows, int64_t N, int64_t K
 /* the kernel that a call of these sizes runs (per_expert: of
  * moe_w4a4_grouped_gemm_per_expert; frag_scales: w->scales_frag is given):
  * "few", "decode", "wide", "panel64", "panel128", "panel192", "panel320" (the rows
- * of its tiles), "tile" or "generic", NULL for sizes that are refused.  Pure host function, no error path. */
+ * of its tiles), "tile" or "generic"; NULL for an empty call, and for per-expert
+ * sizes that are refused.  Activations past 4 GiB of codes are not considered.
+ * Pure host function, no error path. */
 const char *moe_w4a4_grouped_gemm_kernel(int64_t rows, int64_t N, int64_t K, int32_t E,
                                          int32_t Ks, int32_t epilogue, int32_t per_expert,
                                          int32_t frag_scales);
