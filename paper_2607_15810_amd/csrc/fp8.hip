@@ -11,8 +11,8 @@
 // GEMM: v_mfma_scale_f32_32x32x64_f8f6f4 with both block scales 1.0 (the
 // f8f6f4 path, twice the f16 MFMA rate), K = 64 per instruction.  gemm_rows.h
 // holds the kernel of most sizes; the one here serves a K of an odd number of
-// 64-element stages and a few rows per expert along a long K: M-tiles inside one
-// expert, tile indices contiguous per XCD, a ring of 64-element stages filled
+// 64-element stages, and a few rows per expert along a long or a very short K or over
+// a few tiles: M-tiles inside one expert, tile indices contiguous per XCD, a ring of 64-element stages filled
 // by direct global->LDS loads (six per wave and stage), operands read a stage
 // ahead.
 //  * TM = 256 (many rows per expert): tile 256 x 128 weight rows, 2 x 2 waves
